@@ -129,19 +129,15 @@ __device__ __forceinline__ void store_v(float *p, typename VecOf<VW>::T v) {
 // loads; 1: tiered, a column tagged cold (bit 31 set by the plan) is loaded
 // non-temporally so it is inserted for early eviction and the hot columns'
 // rows stay in L2; 2: every gather non-temporal.
-// TIERED = false compiles the plain load only (the choice of load is an
-// instruction bit, so a run-time policy costs a second load per slot).
-template <int VW, bool TIERED>
+// The choice of load is an instruction bit, so a run-time policy costs a second
+// load per slot; only the merge path has one.
+template <int VW>
 __device__ __forceinline__ typename VecOf<VW>::T gather_b(const float *__restrict__ Bl, int32_t raw, int32_t n,
                                                           int policy) {
   using V = typename VecOf<VW>::T;
-  if constexpr (!TIERED) {
-    return load_v<VW>(Bl + (int64_t)raw * n);
-  } else {
-    const float *p = Bl + (int64_t)(raw & 0x7fffffff) * n;
-    if (policy == 2 || (policy == 1 && raw < 0)) return __builtin_nontemporal_load(reinterpret_cast<const V *>(p));
-    return load_v<VW>(p);
-  }
+  const float *p = Bl + (int64_t)(raw & 0x7fffffff) * n;
+  if (policy == 2 || (policy == 1 && raw < 0)) return __builtin_nontemporal_load(reinterpret_cast<const V *>(p));
+  return load_v<VW>(p);
 }
 
 // Loads the (column, value) tile of nonzeros [p, p + min(G, p1 - p)): lane
@@ -164,18 +160,16 @@ __device__ __forceinline__ void load_tile(const int32_t *__restrict__ colidx, co
 // acc += sum over p in [p0, p1) of vals[p] * B[colidx[p], lane columns].
 // (c, v) already holds the tile at p0 (from load_tile).  All G lanes of a
 // group call this with the same p0, p1 (group-uniform control flow), so every
-// ds_bpermute source lane is active.  Software pipeline: the next tile is
-// requested before the current tile's gathers, and the gathers run in
-// batches of UNR with two register buffers, so batch k+1 is in flight while
-// batch k is multiplied in.  Slots past the range end issue no load.
-template <int G, int VW, bool PIPE = true, bool TIERED = true>
+// ds_bpermute source lane is active.  One batch of up to 8 gathers in flight
+// and no prefetch of the next tile: a second batch or tile raises the register
+// count past 6 waves per SIMD, which costs more than it hides.
+template <int G, int VW>
 __device__ __forceinline__ void gather_rows(const int32_t *__restrict__ colidx, const float *__restrict__ vals,
                                             int32_t p0, int32_t p1, int32_t c, float v,
                                             const float *__restrict__ Bl, int32_t n, bool col_ok,
-                                            typename VecOf<VW>::T &acc, int glane, int gbase, int policy) {
+                                            typename VecOf<VW>::T &acc, int glane, int gbase) {
   using V = typename VecOf<VW>::T;
-  if constexpr (!PIPE && G > 1) {
-    // lean variant (no prefetch, one buffer) for kernels held to 64 VGPRs
+  if constexpr (G > 1) {
     constexpr int UNR = G < 8 ? G : 8;
     for (int32_t p = p0; p < p1; p += G) {
       const int32_t cnt = min(G, p1 - p);
@@ -195,64 +189,21 @@ __device__ __forceinline__ void gather_rows(const int32_t *__restrict__ colidx, 
         }
         __builtin_amdgcn_sched_barrier(0);  // broadcasts first, then the gathers back to back
 #pragma unroll
-        for (int u = 0; u < UNR; ++u) bv[u] = col_ok ? gather_b<VW, TIERED>(Bl, ct[u], n, policy) : (V)(0.0f);
+        for (int u = 0; u < UNR; ++u) bv[u] = col_ok ? load_v<VW>(Bl + (int64_t)ct[u] * n) : (V)(0.0f);
 #pragma unroll
         for (int u = 0; u < UNR; ++u)
           if (t0 + u < cnt) acc += av[u] * bv[u];
       }
     }
-  } else if constexpr (G == 1) {
+  } else {
     for (int32_t p = p0; p < p1; ++p) {
       if (p != p0) {
         c = colidx[p];
         v = vals[p];
       }
-      if (col_ok) acc += v * gather_b<VW, TIERED>(Bl, c, n, policy);
-    }
-  } else {
-    constexpr int UNR = G < 8 ? G : 8;
-    constexpr int NB = G / UNR;  // batches per tile
-    for (int32_t p = p0; p < p1; p += G) {
-      const int32_t cnt = min(G, p1 - p);
-      int32_t nc = 0;
-      float nv = 0.0f;
-      if (p + G < p1) load_tile<G>(colidx, vals, p + G, p1, glane, nc, nv);
-      V buf[2][UNR];
-      auto issue = [&](int t0, V(&b)[UNR]) {
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-          const int32_t ct = __shfl(c, gbase + t0 + u, 64);
-          b[u] = (V)(0.0f);
-          if (t0 + u < cnt && col_ok) b[u] = gather_b<VW, TIERED>(Bl, ct, n, policy);
-        }
-      };
-      issue(0, buf[0]);
-#pragma unroll
-      for (int bt = 0; bt < NB; ++bt) {
-        const int t0 = bt * UNR;
-        if (t0 >= cnt) break;
-        if (bt + 1 < NB && t0 + UNR < cnt) issue(t0 + UNR, buf[(bt + 1) & 1]);
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-          const float a = __shfl(v, gbase + t0 + u, 64);
-          if (t0 + u < cnt) acc += a * buf[bt & 1][u];
-        }
-      }
-      c = nc;
-      v = nv;
+      if (col_ok) acc += v * load_v<VW>(Bl + (int64_t)c * n);
     }
   }
-}
-
-template <int G, int VW>
-__device__ __forceinline__ void accumulate(const int32_t *__restrict__ colidx, const float *__restrict__ vals,
-                                           int32_t p0, int32_t p1, const float *__restrict__ Bl, int32_t n,
-                                           bool col_ok, typename VecOf<VW>::T &acc, int glane, int gbase,
-                                           int policy) {
-  int32_t c;
-  float v;
-  load_tile<G>(colidx, vals, p0, p1, glane, c, v);
-  gather_rows<G, VW>(colidx, vals, p0, p1, c, v, Bl, n, col_ok, acc, glane, gbase, policy);
 }
 
 // A wave owns WR = (64/G) * J rows starting at wave-row w0 of the row space
@@ -266,12 +217,12 @@ __device__ __forceinline__ void accumulate(const int32_t *__restrict__ colidx, c
 // gathers per lane are in flight.  Slots past a row's end issue no load.
 // Nonzeros past the first UNR of a row (rare for the short rows this path
 // is planned for) continue through gather_rows.
-template <int G, int VW, int J, int UNR, bool LIST, bool PIPE, bool TIERED>
+template <int G, int VW, int J, int UNR, bool LIST>
 __device__ __forceinline__ void rows_wave(int64_t w0, const int32_t *__restrict__ rowptr,
                                           const int32_t *__restrict__ colidx, const float *__restrict__ vals,
                                           const int32_t *__restrict__ rowlist, int64_t nrows,
                                           const float *__restrict__ B, float *__restrict__ C, int32_t n,
-                                          int32_t col, int policy) {
+                                          int32_t col) {
   using V = typename VecOf<VW>::T;
   constexpr int RPW = 64 / G;
   constexpr int WR = RPW * J;
@@ -322,7 +273,7 @@ __device__ __forceinline__ void rows_wave(int64_t w0, const int32_t *__restrict_
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
       bv[j][u] = (V)(0.0f);
-      if (u < cnt[j] && col_ok) bv[j][u] = gather_b<VW, TIERED>(Bl, ct[j][u], n, policy);
+      if (u < cnt[j] && col_ok) bv[j][u] = load_v<VW>(Bl + (int64_t)ct[j][u] * n);
     }
 #pragma unroll
   for (int j = 0; j < J; ++j) {
@@ -334,8 +285,7 @@ __device__ __forceinline__ void rows_wave(int64_t w0, const int32_t *__restrict_
       int32_t cc;
       float vv;
       load_tile<G>(colidx, vals, p0[j] + UNR, p1[j], glane, cc, vv);
-      gather_rows<G, VW, PIPE, TIERED>(colidx, vals, p0[j] + UNR, p1[j], cc, vv, Bl, n, col_ok, acc[j], glane,
-                                       gbase, policy);
+      gather_rows<G, VW>(colidx, vals, p0[j] + UNR, p1[j], cc, vv, Bl, n, col_ok, acc[j], glane, gbase);
     }
     if (row[j] >= 0 && col_ok) store_nt<VW>(C + (int64_t)row[j] * n + col, acc[j]);
   }
@@ -348,13 +298,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(J == 1 ? 6 
                                                   const float *__restrict__ vals,
                                                   const int32_t *__restrict__ rowlist, int32_t nrows,
                                                   const float *__restrict__ B, float *__restrict__ C, int32_t n,
-                                                  int policy, int order) {
+                                                  int order) {
   constexpr int WR = (64 / G) * J;
   const int wave = threadIdx.x >> 6;
   const uint32_t blk = wg_index(order);
   const int64_t w0 = ((int64_t)blk * kWaves + wave) * WR;
   const int32_t col = blockIdx.y * (G * VW) + (threadIdx.x & (G - 1)) * VW;
-  rows_wave<G, VW, J, UNR, LIST, false, false>(w0, rowptr, colidx, vals, rowlist, nrows, B, C, n, col, policy);
+  rows_wave<G, VW, J, UNR, LIST>(w0, rowptr, colidx, vals, rowlist, nrows, B, C, n, col);
 }
 
 // ------------------------------------------------------- heavy-row split ---
@@ -370,7 +320,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(J == 1 ? 6 
                                                    const int32_t *__restrict__ corder,
                                                    uint32_t chunk_blocks, float *__restrict__ ws,
                                                    const float *__restrict__ B, float *__restrict__ C, int32_t n,
-                                                   int policy, int order) {
+                                                   int order) {
   using V = typename VecOf<VW>::T;
   constexpr int RPW = 64 / G;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -397,11 +347,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(J == 1 ? 6 
     int32_t c0;
     float v0;
     load_tile<G>(colidx, vals, p0, p1, glane, c0, v0);
-    gather_rows<G, VW, false, false>(colidx, vals, p0, p1, c0, v0, B + col, n, col_ok, acc, glane, gbase, policy);
+    gather_rows<G, VW>(colidx, vals, p0, p1, c0, v0, B + col, n, col_ok, acc, glane, gbase);
     if (q < nchunks && col_ok) store_v<VW>(ws + q * n + col, acc);
   } else {
     const int64_t w0 = ((int64_t)(blk - chunk_blocks) * kWaves + wave) * (RPW * J);
-    rows_wave<G, VW, J, UNR, true, false, false>(w0, rowptr, colidx, vals, light, nlight, B, C, n, col, policy);
+    rows_wave<G, VW, J, UNR, true>(w0, rowptr, colidx, vals, light, nlight, B, C, n, col);
   }
 }
 
@@ -583,6 +533,14 @@ __global__ __launch_bounds__(256) void k_split_slices(const int32_t *__restrict_
 // it.  So every element of C is written by exactly one store.
 // rows[0, units): carry rows; rows[units, 2 units): head rows (-1: none).
 // part[0, units n): carry partials; part[units n, 2 units n): head partials.
+//
+// The piece's nonzeros are one contiguous stream, so they are taken in tiles
+// and in batches of 8 gathers whatever rows they belong to (the next tile is
+// loaded behind the current gathers), and a row is closed when the running
+// position reaches its end.  The row ends come from a tile held across the
+// group's lanes: closing a row waits on a lane permute, not on memory.  Walking
+// row by row instead left each short row its own bounds -> entries -> gathers
+// chain.
 template <int G, int VW>
 __global__ __launch_bounds__(256) void k_csr_merge(const int32_t *__restrict__ rowptr,
                                                    const int32_t *__restrict__ colidx,
@@ -593,66 +551,192 @@ __global__ __launch_bounds__(256) void k_csr_merge(const int32_t *__restrict__ r
                                                    int policy, int order) {
   using V = typename VecOf<VW>::T;
   constexpr int RPW = 64 / G;
+  constexpr int EPL = G >= 8 ? 1 : 8 / G;  // entries (and row ends) per lane and tile
+  constexpr int T = G * EPL;               // tile: at least one batch
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int glane = lane & (G - 1), gbase = lane & ~(G - 1);
   const uint32_t blk = wg_index(order);
   const int64_t u = ((int64_t)blk * kWaves + wave) * RPW + lane / G;
   const int32_t col = blockIdx.y * (G * VW) + glane * VW;
   const bool col_ok = col < n;
-  int32_t i0 = 0, i1 = 0, j = 0, j1 = 0;
+  const float *__restrict__ Bl = B + col;
+  int32_t i0 = 0, i1 = 0, j0 = 0, j1 = 0;
   if (u < units) {
     i0 = coords[2 * u];
-    j = coords[2 * u + 1];
+    j0 = coords[2 * u + 1];
     i1 = coords[2 * u + 2];
     j1 = coords[2 * u + 3];
   }
   // the piece ends row i0, which began in an earlier piece
-  const bool head = i0 < i1 && j > rowptr[i0];
-  for (int32_t i = i0; i < i1; ++i) {
-    const int32_t e = rowptr[i + 1];
-    V acc = (V)(0.0f);
-    accumulate<G, VW>(colidx, vals, j, e, B + col, n, col_ok, acc, glane, gbase, policy);
+  bool head = i0 < i1 && j0 > rowptr[i0];
+  // ends of rows [rb, rb + T); rows from i1 on do not end in this piece.  Positions
+  // are unsigned: the last tile of a stream of almost 2^31 entries ends past INT32_MAX.
+  constexpr uint32_t kNoEnd = UINT32_MAX;
+  int32_t i = i0, rb = i0;
+  uint32_t rend[EPL];
+  auto load_ends = [&]() {
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+      const int32_t r = rb + e * G + glane;
+      rend[e] = r < i1 ? (uint32_t)rowptr[r + 1] : kNoEnd;
+    }
+  };
+  auto end_of = [&](int32_t r) {  // group-uniform r in [rb, rb + T)
+    uint32_t v = rend[0];
+#pragma unroll
+    for (int e = 1; e < EPL; ++e) v = (r - rb) / G == e ? rend[e] : v;
+    return G == 1 ? v : __shfl(v, gbase + ((r - rb) & (G - 1)), 64);
+  };
+  V acc = (V)(0.0f);
+  load_ends();
+  uint32_t end = end_of(i);
+  auto close_row = [&]() {
     if (col_ok) {
-      if (head && i == i0)
+      if (head)
         store_v<VW>(part + ((int64_t)units + u) * n + col, acc);
       else
         store_nt<VW>(C + (int64_t)i * n + col, acc);
     }
-    j = e;
+    acc = (V)(0.0f);
+    head = false;
+    ++i;
+    if (i - rb == T) {
+      rb = i;
+      load_ends();
+    }
+    end = end_of(i);
+  };
+  const uint32_t pe = (uint32_t)j1;
+  while (end == (uint32_t)j0) close_row();
+  int32_t c[EPL];
+  float v[EPL];
+  auto load_entries = [&](uint32_t p, int32_t(&cc)[EPL], float(&vv)[EPL]) {
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+      cc[e] = 0;
+      vv[e] = 0.0f;
+      const uint32_t q = p + e * G + glane;
+      if (q < pe) {
+        cc[e] = colidx[q];
+        vv[e] = vals[q];
+      }
+    }
+  };
+  load_entries((uint32_t)j0, c, v);
+  for (uint32_t p = (uint32_t)j0; p < pe; p += T) {
+    int32_t nc[EPL];
+    float nv[EPL];
+    load_entries(p + T, nc, nv);
+#pragma unroll 1
+    for (int t0 = 0; t0 < T; t0 += 8) {
+      if (p + t0 >= pe) break;
+      V bv[8];
+      float av[8];
+      int32_t ct[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {  // EPL > 1: one batch per tile, so t0 = 0
+        if constexpr (EPL > 1) {
+          ct[q] = G == 1 ? c[q / G] : __shfl(c[q / G], gbase + q % G, 64);
+          av[q] = G == 1 ? v[q / G] : __shfl(v[q / G], gbase + q % G, 64);
+        } else {
+          ct[q] = __shfl(c[0], gbase + t0 + q, 64);
+          av[q] = __shfl(v[0], gbase + t0 + q, 64);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);  // broadcasts first, then the gathers back to back
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        bv[q] = (V)(0.0f);
+        if (p + t0 + q < pe && col_ok) bv[q] = gather_b<VW>(Bl, ct[q], n, policy);
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (p + t0 + q < pe) {
+          acc += av[q] * bv[q];
+          while (end == p + t0 + q + 1) close_row();  // this row, and empty rows after it
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+      c[e] = nc[e];
+      v[e] = nv[e];
+    }
   }
-  V acc = (V)(0.0f);
-  accumulate<G, VW>(colidx, vals, j, j1, B + col, n, col_ok, acc, glane, gbase, policy);
   if (u < units) {
-    const bool has = (i1 < m) && (j1 > j);
+    // entries of row i1 in this piece: those after the last row it ends
+    const bool has = i1 < m && j1 > max(j0, rowptr[i1]);
     if (glane == 0 && blockIdx.y == 0) {
       rows[u] = has ? i1 : -1;
-      rows[units + u] = head ? i0 : -1;
+      rows[units + u] = i0 < i1 && j0 > rowptr[i0] ? i0 : -1;
     }
     if (has && col_ok) store_v<VW>(part + u * n + col, acc);
   }
 }
 
 // The first piece of each run of pieces carrying into the same row r stores
-// C[r]: the run's partials in piece order, then the head of the piece after
-// the run, which ends r.
+// C[r]: the run's partials, then the head of the piece after the run, which
+// ends r.  Row r's end is step rowptr[r + 1] + r of the path, so the run's end
+// is known without reading the pieces between.  A run of up to 4 carries is
+// added by its own lane group; a longer one (a heavy row: hundreds of pieces)
+// by the whole wave, its 64/G lane groups taking every (64/G)-th carry, four
+// in flight each, and meeting in a fixed xor butterfly.  Walked in turn by one
+// lane group, the longest run set the kernel's time (R-MAT 200 k vertices,
+// 3 M edges, n = 32: 71 us).
 template <int G, int VW>
-__global__ __launch_bounds__(256) void k_merge_fixup(const int32_t *__restrict__ rows,
+__global__ __launch_bounds__(256) void k_merge_fixup(const int32_t *__restrict__ rowptr,
+                                                     const int32_t *__restrict__ coords,
+                                                     const int32_t *__restrict__ rows,
                                                      const float *__restrict__ part, int32_t units,
                                                      float *__restrict__ C, int32_t n) {
   using V = typename VecOf<VW>::T;
-  constexpr int RPW = 64 / G;
+  constexpr int S = 64 / G;
+  constexpr int kAlone = 4;  // carries added by one lane group
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int glane = lane & (G - 1);
-  const int64_t u = ((int64_t)blockIdx.x * kWaves + wave) * RPW + lane / G;
+  const int glane = lane & (G - 1), s = lane / G;
+  const int64_t u = ((int64_t)blockIdx.x * kWaves + wave) * S + s;
   const int32_t col = blockIdx.y * (G * VW) + glane * VW;
-  if (u >= units || col >= n) return;
-  const int32_t r = rows[u];
-  if (r < 0 || (u > 0 && rows[u - 1] == r)) return;
-  V sum = load_v<VW>(part + u * n + col);
-  int64_t v = u + 1;
-  for (; v < units && rows[v] == r; ++v) sum += load_v<VW>(part + v * n + col);
-  if (v < units && rows[units + v] == r) sum += load_v<VW>(part + ((int64_t)units + v) * n + col);
-  store_nt<VW>(C + (int64_t)r * n + col, sum);
+  const bool col_ok = col < n;
+  const float *__restrict__ pl = part + (col_ok ? col : 0);  // lanes past n read column 0 and never store
+  int32_t r = -1, end = 0;  // carries [u, end) go to row r
+  if (u < units) {
+    r = rows[u];
+    if (r >= 0 && u > 0 && rows[u - 1] == r) r = -1;
+    if (r >= 0) {
+      const int64_t L = (int64_t)coords[2] + coords[3];  // path steps per piece
+      end = (int32_t)min((int64_t)units, ((int64_t)rowptr[r + 1] + r) / L);
+    }
+  }
+  auto add_head = [&](V sum, int32_t row, int32_t e) {
+    if (e < units && rows[units + e] == row) sum += load_v<VW>(pl + ((int64_t)units + e) * n);
+    return sum;
+  };
+  const bool alone = r >= 0 && end - u <= kAlone;
+  if (alone) {
+    V sum = load_v<VW>(pl + u * n);
+#pragma unroll
+    for (int t = 1; t < kAlone; ++t)
+      if (u + t < end) sum += load_v<VW>(pl + (u + t) * n);
+    sum = add_head(sum, r, end);
+    if (col_ok) store_nt<VW>(C + (int64_t)r * n + col, sum);
+  }
+  uint64_t pending = __ballot(r >= 0 && !alone && glane == 0);
+  while (pending) {  // wave-uniform
+    const int src = __ffsll((long long)pending) - 1;
+    pending &= pending - 1;
+    const int32_t row = __shfl(r, src, 64), e = __shfl(end, src, 64);
+    const int32_t u0 = (int32_t)__shfl((int32_t)u, src, 64);
+    V a0 = (V)(0.0f), a1 = (V)(0.0f), a2 = (V)(0.0f), a3 = (V)(0.0f);
+    int64_t q = (int64_t)u0 + s;
+    for (; q + 3 * S < e; q += 4 * S) {
+      a0 += load_v<VW>(pl + q * n);
+      a1 += load_v<VW>(pl + (q + S) * n);
+      a2 += load_v<VW>(pl + (q + 2 * S) * n);
+      a3 += load_v<VW>(pl + (q + 3 * S) * n);
+    }
+    for (; q < e; q += S) a0 += load_v<VW>(pl + q * n);
+    const V sum = add_head(slice_reduce<G, S>((a0 + a1) + (a2 + a3)), row, e);
+    if (s == 0 && col_ok) store_nt<VW>(C + (int64_t)row * n + col, sum);
+  }
 }
 
 // -------------------------------------------------------------------- ELL ---
@@ -889,7 +973,7 @@ __global__ __launch_bounds__(256) void k_win_split(
     float v0;
     load_tile<G>(code, vals, p0, p1, glane, c0, v0);
     V acc = (V)(0.0f);
-    gather_rows<G, VW, false, false>(code, vals, p0, p1, c0, v0, B + col, n, col_ok, acc, glane, gbase, 0);
+    gather_rows<G, VW>(code, vals, p0, p1, c0, v0, B + col, n, col_ok, acc, glane, gbase);
     if (t < nchunks && col_ok) store_v<VW>(ws + q * n + col, acc);
     return;
   }
@@ -1321,7 +1405,7 @@ hipError_t launch_csr_rows(const CsrOperand &A, const DenseIO &io, int32_t rows_
       const uint32_t nb = blocks_for(A.m, G, J);
       if (nb == 0) return hipSuccess;
       hipLaunchKernelGGL((k_csr_rows<G, VW, J, UNR, false>), dim3(nb, geo.coltiles), dim3(256), 0, s, A.rowptr,
-                         A.colidx, A.vals, nullptr, A.m, io.B, io.C, io.n, io.policy, io.order);
+                         A.colidx, A.vals, nullptr, A.m, io.B, io.C, io.n, io.order);
       return hipGetLastError();
     });
   });
@@ -1352,7 +1436,7 @@ hipError_t launch_csr_split(const CsrOperand &A, const int32_t *light, int32_t n
       const uint32_t grid = (io.order == 1 ? (cb + 7u) & ~7u : cb) + lb;
       hipLaunchKernelGGL((k_csr_split<G, VW, J, UNR>), dim3(grid, geo.coltiles), dim3(256), 0, s, A.rowptr,
                          A.colidx, A.vals, light, nlight, chunks, nchunks, corder, cb, ws, io.B, io.C, io.n,
-                         io.policy, io.order == 1 ? 1 : 0);
+                         io.order == 1 ? 1 : 0);
       return hipGetLastError();
     });
     if (e != hipSuccess) return e;
@@ -1377,8 +1461,8 @@ hipError_t launch_csr_merge(const CsrOperand &A, const int32_t *coords, int32_t 
                        coords, units, A.m, rows, part, io.B, io.C, io.n, io.policy, io.order);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_merge_fixup<G, VW>), dim3(nb, geo.coltiles), dim3(256), 0, s, rows, part, units, io.C,
-                       io.n);
+    hipLaunchKernelGGL((k_merge_fixup<G, VW>), dim3(nb, geo.coltiles), dim3(256), 0, s, A.rowptr, coords, rows, part,
+                       units, io.C, io.n);
     return hipGetLastError();
   });
 }
