@@ -10,8 +10,6 @@
 //               (row, begin, end) of at most c nonzeros in row and chunk order,
 //               the heavy rows and the first chunk of each (plus the total),
 //               placed by exclusive prefix sums (hipCUB) of per-row counts;
-//  * row reach  per row, the larger of |first column - row| and
-//               |last column - row| (-1 for an empty row);
 //  * transpose  the CSR of A^T: a stable radix sort (hipCUB) of the nonzero
 //               positions by column keeps each column's rows ascending, as the
 //               host's counting sort does; row pointers by binary search in
@@ -122,20 +120,6 @@ __global__ __launch_bounds__(256) void k_split_fill(const int32_t *__restrict__ 
     ch[1] = b;
     ch[2] = min(p1, b + c);
   }
-}
-
-__global__ __launch_bounds__(256) void k_row_reach(const int32_t *__restrict__ rowptr,
-                                                   const int32_t *__restrict__ colidx, int32_t m,
-                                                   int64_t *__restrict__ reach) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= m) return;
-  const int32_t p0 = rowptr[i], p1 = rowptr[i + 1];
-  int64_t v = -1;  // empty rows are marked and skipped by the caller
-  if (p1 > p0) {
-    const int64_t a = colidx[p0] - i, b = colidx[p1 - 1] - i;
-    v = max(a < 0 ? -a : a, b < 0 ? -b : b);
-  }
-  reach[i] = v;
 }
 
 // the row holding nonzero p of a valid CSR (m >= 1): the last row starting at
@@ -370,12 +354,6 @@ hipError_t dev_ell(const int32_t *rowptr, const int32_t *colidx, const float *va
 hipError_t dev_merge_coords(const int32_t *rowptr, int32_t m, int64_t nnz, int32_t U, int64_t L, int32_t *coords,
                             hipStream_t s) {
   hipLaunchKernelGGL(k_merge_coords, dim3(grid_for((int64_t)U + 1)), dim3(256), 0, s, rowptr, m, nnz, U, L, coords);
-  return hipGetLastError();
-}
-
-hipError_t dev_row_reach(const int32_t *rowptr, const int32_t *colidx, int32_t m, int64_t *reach, hipStream_t s) {
-  if (m == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_row_reach, dim3(grid_for(m)), dim3(256), 0, s, rowptr, colidx, m, reach);
   return hipGetLastError();
 }
 

@@ -98,7 +98,6 @@ hipError_t dev_ell(const int32_t *rowptr, const int32_t *colidx, const float *va
                    int32_t *ecol, float *eval, hipStream_t s);
 hipError_t dev_merge_coords(const int32_t *rowptr, int32_t m, int64_t nnz, int32_t U, int64_t L, int32_t *coords,
                             hipStream_t s);
-// per row max(|first col - row|, |last col - row|), -1 for an empty row
 // 16x16 BSR (ell_width < 0: nnzb blocks, bptr [mb+1]) or Blocked-ELL
 // (ell_width >= 0: mb * ell_width slots, -1 padding) of a valid CSR in device
 // memory, into caller-owned bcol [slots+1] and bval [(slots+1)*256] (one zero
@@ -136,7 +135,6 @@ uint64_t pattern_hash_host(const int32_t *rowptr, const int32_t *colidx, int32_t
 // column ascending.  Waits for the stream.
 hipError_t dev_transpose(const int32_t *rowptr, const int32_t *colidx, const float *vals, int32_t m, int32_t k,
                          int64_t nnz, int32_t *t_rowptr, int32_t *t_colidx, float *t_vals, hipStream_t s);
-hipError_t dev_row_reach(const int32_t *rowptr, const int32_t *colidx, int32_t m, int64_t *reach, hipStream_t s);
 // alloc(bytes) returns plan-owned device memory (nullptr on failure); waits for s
 // Writes the heavy-split layout into lptr (|light| + 1), colidx_out and
 // vals_out (nnz each): the light rows' entries in list order, then the heavy
@@ -173,7 +171,14 @@ hipError_t dev_heavy_split(const int32_t *rowptr, int32_t m, int32_t T, int32_t 
 
 // analyze.hip: sd_analyze on a CSR matrix whose arrays are device pointers;
 // runs on stream s and waits for it.  Same statistics as the host analysis.
-int analyze_device(const sd_csr_t *A, int32_t dense_threshold, sd_stats_t *out, hipStream_t s);
+// kPlanStats: only what a plan reads (the sizes, the row statistics without the
+// spans' median, nnzb16 and bell16_width); every other field is 0.
+enum DeviceStats { kAllStats, kPlanStats };
+int analyze_device(const sd_csr_t *A, int32_t dense_threshold, sd_stats_t *out, hipStream_t s,
+                   DeviceStats what = kAllStats);
+// Lower median over the non-empty rows of max(|first col - row|, |last col -
+// row|), 0 if there are none (median_row_reach on the host).  Waits for s.
+hipError_t dev_median_reach(const int32_t *rowptr, const int32_t *colidx, int32_t m, hipStream_t s, int64_t *out);
 
 // Kernel attributes of the main kernel a plan will launch (for the
 // resource-bound legality check).

@@ -89,29 +89,6 @@ struct DeviceGuard {
 // public status.
 constexpr int kNeedHost = -100;
 
-// Median over non-empty rows of the row reach, from the device (the same
-// lower median as median_row_reach on the host).
-int device_median_reach(const sd_csr_t *dev, hipStream_t s, int64_t *out) {
-  *out = 0;
-  if (dev->m == 0) return SD_OK;
-  int64_t *d = nullptr;
-  hipError_t e = hipMalloc(&d, sizeof(int64_t) * (size_t)dev->m);
-  if (e != hipSuccess) return hip_fail(e);
-  std::vector<int64_t> h((size_t)dev->m);
-  e = sd::dev_row_reach(dev->rowptr, dev->colidx, dev->m, d, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(h.data(), d, sizeof(int64_t) * h.size(), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  else (void)hipStreamSynchronize(s);  // nothing may still use d when it is freed
-  (void)hipFree(d);
-  if (e != hipSuccess) return hip_fail(e);
-  h.erase(std::remove(h.begin(), h.end(), (int64_t)-1), h.end());
-  if (h.empty()) return SD_OK;
-  const size_t mid = (h.size() - 1) / 2;
-  std::nth_element(h.begin(), h.begin() + (long)mid, h.end());
-  *out = h[mid];
-  return SD_OK;
-}
-
 // A^T of a device CSR, in device memory owned here; freed after the stream
 // it was built on has drained.
 struct DeviceTranspose {
@@ -167,11 +144,11 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
   if (src) {
     if (o.placement != 0) return kNeedHost;
     if (o.transpose) {  // A is checked (by its analysis) before it is transposed
-      if ((st = sd::analyze_device(src, o.dense_threshold, &stats, ds)) != SD_OK) return st;
+      if ((st = sd::analyze_device(src, o.dense_threshold, &stats, ds, sd::kPlanStats)) != SD_OK) return st;
       if ((st = device_transpose(src, ds, &Tt)) != SD_OK) return st;
       src = &Tt.csr;
     }
-    if ((st = sd::analyze_device(src, o.dense_threshold, &stats, ds)) != SD_OK) return st;
+    if ((st = sd::analyze_device(src, o.dense_threshold, &stats, ds, sd::kPlanStats)) != SD_OK) return st;
     A.m = src->m;  // sizes only: no host array is read on this path
     A.k = src->k;
     A.nnz = src->nnz;
@@ -499,7 +476,8 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
     const int64_t rows_per_wg = (int64_t)(sd::kBlockThreads / (geo.G * std::max(1, I.row_slices))) *
                                 (I.family == SD_FMT_CSR_ROW ? std::max(1, I.rows_per_group) : 1);
     if (src) {
-      if ((st = device_median_reach(src, ds, &I.reach)) != SD_OK) return st;
+      const hipError_t e = sd::dev_median_reach(src->rowptr, src->colidx, src->m, ds, &I.reach);
+      if (e != hipSuccess) return hip_fail(e);
     } else {
       I.reach = sd::median_row_reach(A);
     }
