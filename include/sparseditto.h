@@ -24,11 +24,12 @@
  *   sd_plan_cache_size / _save / _load
  *                   measured plan choices kept and reused across processes
  *   sd_plan_info / sd_plan_export / sd_plan_destroy / sd_status_string / sd_last_error
+ *   sd_release_memory
  *
  * Conventions shared by every call:
- *   - Every function except sd_plan_destroy and sd_status_string returns an
- *     sd_status; 0 (SD_OK) is success.  On failure, outputs are left untouched
- *     unless stated otherwise, and nothing is leaked.
+ *   - Every function, except those of type void and the two that return a
+ *     string, returns an sd_status; 0 (SD_OK) is success.  On failure, outputs
+ *     are left untouched unless stated otherwise, and nothing is leaked.
  *   - Host pointers are plain CPU memory; device pointers are HIP device
  *     memory on the plan's device.
  *   - No call keeps a pointer to caller memory after it returns.
@@ -462,6 +463,12 @@ int sd_plan_cache_load(const char *path);
 /* Frees the plan's host and device memory.  NULL is a no-op.  The caller must
  * make sure no sd_spmm on this plan is still running (synchronise its stream). */
 void sd_plan_destroy(sd_plan_t plan);
+
+/* Device memory that destroyed plans and finished conversions leave is kept for
+ * later plans, at most 1 GiB per device.  This returns what is kept to the
+ * device; plans in use are not touched.  An allocation of the library that
+ * would fail does the same by itself before it gives up. */
+void sd_release_memory(void);
 
 /* Static strings; never NULL. */
 const char *sd_status_string(int status);

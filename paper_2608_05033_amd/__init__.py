@@ -146,6 +146,8 @@ def _load():
     lib.sd_plan_export.argtypes = [_P, _i32, _P, ctypes.c_size_t]
     lib.sd_plan_destroy.argtypes = [_P]
     lib.sd_plan_destroy.restype = None
+    lib.sd_release_memory.argtypes = []
+    lib.sd_release_memory.restype = None
     lib.sd_plan_cache_clear.argtypes = []
     lib.sd_plan_cache_clear.restype = None
     lib.sd_plan_cache_size.argtypes = [ctypes.POINTER(_i64)]
@@ -163,7 +165,7 @@ def _load():
 
 _lib = _load()
 EXPORTED = ("sd_analyze", "sd_analyze_device", "sd_plan", "sd_plan_ex", "sd_plan_device", "sd_spmm", "sd_spmm_merge_noalloc", "sd_plan_info", "sd_plan_export_size",
-            "sd_plan_export", "sd_plan_destroy", "sd_plan_cache_clear", "sd_plan_cache_size", "sd_plan_cache_save", "sd_plan_cache_load", "sd_status_string", "sd_last_error")
+            "sd_plan_export", "sd_plan_destroy", "sd_plan_cache_clear", "sd_plan_cache_size", "sd_plan_cache_save", "sd_plan_cache_load", "sd_release_memory", "sd_status_string", "sd_last_error")
 
 
 def _check(status: int, where: str):
@@ -358,6 +360,11 @@ def sd_plan_export(plan: Plan, what: int) -> np.ndarray:
 
 def sd_plan_destroy(plan: Plan) -> None:
     plan.destroy()
+
+
+def sd_release_memory() -> None:
+    """Returns the device memory kept for later plans to the device."""
+    _lib.sd_release_memory()
 
 
 def sd_plan_cache_clear() -> None:

@@ -630,19 +630,14 @@ hipError_t launch_strips(const sd_csr_t *A, int32_t dense_threshold, int32_t *mi
   return hipGetLastError();
 }
 
+// Device scratch, given back once the stream has drained (an early error
+// return may leave kernels that use it in flight).
 struct DevBuf {
+  hipStream_t s;
   void *p = nullptr;
   ~DevBuf() {
-    if (p) (void)hipFree(p);
+    if (p) sd::pool_free(p, hipStreamSynchronize(s) == hipSuccess ? sd::kIdle : sd::kUnknown);
   }
-};
-
-// Declared after the buffers it protects, so it is destroyed first: every
-// return waits for the stream before the buffers are freed (an early error
-// return may leave kernels that use them in flight).
-struct StreamDrain {
-  hipStream_t s;
-  ~StreamDrain() { (void)hipStreamSynchronize(s); }
 };
 
 int hip_status(hipError_t e) {
@@ -683,10 +678,9 @@ int analyze_device(const sd_csr_t *A, int32_t dense_threshold, sd_stats_t *out, 
   const size_t at_sel = L.take(all ? kSelBins : 0), at_deg = L.take(all ? (size_t)k : 0);
   const size_t n_zero = L.words;
   const size_t at_mid = L.take(((size_t)m + 3) / 4), at_big = L.take(n_big), at_span = L.take(all ? (size_t)m : 0);
-  DevBuf buf;
-  StreamDrain drain{s};
+  DevBuf buf{s};
   hipError_t e;
-  if ((e = hipMalloc(&buf.p, 4 * L.words)) != hipSuccess) return hip_status(e);
+  if ((e = sd::pool_alloc(&buf.p, 4 * L.words)) != hipSuccess) return hip_status(e);
   uint32_t *w = static_cast<uint32_t *>(buf.p);
   DevAgg *agg = reinterpret_cast<DevAgg *>(w + at_agg);
   uint32_t *len_hist = w + at_len, *sel_hist = w + at_sel, *spans = all ? w + at_span : nullptr;
@@ -779,10 +773,9 @@ hipError_t dev_median_reach(const int32_t *rowptr, const int32_t *colidx, int32_
   Layout L;
   const size_t at_agg = L.take((sizeof(DevAgg) + 3) / 4), at_sel = L.take(kSelBins), n_zero = L.words;
   const size_t at_key = L.take((size_t)m);
-  DevBuf buf;
-  StreamDrain drain{s};
+  DevBuf buf{s};
   hipError_t e;
-  if ((e = hipMalloc(&buf.p, 4 * L.words)) != hipSuccess) return e;
+  if ((e = sd::pool_alloc(&buf.p, 4 * L.words)) != hipSuccess) return e;
   uint32_t *w = static_cast<uint32_t *>(buf.p);
   DevAgg *agg = reinterpret_cast<DevAgg *>(w + at_agg);
   hipLaunchKernelGGL(k_an_zero, dim3(8), dim3(256), 0, s, w, (int64_t)n_zero);

@@ -325,7 +325,7 @@ __global__ __launch_bounds__(256) void k_fill_i32(int32_t *__restrict__ x, int64
 
 uint32_t grid_for(int64_t items) { return (uint32_t)((items + 255) / 256); }
 
-// Device scratch of one conversion.  Freed on return, after the stream has
+// Device scratch of one conversion.  Given back on return, after the stream has
 // drained: an early error return may leave kernels that use it in flight.
 struct Scratch {
   hipStream_t s;
@@ -335,9 +335,9 @@ struct Scratch {
   ~Scratch() {
     bool any = false;
     for (void *q : p) any = any || q;
-    if (any) (void)hipStreamSynchronize(s);
+    const bool drained = !any || hipStreamSynchronize(s) == hipSuccess;
     for (void *q : p)
-      if (q) (void)hipFree(q);
+      pool_free(q, drained ? kIdle : kUnknown);
   }
 };
 
@@ -372,8 +372,8 @@ hipError_t dev_light_by_last_col(const int32_t *rowptr, const int32_t *colidx, i
   const int n = (int)n_light;
   Scratch sc(s);  // keys in / out, rows out, sort workspace
   hipError_t e;
-  if ((e = hipMalloc(&sc.p[0], 2 * sizeof(int32_t) * (size_t)n)) != hipSuccess) return e;
-  if ((e = hipMalloc(&sc.p[1], sizeof(int32_t) * (size_t)n)) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[0], 2 * sizeof(int32_t) * (size_t)n)) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[1], sizeof(int32_t) * (size_t)n)) != hipSuccess) return e;
   int32_t *kin = static_cast<int32_t *>(sc.p[0]), *kout = kin + n, *rout = static_cast<int32_t *>(sc.p[1]);
   hipLaunchKernelGGL(k_last_col_keys, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, rowptr, colidx, k, light,
                      n_light, kin);
@@ -383,7 +383,7 @@ hipError_t dev_light_by_last_col(const int32_t *rowptr, const int32_t *colidx, i
   size_t tmp = 0;
   if ((e = hipcub::DeviceRadixSort::SortPairs(nullptr, tmp, kin, kout, light, rout, n, 0, bits, s)) != hipSuccess)
     return e;
-  if ((e = hipMalloc(&sc.p[2], std::max<size_t>(tmp, 1))) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[2], std::max<size_t>(tmp, 1))) != hipSuccess) return e;
   if ((e = hipcub::DeviceRadixSort::SortPairs(sc.p[2], tmp, kin, kout, light, rout, n, 0, bits, s)) != hipSuccess)
     return e;
   if ((e = hipMemcpyAsync(light, rout, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToDevice, s)) != hipSuccess)
@@ -411,8 +411,8 @@ hipError_t dev_chunk_order(const int32_t *colidx, const int32_t *chunks, int64_t
   }
   Scratch sc(s);  // keys in / out, indices in, sort workspace
   hipError_t e;
-  if ((e = hipMalloc(&sc.p[0], 2 * sizeof(int32_t) * (size_t)n)) != hipSuccess) return e;
-  if ((e = hipMalloc(&sc.p[1], sizeof(int32_t) * (size_t)n)) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[0], 2 * sizeof(int32_t) * (size_t)n)) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[1], sizeof(int32_t) * (size_t)n)) != hipSuccess) return e;
   int32_t *kin = static_cast<int32_t *>(sc.p[0]), *kout = kin + n, *iin = static_cast<int32_t *>(sc.p[1]);
   hipLaunchKernelGGL(k_chunk_mid_keys, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, colidx, chunks,
                      (int64_t)n, kin, iin);
@@ -423,7 +423,7 @@ hipError_t dev_chunk_order(const int32_t *colidx, const int32_t *chunks, int64_t
   // a radix sort is stable: equal keys keep ascending chunk indices
   if ((e = hipcub::DeviceRadixSort::SortPairs(nullptr, tmp, kin, kout, iin, corder, n, 0, bits, s)) != hipSuccess)
     return e;
-  if ((e = hipMalloc(&sc.p[2], std::max<size_t>(tmp, 1))) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[2], std::max<size_t>(tmp, 1))) != hipSuccess) return e;
   if ((e = hipcub::DeviceRadixSort::SortPairs(sc.p[2], tmp, kin, kout, iin, corder, n, 0, bits, s)) != hipSuccess)
     return e;
   return hipStreamSynchronize(s);  // the scratch arrays are freed on return
@@ -479,7 +479,7 @@ hipError_t dev_split_layout(const int32_t *rowptr, const int32_t *colidx, const 
   Scratch sc(s);  // lengths and starts (int64) of the light rows, then of the heavy rows; scan workspace
   hipError_t e;
   const int64_t nl = std::max<int64_t>(1, n_light), nh = std::max<int64_t>(1, n_heavy);
-  if ((e = hipMalloc(&sc.p[0], 2 * sizeof(int64_t) * (size_t)(nl + nh))) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[0], 2 * sizeof(int64_t) * (size_t)(nl + nh))) != hipSuccess) return e;
   int64_t *len_l = static_cast<int64_t *>(sc.p[0]), *st_l = len_l + nl, *len_h = st_l + nl, *st_h = len_h + nh;
   int64_t light_total = 0;
   if (n_light > 0) {
@@ -488,7 +488,7 @@ hipError_t dev_split_layout(const int32_t *rowptr, const int32_t *colidx, const 
     if ((e = hipGetLastError()) != hipSuccess) return e;
     size_t tmp = 0;
     if ((e = hipcub::DeviceScan::ExclusiveSum(nullptr, tmp, len_l, st_l, (int)n_light, s)) != hipSuccess) return e;
-    if ((e = hipMalloc(&sc.p[1], std::max<size_t>(tmp, 1))) != hipSuccess) return e;
+    if ((e = pool_alloc(&sc.p[1], std::max<size_t>(tmp, 1))) != hipSuccess) return e;
     if ((e = hipcub::DeviceScan::ExclusiveSum(sc.p[1], tmp, len_l, st_l, (int)n_light, s)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_lptr_from_starts, dim3(g), dim3(256), 0, s, st_l, len_l, n_light, lptr);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -513,7 +513,7 @@ hipError_t dev_split_layout(const int32_t *rowptr, const int32_t *colidx, const 
     if ((e = hipGetLastError()) != hipSuccess) return e;
     size_t tmp = 0;
     if ((e = hipcub::DeviceScan::ExclusiveSum(nullptr, tmp, len_h, st_h, (int)n_heavy, s)) != hipSuccess) return e;
-    if ((e = hipMalloc(&sc.p[2], std::max<size_t>(tmp, 1))) != hipSuccess) return e;
+    if ((e = pool_alloc(&sc.p[2], std::max<size_t>(tmp, 1))) != hipSuccess) return e;
     if ((e = hipcub::DeviceScan::ExclusiveSum(sc.p[2], tmp, len_h, st_h, (int)n_heavy, s)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_move_rows, dim3((uint32_t)((n_heavy + 3) / 4)), dim3(256), 0, s, rowptr, colidx, vals,
                        heavy_rows, st_h, light_total, n_heavy, colidx_out, vals_out);
@@ -646,13 +646,13 @@ hipError_t dev_split_windows(const int32_t *lptr, int64_t n_light, int32_t *coli
   const int n = (int)E;
   Scratch sc(s);
   // entry keys, sorted keys, run keys, run lengths + run count, candidate keys (x2), kept keys (x2), flags, temp
-  if ((e = hipMalloc(&sc.p[0], sizeof(uint64_t) * (size_t)n)) != hipSuccess) return e;
-  if ((e = hipMalloc(&sc.p[1], sizeof(uint64_t) * (size_t)n)) != hipSuccess) return e;
-  if ((e = hipMalloc(&sc.p[2], sizeof(uint64_t) * (size_t)n)) != hipSuccess) return e;
-  if ((e = hipMalloc(&sc.p[3], sizeof(int32_t) * ((size_t)n + 1))) != hipSuccess) return e;
-  if ((e = hipMalloc(&sc.p[4], 2 * sizeof(uint64_t) * (size_t)n)) != hipSuccess) return e;
-  if ((e = hipMalloc(&sc.p[5], sizeof(int32_t) * (size_t)n)) != hipSuccess) return e;
-  if ((e = hipMalloc(&sc.p[6], sizeof(int64_t))) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[0], sizeof(uint64_t) * (size_t)n)) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[1], sizeof(uint64_t) * (size_t)n)) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[2], sizeof(uint64_t) * (size_t)n)) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[3], sizeof(int32_t) * ((size_t)n + 1))) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[4], 2 * sizeof(uint64_t) * (size_t)n)) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[5], sizeof(int32_t) * (size_t)n)) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[6], sizeof(int64_t))) != hipSuccess) return e;
   uint64_t *ekey = static_cast<uint64_t *>(sc.p[0]), *skey = static_cast<uint64_t *>(sc.p[1]);
   uint64_t *rkey = static_cast<uint64_t *>(sc.p[2]);
   int32_t *rlen = static_cast<int32_t *>(sc.p[3]), *nruns = rlen + n;
@@ -673,7 +673,7 @@ hipError_t dev_split_windows(const int32_t *lptr, int64_t n_light, int32_t *coli
   if ((e = hipcub::DeviceRadixSort::SortKeys(nullptr, t3, k2, k2s, n, 0, 64, s)) != hipSuccess) return e;
   if ((e = hipcub::DeviceReduce::Sum(nullptr, t4, flag, uses_d, n, s)) != hipSuccess) return e;
   t5 = std::max({t1, t2, t3, t4, (size_t)1});
-  if ((e = hipMalloc(&sc.p[7], t5)) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[7], t5)) != hipSuccess) return e;
   if ((e = hipcub::DeviceRadixSort::SortKeys(sc.p[7], t1, ekey, skey, n, 0, 32 + wbits, s)) != hipSuccess) return e;
   if ((e = hipcub::DeviceRunLengthEncode::Encode(sc.p[7], t2, skey, rkey, rlen, nruns, n, s)) != hipSuccess)
     return e;
@@ -723,8 +723,8 @@ hipError_t dev_heavy_split(const int32_t *rowptr, int32_t m, int32_t T, int32_t 
   const size_t mm = (size_t)std::max(1, m);
   Scratch sc(s);  // flags / counts (int32 x 3) and their exclusive prefix sums (int64 x 3)
   hipError_t e;
-  if ((e = hipMalloc(&sc.p[0], 3 * sizeof(int32_t) * mm)) != hipSuccess) return e;
-  if ((e = hipMalloc(&sc.p[1], 3 * sizeof(int64_t) * (mm + 1))) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[0], 3 * sizeof(int32_t) * mm)) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[1], 3 * sizeof(int64_t) * (mm + 1))) != hipSuccess) return e;
   int32_t *f = static_cast<int32_t *>(sc.p[0]);
   int64_t *pos = static_cast<int64_t *>(sc.p[1]);
   int32_t *fl = f, *fh = f + mm, *fp = f + 2 * mm;
@@ -735,7 +735,7 @@ hipError_t dev_heavy_split(const int32_t *rowptr, int32_t m, int32_t T, int32_t 
     // exclusive sums over the m rows; each total is the last prefix plus the last count
     size_t tmp_bytes = 0;
     if ((e = hipcub::DeviceScan::ExclusiveSum(nullptr, tmp_bytes, fl, pl, m, s)) != hipSuccess) return e;
-    if ((e = hipMalloc(&sc.p[2], std::max<size_t>(tmp_bytes, 1))) != hipSuccess) return e;
+    if ((e = pool_alloc(&sc.p[2], std::max<size_t>(tmp_bytes, 1))) != hipSuccess) return e;
     for (int t = 0; t < 3; ++t) {
       int32_t *in = t == 0 ? fl : t == 1 ? fh : fp;
       int64_t *out = t == 0 ? pl : t == 1 ? ph : pp;
@@ -785,7 +785,7 @@ hipError_t dev_block16(const int32_t *rowptr, const int32_t *colidx, const float
   Scratch sc(s);  // keys, sorted keys, positions, sorted positions, heads, block numbers, block keys, temporary, bptr
   int32_t *ptr = bptr;
   if (!ptr) {
-    if ((e = hipMalloc(&sc.p[8], sizeof(int32_t) * (size_t)(mb + 1))) != hipSuccess) return e;
+    if ((e = pool_alloc(&sc.p[8], sizeof(int32_t) * (size_t)(mb + 1))) != hipSuccess) return e;
     ptr = static_cast<int32_t *>(sc.p[8]);
   }
   // padding, and the zero block after the stored ones
@@ -798,10 +798,10 @@ hipError_t dev_block16(const int32_t *rowptr, const int32_t *colidx, const float
     return hipStreamSynchronize(s);
   }
   const size_t n4 = sizeof(int32_t) * (size_t)nnz, n8 = sizeof(uint64_t) * (size_t)nnz;
-  if ((e = hipMalloc(&sc.p[0], n8)) != hipSuccess || (e = hipMalloc(&sc.p[1], n8)) != hipSuccess ||
-      (e = hipMalloc(&sc.p[2], n4)) != hipSuccess || (e = hipMalloc(&sc.p[3], n4)) != hipSuccess ||
-      (e = hipMalloc(&sc.p[4], n4)) != hipSuccess || (e = hipMalloc(&sc.p[5], n4)) != hipSuccess ||
-      (e = hipMalloc(&sc.p[6], sizeof(uint64_t) * (size_t)std::max<int64_t>(1, nnzb))) != hipSuccess)
+  if ((e = pool_alloc(&sc.p[0], n8)) != hipSuccess || (e = pool_alloc(&sc.p[1], n8)) != hipSuccess ||
+      (e = pool_alloc(&sc.p[2], n4)) != hipSuccess || (e = pool_alloc(&sc.p[3], n4)) != hipSuccess ||
+      (e = pool_alloc(&sc.p[4], n4)) != hipSuccess || (e = pool_alloc(&sc.p[5], n4)) != hipSuccess ||
+      (e = pool_alloc(&sc.p[6], sizeof(uint64_t) * (size_t)std::max<int64_t>(1, nnzb))) != hipSuccess)
     return e;
   uint64_t *keys = static_cast<uint64_t *>(sc.p[0]), *skeys = static_cast<uint64_t *>(sc.p[1]);
   int32_t *pos = static_cast<int32_t *>(sc.p[2]), *perm = static_cast<int32_t *>(sc.p[3]);
@@ -818,7 +818,7 @@ hipError_t dev_block16(const int32_t *rowptr, const int32_t *colidx, const float
       (e = hipcub::DeviceScan::InclusiveSum(nullptr, tmp_scan, head, incl, (int)nnz, s)) != hipSuccess)
     return e;
   size_t tmp = std::max<size_t>({tmp_sort, tmp_scan, 1});
-  if ((e = hipMalloc(&sc.p[7], tmp)) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[7], tmp)) != hipSuccess) return e;
   if ((e = hipcub::DeviceRadixSort::SortPairs(sc.p[7], tmp_sort, keys, skeys, pos, perm, (int)nnz, 0, end_bit,
                                                s)) != hipSuccess)
     return e;
@@ -874,8 +874,8 @@ hipError_t dev_sell(const int32_t *rowptr, const int32_t *colidx, const float *v
   }
   Scratch sc(s);  // keys, sorted keys, rows, slice sizes, temporary
   const size_t mm = (size_t)m;
-  if ((e = hipMalloc(&sc.p[0], 8 * mm)) != hipSuccess || (e = hipMalloc(&sc.p[1], 8 * mm)) != hipSuccess ||
-      (e = hipMalloc(&sc.p[2], 4 * mm)) != hipSuccess || (e = hipMalloc(&sc.p[3], 8 * (size_t)ns)) != hipSuccess)
+  if ((e = pool_alloc(&sc.p[0], 8 * mm)) != hipSuccess || (e = pool_alloc(&sc.p[1], 8 * mm)) != hipSuccess ||
+      (e = pool_alloc(&sc.p[2], 4 * mm)) != hipSuccess || (e = pool_alloc(&sc.p[3], 8 * (size_t)ns)) != hipSuccess)
     return e;
   uint64_t *keys = static_cast<uint64_t *>(sc.p[0]), *skeys = static_cast<uint64_t *>(sc.p[1]);
   int32_t *rows = static_cast<int32_t *>(sc.p[2]);
@@ -890,7 +890,7 @@ hipError_t dev_sell(const int32_t *rowptr, const int32_t *colidx, const float *v
           hipSuccess ||
       (e = hipcub::DeviceScan::ExclusiveSum(nullptr, tmp_scan, size, *sptr, (int)ns, s)) != hipSuccess)
     return e;
-  if ((e = hipMalloc(&sc.p[4], std::max<size_t>({tmp_sort, tmp_scan, 1}))) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[4], std::max<size_t>({tmp_sort, tmp_scan, 1}))) != hipSuccess) return e;
   if ((e = hipcub::DeviceRadixSort::SortPairs(sc.p[4], tmp_sort, keys, skeys, rows, *perm, m, 0, end_bit, s)) !=
       hipSuccess)
     return e;
@@ -925,7 +925,7 @@ hipError_t dev_tag_cold(const int32_t *colidx, int64_t nnz, int32_t k, int64_t b
   hipError_t e;
   Scratch sc(s);
   const size_t kk = (size_t)std::max(1, k);
-  if ((e = hipMalloc(&sc.p[0], 4 * kk)) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[0], 4 * kk)) != hipSuccess) return e;
   int32_t *deg = static_cast<int32_t *>(sc.p[0]);
   if ((e = hipMemsetAsync(deg, 0, 4 * kk, s)) != hipSuccess) return e;
   if (nnz > 0) {
@@ -972,7 +972,7 @@ hipError_t dev_pattern_hash(const int32_t *rowptr, const int32_t *colidx, int32_
                             uint64_t *out) {
   Scratch sc(s);
   hipError_t e;
-  if ((e = hipMalloc(&sc.p[0], sizeof(unsigned long long))) != hipSuccess) return e;
+  if ((e = pool_alloc(&sc.p[0], sizeof(unsigned long long))) != hipSuccess) return e;
   unsigned long long *sum = static_cast<unsigned long long *>(sc.p[0]);
   if ((e = hipMemsetAsync(sum, 0, sizeof(unsigned long long), s)) != hipSuccess) return e;
   const int64_t lens[2] = {(int64_t)m + 1, nnz};
@@ -998,7 +998,7 @@ hipError_t dev_transpose(const int32_t *rowptr, const int32_t *colidx, const flo
     Scratch sc(s);  // sorted keys, positions, sorted positions, sort temporary
     const size_t bytes = sizeof(int32_t) * (size_t)nnz;
     for (int t = 0; t < 3; ++t)
-      if ((e = hipMalloc(&sc.p[t], bytes)) != hipSuccess) return e;
+      if ((e = pool_alloc(&sc.p[t], bytes)) != hipSuccess) return e;
     uint32_t *keys_out = static_cast<uint32_t *>(sc.p[0]);
     int32_t *pos = static_cast<int32_t *>(sc.p[1]), *perm = static_cast<int32_t *>(sc.p[2]);
     hipLaunchKernelGGL(k_iota, dim3(grid_for(nnz)), dim3(256), 0, s, pos, nnz);
@@ -1010,7 +1010,7 @@ hipError_t dev_transpose(const int32_t *rowptr, const int32_t *colidx, const flo
     if ((e = hipcub::DeviceRadixSort::SortPairs(nullptr, tmp, keys_in, keys_out, pos, perm, (int)nnz, 0, end_bit,
                                                  s)) != hipSuccess)
       return e;
-    if ((e = hipMalloc(&sc.p[3], std::max<size_t>(tmp, 1))) != hipSuccess) return e;
+    if ((e = pool_alloc(&sc.p[3], std::max<size_t>(tmp, 1))) != hipSuccess) return e;
     if ((e = hipcub::DeviceRadixSort::SortPairs(sc.p[3], tmp, keys_in, keys_out, pos, perm, (int)nnz, 0, end_bit,
                                                  s)) != hipSuccess)
       return e;

@@ -92,6 +92,13 @@ hipError_t launch_win_split(const CsrOperand &A, const int32_t *light, int32_t n
 // never written for a zero-filled buffer.
 hipError_t launch_cache_flush(const void *buf, size_t bytes, float *sink, hipStream_t s);
 
+// pool.hip: device memory on the current device, reused between calls.  A block
+// is given back as idle, as possibly still read by work in flight, or (after a
+// failed synchronisation) as unknown, which frees it at once.
+enum PoolState { kIdle, kInFlight, kUnknown };
+hipError_t pool_alloc(void **out, size_t bytes);
+void pool_free(void *p, PoolState state);
+
 // convert.hip: conversions and partitions on the device, producing exactly
 // the arrays of the host conversions (ell_convert, merge_split, heavy_split).
 hipError_t dev_ell(const int32_t *rowptr, const int32_t *colidx, const float *vals, int32_t m, int32_t W,

@@ -36,7 +36,7 @@ int hip_fail(hipError_t e) {
 int hip_alloc_copy(sd_plan_s *p, void **dst, const void *src, size_t bytes) {
   if (bytes == 0) bytes = 4;  // keep every pointer valid
   void *d = nullptr;
-  hipError_t e = hipMalloc(&d, bytes);
+  hipError_t e = sd::pool_alloc(&d, bytes);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     g_last_error = hipGetErrorString(e);
@@ -61,7 +61,7 @@ void release(sd_plan_s *p) {
     int cur = 0;
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(p->device);
-    for (void *d : p->allocations) (void)hipFree(d);
+    for (void *d : p->allocations) sd::pool_free(d, sd::kInFlight);
     (void)hipSetDevice(cur);
   }
   p->allocations.clear();
@@ -96,9 +96,9 @@ struct DeviceTranspose {
   hipStream_t s = nullptr;
   void *p[3] = {nullptr, nullptr, nullptr};
   ~DeviceTranspose() {
-    if (p[0] || p[1] || p[2]) (void)hipStreamSynchronize(s);
-    for (void *q : p)
-      if (q) (void)hipFree(q);
+    if (!p[0] && !p[1] && !p[2]) return;
+    const bool drained = hipStreamSynchronize(s) == hipSuccess;
+    for (void *q : p) sd::pool_free(q, drained ? sd::kIdle : sd::kUnknown);
   }
 };
 
@@ -107,7 +107,7 @@ int device_transpose(const sd_csr_t *A, hipStream_t s, DeviceTranspose *T) {
   const size_t sizes[3] = {4 * ((size_t)A->k + 1), 4 * (size_t)std::max<int64_t>(1, A->nnz),
                            4 * (size_t)std::max<int64_t>(1, A->nnz)};
   for (int t = 0; t < 3; ++t) {
-    hipError_t e = hipMalloc(&T->p[t], sizes[t]);
+    hipError_t e = sd::pool_alloc(&T->p[t], sizes[t]);
     if (e != hipSuccess) return hip_fail(e);
   }
   T->csr.m = A->k;

@@ -96,3 +96,36 @@ def test_analyze_strips_bad_columns(kind, what):
         with pytest.raises(sd.SparseDittoError) as e:
             sd.sd_plan_device(*_device_csr(bad), A.m, A.k, A.nnz, 8)
         assert e.value.status == sd.SD_ERR_INVALID_CSR
+
+
+def test_memory_reuse_in_flight():
+    """Plans destroyed with their products still in flight, on two streams, and
+    rebuilt in the memory they leave: every product is its own plan's."""
+    mats = [gen.rmat(12, 60000, seed=s) for s in range(4)]
+    dev = [_device_csr(A) for A in mats]
+    n = 64
+    B = torch.randn(mats[0].k, n, device="cuda")
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    want = []
+    for A, d in zip(mats, dev):
+        with sd.sd_plan_device(*d, A.m, A.k, A.nnz, n) as plan:
+            C = torch.empty(A.m, n, device="cuda")
+            sd.sd_spmm(plan, B, C)
+            torch.cuda.synchronize()
+            want.append(C)
+    for turn in range(6):
+        got = []
+        for i, (A, d) in enumerate(zip(mats, dev)):
+            s = streams[(i + turn) % 2]
+            plan = sd.sd_plan_device(*d, A.m, A.k, A.nnz, n, stream=s)
+            C = torch.empty(A.m, n, device="cuda")
+            for _ in range(20):
+                sd.sd_spmm(plan, B, C, s)
+            plan.destroy()  # without waiting
+            got.append(C)
+        torch.cuda.synchronize()
+        for c, w in zip(got, want):
+            assert torch.equal(c, w)
+        if turn == 2:
+            sd.sd_release_memory()
