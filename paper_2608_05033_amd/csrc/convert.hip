@@ -6,10 +6,11 @@
 //  * merge path U + 1 split coordinates (rows, nonzeros consumed), one binary
 //               search per coordinate on the merged sequence of row ends and
 //               nonzero indices;
-//  * heavy split light rows (r < T) in row order; for heavy rows, chunks
-//               (row, begin, end) of at most c nonzeros in row and chunk order,
-//               the heavy rows and the first chunk of each (plus the total),
-//               placed by exclusive prefix sums (hipCUB) of per-row counts;
+//  * heavy split light rows (r < T), by the column of their last nonzero or in
+//               row order; heavy rows and the first chunk of each (plus the
+//               total); chunks (row, begin, end) of at most c nonzeros in row
+//               and chunk order and their processing order; the entries in that
+//               layout.  Places come from running sums over the rows;
 //  * transpose  the CSR of A^T: a stable radix sort (hipCUB) of the nonzero
 //               positions by column keeps each column's rows ascending, as the
 //               host's counting sort does; row pointers by binary search in
@@ -81,45 +82,6 @@ __global__ __launch_bounds__(256) void k_merge_coords(const int32_t *__restrict_
   }
   coords[2 * u] = (int32_t)lo;
   coords[2 * u + 1] = (int32_t)(d - lo);
-}
-
-__global__ __launch_bounds__(256) void k_split_counts(const int32_t *__restrict__ rowptr, int32_t m, int32_t T,
-                                                      int32_t c, int32_t *__restrict__ light,
-                                                      int32_t *__restrict__ heavy, int32_t *__restrict__ pieces) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= m) return;
-  const int64_t r = rowptr[i + 1] - rowptr[i];
-  const bool is_light = r < T;
-  light[i] = is_light ? 1 : 0;
-  heavy[i] = is_light ? 0 : 1;
-  pieces[i] = is_light ? 0 : (int32_t)((r + c - 1) / c);
-}
-
-__global__ __launch_bounds__(256) void k_split_fill(const int32_t *__restrict__ rowptr, int32_t m, int32_t T,
-                                                    int32_t c, const int64_t *__restrict__ light_pos,
-                                                    const int64_t *__restrict__ heavy_pos,
-                                                    const int64_t *__restrict__ chunk_pos,
-                                                    int32_t *__restrict__ light, int32_t *__restrict__ chunks,
-                                                    int32_t *__restrict__ heavy_rows,
-                                                    int32_t *__restrict__ heavy_ptr) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= m) return;
-  const int32_t p0 = rowptr[i], p1 = rowptr[i + 1];
-  if (p1 - p0 < T) {
-    light[light_pos[i]] = (int32_t)i;
-    return;
-  }
-  const int64_t h = heavy_pos[i], first = chunk_pos[i];
-  heavy_rows[h] = (int32_t)i;
-  heavy_ptr[h] = (int32_t)first;
-  const int32_t n_pieces = (int32_t)(((int64_t)(p1 - p0) + c - 1) / c);
-  for (int32_t q = 0; q < n_pieces; ++q) {
-    const int32_t b = p0 + q * c;
-    int32_t *ch = chunks + 3 * (first + q);
-    ch[0] = (int32_t)i;
-    ch[1] = b;
-    ch[2] = min(p1, b + c);
-  }
 }
 
 // the row holding nonzero p of a valid CSR (m >= 1): the last row starting at
@@ -357,173 +319,300 @@ hipError_t dev_merge_coords(const int32_t *rowptr, int32_t m, int64_t nnz, int32
   return hipGetLastError();
 }
 
-__global__ void k_last_col_keys(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx, int32_t k,
-                                const int32_t *__restrict__ light, int64_t n, int32_t *__restrict__ keys) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int32_t r = light[i];
-  keys[i] = rowptr[r + 1] > rowptr[r] ? colidx[rowptr[r + 1] - 1] : k;
+namespace {
+
+// ---- heavy split
+// Rows are taken 1,024 per workgroup, four consecutive ones per thread.  Three
+// running sums place everything: heavy rows (light rows are the others), their
+// chunks, and their nonzeros.  One pass adds them per workgroup, one workgroup
+// scans those sums (the host reads the three totals to size the arrays), and a
+// second pass writes.  Chunks are then cut in the split layout's coordinates by
+// one thread each, and the entries moved by 16 lanes per light row and a wave per
+// chunk, so a row of any length is spread over the chip.
+constexpr int kSplitRows = 1024;
+
+struct SplitSums {
+  uint32_t heavy, chunks, nnz;
+};
+__device__ __forceinline__ SplitSums operator+(SplitSums a, SplitSums b) {
+  return {a.heavy + b.heavy, a.chunks + b.chunks, a.nnz + b.nnz};
+}
+__device__ __forceinline__ SplitSums shfl_up(SplitSums a, int d) {
+  return {(uint32_t)__shfl_up((int)a.heavy, d, 64), (uint32_t)__shfl_up((int)a.chunks, d, 64),
+          (uint32_t)__shfl_up((int)a.nnz, d, 64)};
+}
+__device__ __forceinline__ SplitSums split_row(const int32_t *__restrict__ rowptr, int64_t i, int32_t m, int32_t T,
+                                               int32_t c, int32_t &p0, int32_t &len) {
+  if (i >= m) return {0, 0, 0};
+  p0 = rowptr[i];
+  len = rowptr[i + 1] - p0;
+  if (len < T) return {0, 0, 0};
+  return {1, (uint32_t)(((int64_t)len + c - 1) / c), (uint32_t)len};
 }
 
-hipError_t dev_light_by_last_col(const int32_t *rowptr, const int32_t *colidx, int32_t k, int32_t *light,
-                                 int64_t n_light, hipStream_t s) {
-  if (n_light < 2) return hipSuccess;
-  if (n_light > INT32_MAX) return hipErrorInvalidValue;
-  const int n = (int)n_light;
-  Scratch sc(s);  // keys in / out, rows out, sort workspace
-  hipError_t e;
-  if ((e = pool_alloc(&sc.p[0], 2 * sizeof(int32_t) * (size_t)n)) != hipSuccess) return e;
-  if ((e = pool_alloc(&sc.p[1], sizeof(int32_t) * (size_t)n)) != hipSuccess) return e;
-  int32_t *kin = static_cast<int32_t *>(sc.p[0]), *kout = kin + n, *rout = static_cast<int32_t *>(sc.p[1]);
-  hipLaunchKernelGGL(k_last_col_keys, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, rowptr, colidx, k, light,
-                     n_light, kin);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  int bits = 1;
-  while (bits < 31 && ((int64_t)1 << bits) <= (int64_t)k) ++bits;  // keys lie in [0, k]
-  size_t tmp = 0;
-  if ((e = hipcub::DeviceRadixSort::SortPairs(nullptr, tmp, kin, kout, light, rout, n, 0, bits, s)) != hipSuccess)
-    return e;
-  if ((e = pool_alloc(&sc.p[2], std::max<size_t>(tmp, 1))) != hipSuccess) return e;
-  if ((e = hipcub::DeviceRadixSort::SortPairs(sc.p[2], tmp, kin, kout, light, rout, n, 0, bits, s)) != hipSuccess)
-    return e;
-  if ((e = hipMemcpyAsync(light, rout, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToDevice, s)) != hipSuccess)
-    return e;
-  return hipStreamSynchronize(s);  // the scratch arrays are freed on return
+// Exclusive prefix of v over the workgroup (N waves), and the total.
+template <int N>
+__device__ __forceinline__ SplitSums block_prefix(SplitSums v, SplitSums *__restrict__ waves, SplitSums &total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  SplitSums x = v;
+  for (int d = 1; d < 64; d <<= 1) {
+    const SplitSums y = shfl_up(x, d);
+    if (lane >= d) x = x + y;
+  }
+  __syncthreads();
+  if (lane == 63) waves[wave] = x;
+  __syncthreads();
+  SplitSums before{0, 0, 0};
+  total = {0, 0, 0};
+  for (int w = 0; w < N; ++w) {
+    if (w < wave) before = before + waves[w];
+    total = total + waves[w];
+  }
+  return {before.heavy + x.heavy - v.heavy, before.chunks + x.chunks - v.chunks, before.nnz + x.nnz - v.nnz};
 }
 
-__global__ void k_chunk_mid_keys(const int32_t *__restrict__ colidx, const int32_t *__restrict__ chunks, int64_t n,
-                                 int32_t *__restrict__ keys, int32_t *__restrict__ idx) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= n) return;
-  const int64_t b = chunks[3 * q + 1], e = chunks[3 * q + 2];
-  keys[q] = colidx[(b + e) / 2];
+__global__ __launch_bounds__(256) void k_split_sums(const int32_t *__restrict__ rowptr, int32_t m, int32_t T,
+                                                    int32_t c, SplitSums *__restrict__ sums) {
+  __shared__ SplitSums waves[4];
+  SplitSums v{0, 0, 0}, total;
+  int32_t p0, len;
+  for (int t = 0; t < 4; ++t)
+    v = v + split_row(rowptr, (int64_t)blockIdx.x * kSplitRows + threadIdx.x * 4 + t, m, T, c, p0, len);
+  block_prefix<4>(v, waves, total);
+  if (threadIdx.x == 0) sums[blockIdx.x] = total;
+}
+
+// In place: sums[b] = the sum before workgroup b, sums[nb] = the total.
+__global__ __launch_bounds__(1024) void k_split_scan(SplitSums *__restrict__ sums, int32_t nb) {
+  __shared__ SplitSums waves[16];
+  SplitSums carry{0, 0, 0};
+  for (int32_t b0 = 0; b0 < nb; b0 += 1024) {  // the same trip count for every thread
+    const int32_t b = b0 + (int32_t)threadIdx.x;
+    SplitSums v{0, 0, 0}, total;
+    if (b < nb) v = sums[b];
+    const SplitSums before = block_prefix<16>(v, waves, total);
+    if (b < nb) sums[b] = carry + before;
+    carry = carry + total;
+  }
+  if (threadIdx.x == 0) sums[nb] = carry;
+}
+
+__global__ __launch_bounds__(256) void k_split_fill(const int32_t *__restrict__ rowptr, int32_t m, int32_t T,
+                                                    int32_t c, const SplitSums *__restrict__ sums, int32_t nb,
+                                                    int32_t *__restrict__ light, int32_t *__restrict__ heavy_rows,
+                                                    int32_t *__restrict__ heavy_ptr,
+                                                    uint32_t *__restrict__ heavy_start) {
+  __shared__ SplitSums waves[4];
+  const int64_t i0 = (int64_t)blockIdx.x * kSplitRows + threadIdx.x * 4;
+  SplitSums r[4], v{0, 0, 0}, total;
+  int32_t p0, len;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    r[t] = split_row(rowptr, i0 + t, m, T, c, p0, len);
+    v = v + r[t];
+  }
+  SplitSums at = sums[blockIdx.x] + block_prefix<4>(v, waves, total);
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int64_t i = i0 + t;
+    if (i < m) {
+      if (r[t].heavy) {
+        heavy_rows[at.heavy] = (int32_t)i;
+        heavy_ptr[at.heavy] = (int32_t)at.chunks;
+        heavy_start[at.heavy] = at.nnz;
+      } else {
+        light[i - at.heavy] = (int32_t)i;
+      }
+    }
+    at = at + r[t];
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) heavy_ptr[sums[nb].heavy] = (int32_t)sums[nb].chunks;
+}
+
+// Chunk q: (row, begin, end) in the split layout, where the heavy rows' entries
+// follow the light_nnz entries of the light rows; its middle column as sort key
+// and, for the move, where its entries lie in the input.
+__global__ __launch_bounds__(256) void k_split_chunks(const int32_t *__restrict__ rowptr,
+                                                      const int32_t *__restrict__ colidx,
+                                                      const int32_t *__restrict__ heavy_rows,
+                                                      const int32_t *__restrict__ heavy_ptr,
+                                                      const uint32_t *__restrict__ heavy_start, int32_t n_heavy,
+                                                      int32_t n_chunks, int32_t c, uint32_t light_nnz,
+                                                      int32_t *__restrict__ chunks, int32_t *__restrict__ from,
+                                                      int32_t *__restrict__ keys, int32_t *__restrict__ idx) {
+  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (q >= n_chunks) return;
+  int32_t lo = 0, hi = n_heavy - 1;  // the last heavy row whose chunks start at or before q
+  while (lo < hi) {
+    const int32_t mid = lo + (hi - lo + 1) / 2;
+    if (heavy_ptr[mid] <= q) lo = mid;
+    else hi = mid - 1;
+  }
+  const int32_t row = heavy_rows[lo], p0 = rowptr[row], len = rowptr[row + 1] - p0;
+  const int64_t off = (q - heavy_ptr[lo]) * c;
+  const int32_t take = (int32_t)min((int64_t)c, len - off);
+  const int64_t begin = (int64_t)light_nnz + heavy_start[lo] + off;
+  chunks[3 * q] = row;
+  chunks[3 * q + 1] = (int32_t)begin;
+  chunks[3 * q + 2] = (int32_t)(begin + take);
+  from[q] = (int32_t)(p0 + off);
+  keys[q] = colidx[p0 + off + take / 2];  // the entry at (begin + end) / 2 of the split layout
   idx[q] = (int32_t)q;
 }
 
-hipError_t dev_chunk_order(const int32_t *colidx, const int32_t *chunks, int64_t n_chunks, int32_t k, int32_t order,
-                           int32_t *corder, hipStream_t s) {
-  if (n_chunks == 0) return hipSuccess;
-  if (n_chunks > INT32_MAX) return hipErrorInvalidValue;
-  const int n = (int)n_chunks;
-  if (order != 2 || n < 2) {
-    hipLaunchKernelGGL(k_iota, dim3(grid_for(n)), dim3(256), 0, s, corder, (int64_t)n);
-    return hipGetLastError();
-  }
-  Scratch sc(s);  // keys in / out, indices in, sort workspace
-  hipError_t e;
-  if ((e = pool_alloc(&sc.p[0], 2 * sizeof(int32_t) * (size_t)n)) != hipSuccess) return e;
-  if ((e = pool_alloc(&sc.p[1], sizeof(int32_t) * (size_t)n)) != hipSuccess) return e;
-  int32_t *kin = static_cast<int32_t *>(sc.p[0]), *kout = kin + n, *iin = static_cast<int32_t *>(sc.p[1]);
-  hipLaunchKernelGGL(k_chunk_mid_keys, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, colidx, chunks,
-                     (int64_t)n, kin, iin);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  int bits = 1;
-  while (bits < 31 && ((int64_t)1 << bits) < (int64_t)k) ++bits;  // keys lie in [0, k)
-  size_t tmp = 0;
-  // a radix sort is stable: equal keys keep ascending chunk indices
-  if ((e = hipcub::DeviceRadixSort::SortPairs(nullptr, tmp, kin, kout, iin, corder, n, 0, bits, s)) != hipSuccess)
-    return e;
-  if ((e = pool_alloc(&sc.p[2], std::max<size_t>(tmp, 1))) != hipSuccess) return e;
-  if ((e = hipcub::DeviceRadixSort::SortPairs(sc.p[2], tmp, kin, kout, iin, corder, n, 0, bits, s)) != hipSuccess)
-    return e;
-  return hipStreamSynchronize(s);  // the scratch arrays are freed on return
-}
-
-__global__ void k_row_lengths(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ rows, int64_t n,
-                              int64_t *__restrict__ len) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) len[i] = (int64_t)rowptr[rows[i] + 1] - rowptr[rows[i]];
-}
-
-// One wave per listed row: its entries to [start[i], start[i] + length).
-__global__ void k_move_rows(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ colidx,
-                            const float *__restrict__ vals, const int32_t *__restrict__ rows,
-                            const int64_t *__restrict__ start, int64_t base, int64_t n,
-                            int32_t *__restrict__ colidx_out, float *__restrict__ vals_out) {
-  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+__global__ __launch_bounds__(256) void k_last_col_keys(const int32_t *__restrict__ rowptr,
+                                                       const int32_t *__restrict__ colidx, int32_t k,
+                                                       const int32_t *__restrict__ light, int64_t n,
+                                                       int32_t *__restrict__ keys) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
-  const int32_t r = rows[i];
-  const int32_t p0 = rowptr[r], len = rowptr[r + 1] - p0;
-  const int64_t q0 = base + start[i];
-  for (int32_t t = threadIdx.x & 63; t < len; t += 64) {
+  const int32_t r = light[i], p1 = rowptr[r + 1];
+  keys[i] = p1 > rowptr[r] ? colidx[p1 - 1] : k;
+}
+
+// Lengths of the light rows in list order, and a last 0 (their exclusive sum is
+// the row pointers and the total).
+__global__ __launch_bounds__(256) void k_light_lengths(const int32_t *__restrict__ rowptr,
+                                                       const int32_t *__restrict__ light, int64_t n,
+                                                       int32_t *__restrict__ len) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) len[i] = rowptr[light[i] + 1] - rowptr[light[i]];
+  else if (i == n) len[i] = 0;
+}
+
+// W lanes per light row.
+template <int W>
+__global__ __launch_bounds__(256) void k_move_light(const int32_t *__restrict__ rowptr,
+                                                    const int32_t *__restrict__ colidx,
+                                                    const float *__restrict__ vals,
+                                                    const int32_t *__restrict__ light, int64_t n,
+                                                    const int32_t *__restrict__ lptr,
+                                                    int32_t *__restrict__ colidx_out, float *__restrict__ vals_out) {
+  const int64_t i = (int64_t)blockIdx.x * (256 / W) + threadIdx.x / W;
+  if (i >= n) return;
+  const int32_t p0 = rowptr[light[i]], q0 = lptr[i], len = lptr[i + 1] - q0;
+  for (int32_t t = threadIdx.x & (W - 1); t < len; t += W) {
     colidx_out[q0 + t] = colidx[p0 + t];
     vals_out[q0 + t] = vals[p0 + t];
   }
 }
 
-__global__ void k_lptr_from_starts(const int64_t *__restrict__ start, const int64_t *__restrict__ len, int64_t n,
-                                   int32_t *__restrict__ lptr) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) lptr[i] = (int32_t)start[i];
-  if (i == n - 1) lptr[n] = (int32_t)(start[i] + len[i]);
-}
-
-// Heavy row h: its chunks move by (new start - old start).
-__global__ void k_shift_chunks(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ heavy_rows,
-                               const int32_t *__restrict__ heavy_ptr, const int64_t *__restrict__ start,
-                               int64_t base, int64_t n_heavy, int32_t *__restrict__ chunks) {
-  const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (h >= n_heavy) return;
-  const int64_t shift = base + start[h] - rowptr[heavy_rows[h]];
-  for (int32_t q = heavy_ptr[h]; q < heavy_ptr[h + 1]; ++q) {
-    chunks[3 * (int64_t)q + 1] = (int32_t)(chunks[3 * (int64_t)q + 1] + shift);
-    chunks[3 * (int64_t)q + 2] = (int32_t)(chunks[3 * (int64_t)q + 2] + shift);
+// A wave per chunk.
+__global__ __launch_bounds__(256) void k_move_chunks(const int32_t *__restrict__ colidx,
+                                                     const float *__restrict__ vals,
+                                                     const int32_t *__restrict__ chunks,
+                                                     const int32_t *__restrict__ from, int64_t n,
+                                                     int32_t *__restrict__ colidx_out, float *__restrict__ vals_out) {
+  const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (q >= n) return;
+  const int32_t p0 = from[q], b = chunks[3 * q + 1], len = chunks[3 * q + 2] - b;
+  for (int32_t t = threadIdx.x & 63; t < len; t += 64) {
+    colidx_out[b + t] = colidx[p0 + t];
+    vals_out[b + t] = vals[p0 + t];
   }
 }
 
-hipError_t dev_split_layout(const int32_t *rowptr, const int32_t *colidx, const float *vals, int64_t nnz,
-                            const int32_t *light, int64_t n_light, const int32_t *heavy_rows,
-                            const int32_t *heavy_ptr, int64_t n_heavy, int32_t *lptr, int32_t *colidx_out,
-                            float *vals_out, int32_t *chunks, hipStream_t s) {
-  (void)nnz;
-  Scratch sc(s);  // lengths and starts (int64) of the light rows, then of the heavy rows; scan workspace
+// Stable radix sort of (key, value) pairs by the low `bits` bits.
+hipError_t sort_pairs(Scratch &sc, int slot, const int32_t *keys, int32_t *keys_out, const int32_t *vals,
+                      int32_t *vals_out, int n, int bits, hipStream_t s) {
+  size_t tmp = 0;
+  hipError_t e = hipcub::DeviceRadixSort::SortPairs(nullptr, tmp, keys, keys_out, vals, vals_out, n, 0, bits, s);
+  if (e == hipSuccess) e = pool_alloc(&sc.p[slot], std::max<size_t>(tmp, 1));
+  if (e == hipSuccess)
+    e = hipcub::DeviceRadixSort::SortPairs(sc.p[slot], tmp, keys, keys_out, vals, vals_out, n, 0, bits, s);
+  return e;
+}
+
+}  // namespace
+
+hipError_t dev_split(const int32_t *rowptr, const int32_t *colidx, const float *vals, int32_t m, int32_t k, int64_t nnz,
+                     int32_t T, int32_t c, int32_t light_order, int32_t chunk_order,
+                     const std::function<void *(size_t)> &alloc, hipStream_t s, DeviceSplit *out) {
   hipError_t e;
-  const int64_t nl = std::max<int64_t>(1, n_light), nh = std::max<int64_t>(1, n_heavy);
-  if ((e = pool_alloc(&sc.p[0], 2 * sizeof(int64_t) * (size_t)(nl + nh))) != hipSuccess) return e;
-  int64_t *len_l = static_cast<int64_t *>(sc.p[0]), *st_l = len_l + nl, *len_h = st_l + nl, *st_h = len_h + nh;
-  int64_t light_total = 0;
+  const int32_t nb = (int32_t)(((int64_t)m + kSplitRows - 1) / kSplitRows);
+  Scratch sc(s);
+  if ((e = pool_alloc(&sc.p[0], sizeof(SplitSums) * ((size_t)nb + 1))) != hipSuccess) return e;
+  SplitSums *sums = static_cast<SplitSums *>(sc.p[0]);
+  if (nb > 0)
+    hipLaunchKernelGGL(k_split_sums, dim3((uint32_t)nb), dim3(256), 0, s, rowptr, m, T, c, sums);
+  hipLaunchKernelGGL(k_split_scan, dim3(1), dim3(1024), 0, s, sums, nb);
+  SplitSums tot{0, 0, 0};
+  if ((e = hipGetLastError()) != hipSuccess ||
+      (e = hipMemcpyAsync(&tot, sums + nb, sizeof(tot), hipMemcpyDeviceToHost, s)) != hipSuccess ||
+      (e = hipStreamSynchronize(s)) != hipSuccess)
+    return e;
+  const int64_t n_heavy = tot.heavy, n_chunks = tot.chunks, n_light = (int64_t)m - n_heavy;
+  const uint32_t light_nnz = (uint32_t)(nnz - (int64_t)tot.nnz);
+  if (n_chunks > INT32_MAX) return hipErrorInvalidValue;
+  auto ints = [&](int64_t n) { return static_cast<int32_t *>(alloc(sizeof(int32_t) * (size_t)std::max<int64_t>(1, n))); };
+  out->n_light = n_light;
+  out->n_heavy = n_heavy;
+  out->n_chunks = n_chunks;
+  out->light = ints(n_light);
+  out->lptr = ints(n_light + 1);
+  out->colidx = ints(nnz);
+  out->vals = reinterpret_cast<float *>(ints(nnz));
+  out->chunks = ints(3 * n_chunks);
+  out->corder = ints(n_chunks);
+  out->heavy_rows = ints(n_heavy);
+  out->heavy_ptr = ints(n_heavy + 1);
+  if (!out->light || !out->lptr || !out->colidx || !out->vals || !out->chunks || !out->corder || !out->heavy_rows ||
+      !out->heavy_ptr)
+    return hipErrorOutOfMemory;
+  // heavy starts; chunk sources, keys in and out, indices; light keys in and out, rows before the sort
+  const size_t nh = (size_t)n_heavy, nc = (size_t)n_chunks, nl = (size_t)n_light;
+  if ((e = pool_alloc(&sc.p[1], sizeof(int32_t) * (nh + 4 * nc + 3 * nl + 1))) != hipSuccess) return e;
+  int32_t *w = static_cast<int32_t *>(sc.p[1]);
+  uint32_t *hstart = reinterpret_cast<uint32_t *>(w);
+  int32_t *from = w + nh, *ckey = from + nc, *ckey2 = ckey + nc, *cidx = ckey2 + nc;
+  int32_t *lkey = cidx + nc, *lkey2 = lkey + nl + 1, *lraw = lkey2 + nl;  // lkey also holds n_light + 1 lengths
+  const bool by_last = light_order == 2 && n_light > 1, by_mid = chunk_order == 2 && n_chunks > 1;
+  int bits = 1;
+  while (bits < 31 && ((int64_t)1 << bits) <= (int64_t)k) ++bits;  // light keys lie in [0, k], chunk keys below k
+  if (nb > 0)
+    hipLaunchKernelGGL(k_split_fill, dim3((uint32_t)nb), dim3(256), 0, s, rowptr, m, T, c, sums, nb,
+                       by_last ? lraw : out->light, out->heavy_rows, out->heavy_ptr, hstart);
+  else
+    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(256), 0, s, out->heavy_ptr, (int64_t)1, 0);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (n_chunks > 0) {
+    hipLaunchKernelGGL(k_split_chunks, dim3(grid_for(n_chunks)), dim3(256), 0, s, rowptr, colidx, out->heavy_rows,
+                       out->heavy_ptr, hstart, (int32_t)n_heavy, (int32_t)n_chunks, c, light_nnz, out->chunks, from,
+                       ckey, by_mid ? cidx : out->corder);
+    hipLaunchKernelGGL(k_move_chunks, dim3((uint32_t)((n_chunks + 3) / 4)), dim3(256), 0, s, colidx, vals,
+                       out->chunks, from, n_chunks, out->colidx, out->vals);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (by_mid && (e = sort_pairs(sc, 2, ckey, ckey2, cidx, out->corder, (int)n_chunks, bits, s)) != hipSuccess)
+      return e;
+  }
+  if (by_last) {
+    hipLaunchKernelGGL(k_last_col_keys, dim3(grid_for(n_light)), dim3(256), 0, s, rowptr, colidx, k, lraw, n_light,
+                       lkey);
+    if ((e = hipGetLastError()) != hipSuccess ||
+        (e = sort_pairs(sc, 3, lkey, lkey2, lraw, out->light, (int)n_light, bits, s)) != hipSuccess)
+      return e;
+  }
+  hipLaunchKernelGGL(k_light_lengths, dim3(grid_for(n_light + 1)), dim3(256), 0, s, rowptr, out->light, n_light, lkey);
+  size_t tmp = 0;
+  if ((e = hipGetLastError()) != hipSuccess ||
+      (e = hipcub::DeviceScan::ExclusiveSum(nullptr, tmp, lkey, out->lptr, (size_t)n_light + 1, s)) != hipSuccess ||
+      (e = pool_alloc(&sc.p[4], std::max<size_t>(tmp, 1))) != hipSuccess ||
+      (e = hipcub::DeviceScan::ExclusiveSum(sc.p[4], tmp, lkey, out->lptr, (size_t)n_light + 1, s)) != hipSuccess)
+    return e;
   if (n_light > 0) {
-    const uint32_t g = (uint32_t)((n_light + 255) / 256);
-    hipLaunchKernelGGL(k_row_lengths, dim3(g), dim3(256), 0, s, rowptr, light, n_light, len_l);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    size_t tmp = 0;
-    if ((e = hipcub::DeviceScan::ExclusiveSum(nullptr, tmp, len_l, st_l, (int)n_light, s)) != hipSuccess) return e;
-    if ((e = pool_alloc(&sc.p[1], std::max<size_t>(tmp, 1))) != hipSuccess) return e;
-    if ((e = hipcub::DeviceScan::ExclusiveSum(sc.p[1], tmp, len_l, st_l, (int)n_light, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_lptr_from_starts, dim3(g), dim3(256), 0, s, st_l, len_l, n_light, lptr);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_move_rows, dim3((uint32_t)((n_light + 3) / 4)), dim3(256), 0, s, rowptr, colidx, vals, light,
-                       st_l, (int64_t)0, n_light, colidx_out, vals_out);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    int64_t last[2] = {0, 0};
-    if ((e = hipMemcpyAsync(&last[0], st_l + n_light - 1, sizeof(int64_t), hipMemcpyDeviceToHost, s)) != hipSuccess ||
-        (e = hipMemcpyAsync(&last[1], len_l + n_light - 1, sizeof(int64_t), hipMemcpyDeviceToHost, s)) != hipSuccess ||
-        (e = hipStreamSynchronize(s)) != hipSuccess)
-      return e;
-    light_total = last[0] + last[1];
-  } else {
-    const int32_t zero = 0;
-    if ((e = hipMemcpyAsync(lptr, &zero, sizeof(int32_t), hipMemcpyHostToDevice, s)) != hipSuccess ||
-        (e = hipStreamSynchronize(s)) != hipSuccess)
-      return e;
-  }
-  if (n_heavy > 0) {
-    const uint32_t g = (uint32_t)((n_heavy + 255) / 256);
-    hipLaunchKernelGGL(k_row_lengths, dim3(g), dim3(256), 0, s, rowptr, heavy_rows, n_heavy, len_h);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    size_t tmp = 0;
-    if ((e = hipcub::DeviceScan::ExclusiveSum(nullptr, tmp, len_h, st_h, (int)n_heavy, s)) != hipSuccess) return e;
-    if ((e = pool_alloc(&sc.p[2], std::max<size_t>(tmp, 1))) != hipSuccess) return e;
-    if ((e = hipcub::DeviceScan::ExclusiveSum(sc.p[2], tmp, len_h, st_h, (int)n_heavy, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_move_rows, dim3((uint32_t)((n_heavy + 3) / 4)), dim3(256), 0, s, rowptr, colidx, vals,
-                       heavy_rows, st_h, light_total, n_heavy, colidx_out, vals_out);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_shift_chunks, dim3(g), dim3(256), 0, s, rowptr, heavy_rows, heavy_ptr, st_h, light_total,
-                       n_heavy, chunks);
+    // 8 lanes for short rows on average, else 16
+    if ((int64_t)light_nnz <= 8 * n_light)
+      hipLaunchKernelGGL((k_move_light<8>), dim3((uint32_t)((n_light + 31) / 32)), dim3(256), 0, s, rowptr, colidx,
+                         vals, out->light, n_light, out->lptr, out->colidx, out->vals);
+    else
+      hipLaunchKernelGGL((k_move_light<16>), dim3((uint32_t)((n_light + 15) / 16)), dim3(256), 0, s, rowptr, colidx,
+                         vals, out->light, n_light, out->lptr, out->colidx, out->vals);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  return hipStreamSynchronize(s);  // the scratch arrays are freed on return
+  return hipStreamSynchronize(s);  // the scratch arrays are given back on return
 }
+
+namespace {
 
 // ---- packed column windows over the split layout
 // Light entry p belongs to the light row t with lptr[t] <= p < lptr[t + 1]
@@ -617,6 +706,8 @@ __global__ __launch_bounds__(256) void k_win_codes(const uint64_t *__restrict__ 
   code[p] = hit ? (int32_t)(-2 - (lo - wptr[w])) : col;
   staged[p] = hit ? 1 : 0;
 }
+
+}  // namespace
 
 hipError_t dev_split_windows(const int32_t *lptr, int64_t n_light, int32_t *colidx, int32_t R, int32_t cap,
                              const std::function<void *(size_t)> &alloc, hipStream_t s, int32_t **wptr,
@@ -712,68 +803,6 @@ hipError_t dev_split_windows(const int32_t *lptr, int64_t n_light, int32_t *coli
   for (int64_t w = 0; w < nw; ++w) *wmax = std::max(*wmax, hw[(size_t)w + 1] - hw[(size_t)w]);
   *n_staged = n_kept;
   return hipSuccess;  // synchronised above; the scratch arrays are freed on return
-}
-
-hipError_t dev_heavy_split(const int32_t *rowptr, int32_t m, int32_t T, int32_t c,
-                           const std::function<void *(size_t)> &alloc, hipStream_t s, int32_t **light,
-                           int32_t **chunks, int32_t **heavy_rows, int32_t **heavy_ptr, int64_t *n_light,
-                           int64_t *n_heavy, int64_t *n_chunks) {
-  *light = *chunks = *heavy_rows = *heavy_ptr = nullptr;
-  *n_light = *n_heavy = *n_chunks = 0;
-  const size_t mm = (size_t)std::max(1, m);
-  Scratch sc(s);  // flags / counts (int32 x 3) and their exclusive prefix sums (int64 x 3)
-  hipError_t e;
-  if ((e = pool_alloc(&sc.p[0], 3 * sizeof(int32_t) * mm)) != hipSuccess) return e;
-  if ((e = pool_alloc(&sc.p[1], 3 * sizeof(int64_t) * (mm + 1))) != hipSuccess) return e;
-  int32_t *f = static_cast<int32_t *>(sc.p[0]);
-  int64_t *pos = static_cast<int64_t *>(sc.p[1]);
-  int32_t *fl = f, *fh = f + mm, *fp = f + 2 * mm;
-  int64_t *pl = pos, *ph = pos + (mm + 1), *pp = pos + 2 * (mm + 1);
-  if (m > 0) {
-    hipLaunchKernelGGL(k_split_counts, dim3(grid_for(m)), dim3(256), 0, s, rowptr, m, T, c, fl, fh, fp);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    // exclusive sums over the m rows; each total is the last prefix plus the last count
-    size_t tmp_bytes = 0;
-    if ((e = hipcub::DeviceScan::ExclusiveSum(nullptr, tmp_bytes, fl, pl, m, s)) != hipSuccess) return e;
-    if ((e = pool_alloc(&sc.p[2], std::max<size_t>(tmp_bytes, 1))) != hipSuccess) return e;
-    for (int t = 0; t < 3; ++t) {
-      int32_t *in = t == 0 ? fl : t == 1 ? fh : fp;
-      int64_t *out = t == 0 ? pl : t == 1 ? ph : pp;
-      size_t b = tmp_bytes;
-      if ((e = hipcub::DeviceScan::ExclusiveSum(sc.p[2], b, in, out, m, s)) != hipSuccess) return e;
-    }
-  }
-  // totals: last prefix + last count
-  int64_t last_pos[3] = {0, 0, 0};
-  int32_t last_cnt[3] = {0, 0, 0};
-  if (m > 0) {
-    for (int t = 0; t < 3; ++t) {
-      const int64_t *out = t == 0 ? pl : t == 1 ? ph : pp;
-      const int32_t *in = t == 0 ? fl : t == 1 ? fh : fp;
-      if ((e = hipMemcpyAsync(&last_pos[t], out + (m - 1), sizeof(int64_t), hipMemcpyDeviceToHost, s)) !=
-              hipSuccess ||
-          (e = hipMemcpyAsync(&last_cnt[t], in + (m - 1), sizeof(int32_t), hipMemcpyDeviceToHost, s)) != hipSuccess)
-        return e;
-    }
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-  }
-  *n_light = last_pos[0] + last_cnt[0];
-  *n_heavy = last_pos[1] + last_cnt[1];
-  *n_chunks = last_pos[2] + last_cnt[2];
-  *light = static_cast<int32_t *>(alloc(sizeof(int32_t) * (size_t)std::max<int64_t>(1, *n_light)));
-  *chunks = static_cast<int32_t *>(alloc(3 * sizeof(int32_t) * (size_t)std::max<int64_t>(1, *n_chunks)));
-  *heavy_rows = static_cast<int32_t *>(alloc(sizeof(int32_t) * (size_t)std::max<int64_t>(1, *n_heavy)));
-  *heavy_ptr = static_cast<int32_t *>(alloc(sizeof(int32_t) * (size_t)(*n_heavy + 1)));
-  if (!*light || !*chunks || !*heavy_rows || !*heavy_ptr) return hipErrorOutOfMemory;
-  if (m > 0) {
-    hipLaunchKernelGGL(k_split_fill, dim3(grid_for(m)), dim3(256), 0, s, rowptr, m, T, c, pl, ph, pp, *light,
-                       *chunks, *heavy_rows, *heavy_ptr);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  const int32_t total = (int32_t)*n_chunks;
-  if ((e = hipMemcpyAsync(*heavy_ptr + *n_heavy, &total, sizeof(int32_t), hipMemcpyHostToDevice, s)) != hipSuccess)
-    return e;
-  return hipStreamSynchronize(s);  // the scratch arrays are freed on return
 }
 
 hipError_t dev_block16(const int32_t *rowptr, const int32_t *colidx, const float *vals, int32_t m, int32_t k,

@@ -100,7 +100,7 @@ hipError_t pool_alloc(void **out, size_t bytes);
 void pool_free(void *p, PoolState state);
 
 // convert.hip: conversions and partitions on the device, producing exactly
-// the arrays of the host conversions (ell_convert, merge_split, heavy_split).
+// the arrays of the host conversions (ell_convert, merge_split, ...).
 hipError_t dev_ell(const int32_t *rowptr, const int32_t *colidx, const float *vals, int32_t m, int32_t W,
                    int32_t *ecol, float *eval, hipStream_t s);
 hipError_t dev_merge_coords(const int32_t *rowptr, int32_t m, int64_t nnz, int32_t U, int64_t L, int32_t *coords,
@@ -142,16 +142,20 @@ uint64_t pattern_hash_host(const int32_t *rowptr, const int32_t *colidx, int32_t
 // column ascending.  Waits for the stream.
 hipError_t dev_transpose(const int32_t *rowptr, const int32_t *colidx, const float *vals, int32_t m, int32_t k,
                          int64_t nnz, int32_t *t_rowptr, int32_t *t_colidx, float *t_vals, hipStream_t s);
-// alloc(bytes) returns plan-owned device memory (nullptr on failure); waits for s
-// Writes the heavy-split layout into lptr (|light| + 1), colidx_out and
-// vals_out (nnz each): the light rows' entries in list order, then the heavy
-// rows' in the order of heavy_rows; moves each heavy row's chunks (heavy_ptr
-// groups them; their begin and end are in the input's coordinates on entry)
-// to the new coordinates.  The inputs must not alias the outputs.
-hipError_t dev_split_layout(const int32_t *rowptr, const int32_t *colidx, const float *vals, int64_t nnz,
-                            const int32_t *light, int64_t n_light, const int32_t *heavy_rows,
-                            const int32_t *heavy_ptr, int64_t n_heavy, int32_t *lptr, int32_t *colidx_out,
-                            float *vals_out, int32_t *chunks, hipStream_t s);
+// The heavy-split layout of a valid CSR in device memory: rows of T nonzeros
+// and more are heavy, cut into chunks of at most c.  light_order and
+// chunk_order as in sd_plan_opts_t (1 or 2).  alloc(bytes) returns plan-owned
+// device memory (nullptr on failure).  The same arrays as the host's
+// heavy_split, split_layout and chunk_order.  Waits for the stream.
+struct DeviceSplit {
+  int64_t n_light = 0, n_heavy = 0, n_chunks = 0;
+  int32_t *light = nullptr, *lptr = nullptr, *colidx = nullptr, *chunks = nullptr, *corder = nullptr,
+          *heavy_rows = nullptr, *heavy_ptr = nullptr;
+  float *vals = nullptr;
+};
+hipError_t dev_split(const int32_t *rowptr, const int32_t *colidx, const float *vals, int32_t m, int32_t k, int64_t nnz,
+                     int32_t T, int32_t c, int32_t light_order, int32_t chunk_order,
+                     const std::function<void *(size_t)> &alloc, hipStream_t s, DeviceSplit *out);
 // Packed column windows over a split layout in device memory (lptr [n_light
 // + 1], colidx [nnz], the layout's columns): windows of R light-list
 // positions stage the columns two or more of their rows use, at most cap, the
@@ -162,19 +166,6 @@ hipError_t dev_split_layout(const int32_t *rowptr, const int32_t *colidx, const 
 hipError_t dev_split_windows(const int32_t *lptr, int64_t n_light, int32_t *colidx, int32_t R, int32_t cap,
                              const std::function<void *(size_t)> &alloc, hipStream_t s, int32_t **wptr,
                              int32_t **wcols, int32_t *wmax, int64_t *n_staged, int64_t *staged_uses);
-// Chunk processing order of a split layout: by the column of each chunk's
-// middle entry colidx[(begin + end) / 2], ties by chunk index (order 2), or
-// the chunk list itself (order 1).  corder: n_chunks int32.
-hipError_t dev_chunk_order(const int32_t *colidx, const int32_t *chunks, int64_t n_chunks, int32_t k, int32_t order,
-                           int32_t *corder, hipStream_t s);
-// Reorders the light rows (device, ascending on entry) by the column of their
-// last nonzero, ties by row, empty rows last (a stable radix sort by key).
-hipError_t dev_light_by_last_col(const int32_t *rowptr, const int32_t *colidx, int32_t k, int32_t *light,
-                                 int64_t n_light, hipStream_t s);
-hipError_t dev_heavy_split(const int32_t *rowptr, int32_t m, int32_t T, int32_t c,
-                           const std::function<void *(size_t)> &alloc, hipStream_t s, int32_t **light,
-                           int32_t **chunks, int32_t **heavy_rows, int32_t **heavy_ptr, int64_t *n_light,
-                           int64_t *n_heavy, int64_t *n_chunks);
 
 // analyze.hip: sd_analyze on a CSR matrix whose arrays are device pointers;
 // runs on stream s and waits for it.  Same statistics as the host analysis.

@@ -343,42 +343,44 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
       // CSR families from device memory: device-to-device copies, then the
       // partitions on the device
       I.cache_policy = pc.family == SD_FMT_CSR_MERGE ? pc.policy : 1;
-      if ((st = hip_alloc_copy(p, reinterpret_cast<void **>(&p->d_rowptr), nullptr, 4 * ((size_t)A.m + 1))) !=
-              SD_OK ||
-          (st = hip_alloc_copy(p, reinterpret_cast<void **>(&p->d_colidx), nullptr, 4 * (size_t)A.nnz)) != SD_OK ||
-          (st = hip_alloc_copy(p, reinterpret_cast<void **>(&p->d_vals), nullptr, 4 * (size_t)A.nnz)) != SD_OK)
-        return st;
-      hipError_t e = hipMemcpyAsync(p->d_rowptr, src->rowptr, 4 * ((size_t)A.m + 1), hipMemcpyDeviceToDevice, ds);
-      if (e == hipSuccess && I.cache_policy == 2) {  // tiered: the columns with their cold tags
-        const int64_t budget = (o.hot_budget_kib > 0 ? (int64_t)o.hot_budget_kib << 10 : (int64_t)2 << 20);
-        e = sd::dev_tag_cold(src->colidx, A.nnz, A.k, std::max<int64_t>(1, budget / (4 * (int64_t)n)), p->d_colidx,
-                             &I.hot_columns, &I.hot_nnz, ds);
-      } else if (e == hipSuccess && A.nnz) {
-        e = hipMemcpyAsync(p->d_colidx, src->colidx, 4 * (size_t)A.nnz, hipMemcpyDeviceToDevice, ds);
-      }
-      if (e == hipSuccess && A.nnz)
-        e = hipMemcpyAsync(p->d_vals, src->values, 4 * (size_t)A.nnz, hipMemcpyDeviceToDevice, ds);
-      if (e != hipSuccess) return hip_fail(e);
-      if (pc.family == SD_FMT_CSR_SPLIT || pc.family == SD_FMT_WIN) {
-        auto alloc = [&](size_t bytes) -> void * {
-          void *q = nullptr;
-          return hip_alloc_copy(p, &q, nullptr, bytes) == SD_OK ? q : nullptr;
-        };
-        e = sd::dev_heavy_split(src->rowptr, A.m, pc.T, pc.c, alloc, ds, &p->d_light, &p->d_chunks,
-                                &p->d_heavy_rows, &p->d_heavy_ptr, &I.n_light, &I.n_heavy, &I.n_chunks);
-        if (e == hipSuccess && light_order == 2)
-          e = sd::dev_light_by_last_col(src->rowptr, src->colidx, A.k, p->d_light, I.n_light, ds);
-        // the split layout, over the copies just made of rowptr / colidx / values
-        if (e == hipSuccess)
-          e = sd::dev_split_layout(src->rowptr, src->colidx, src->values, A.nnz, p->d_light, I.n_light,
-                                   p->d_heavy_rows, p->d_heavy_ptr, I.n_heavy, p->d_rowptr, p->d_colidx,
-                                   p->d_vals, p->d_chunks, ds);
-        if (e != hipSuccess) return hip_fail(e);
-        if ((st = hip_alloc_copy(p, reinterpret_cast<void **>(&p->d_corder), nullptr, 4 * (size_t)I.n_chunks)) !=
-            SD_OK)
+      auto alloc = [&](size_t bytes) -> void * {
+        void *q = nullptr;
+        return hip_alloc_copy(p, &q, nullptr, bytes) == SD_OK ? q : nullptr;
+      };
+      hipError_t e = hipSuccess;
+      if (pc.family != SD_FMT_CSR_SPLIT && pc.family != SD_FMT_WIN) {
+        if ((st = hip_alloc_copy(p, reinterpret_cast<void **>(&p->d_rowptr), nullptr, 4 * ((size_t)A.m + 1))) !=
+                SD_OK ||
+            (st = hip_alloc_copy(p, reinterpret_cast<void **>(&p->d_colidx), nullptr, 4 * (size_t)A.nnz)) != SD_OK ||
+            (st = hip_alloc_copy(p, reinterpret_cast<void **>(&p->d_vals), nullptr, 4 * (size_t)A.nnz)) != SD_OK)
           return st;
-        e = sd::dev_chunk_order(p->d_colidx, p->d_chunks, I.n_chunks, A.k, chunk_ord, p->d_corder, ds);
+        e = hipMemcpyAsync(p->d_rowptr, src->rowptr, 4 * ((size_t)A.m + 1), hipMemcpyDeviceToDevice, ds);
+        if (e == hipSuccess && I.cache_policy == 2) {  // tiered: the columns with their cold tags
+          const int64_t budget = (o.hot_budget_kib > 0 ? (int64_t)o.hot_budget_kib << 10 : (int64_t)2 << 20);
+          e = sd::dev_tag_cold(src->colidx, A.nnz, A.k, std::max<int64_t>(1, budget / (4 * (int64_t)n)), p->d_colidx,
+                               &I.hot_columns, &I.hot_nnz, ds);
+        } else if (e == hipSuccess && A.nnz) {
+          e = hipMemcpyAsync(p->d_colidx, src->colidx, 4 * (size_t)A.nnz, hipMemcpyDeviceToDevice, ds);
+        }
+        if (e == hipSuccess && A.nnz)
+          e = hipMemcpyAsync(p->d_vals, src->values, 4 * (size_t)A.nnz, hipMemcpyDeviceToDevice, ds);
         if (e != hipSuccess) return hip_fail(e);
+      } else {
+        sd::DeviceSplit sp;
+        e = sd::dev_split(src->rowptr, src->colidx, src->values, A.m, A.k, A.nnz, pc.T, pc.c, light_order, chunk_ord,
+                          alloc, ds, &sp);
+        if (e != hipSuccess) return hip_fail(e);
+        I.n_light = sp.n_light;
+        I.n_heavy = sp.n_heavy;
+        I.n_chunks = sp.n_chunks;
+        p->d_light = sp.light;
+        p->d_rowptr = sp.lptr;
+        p->d_colidx = sp.colidx;
+        p->d_vals = sp.vals;
+        p->d_chunks = sp.chunks;
+        p->d_corder = sp.corder;
+        p->d_heavy_rows = sp.heavy_rows;
+        p->d_heavy_ptr = sp.heavy_ptr;
         I.chunk_order = chunk_ord;
         I.light_order = light_order;
         I.heavy_threshold = pc.T;
@@ -402,7 +404,8 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
           m_rep += 4 * (n_windows + 1) + 4 * staged;
           units = I.n_chunks + n_windows;
         }
-      } else if (pc.family == SD_FMT_CSR_MERGE) {
+      }
+      if (pc.family == SD_FMT_CSR_MERGE) {
         const int64_t total = (int64_t)A.m + A.nnz;
         const int64_t L = std::max<int64_t>(1, (total + pc.U - 1) / pc.U);
         if ((st = hip_alloc_copy(p, reinterpret_cast<void **>(&p->d_coords), nullptr,
