@@ -275,9 +275,9 @@ struct StripSums {
   }
 };
 
-__device__ __forceinline__ bool entry_bad(const int32_t *__restrict__ colidx, int32_t p, int32_t row_start, int32_t c,
-                                          int32_t k) {
-  return c < 0 || c >= k || (p > row_start && colidx[p - 1] >= c);
+// prev: the column of entry p - 1 (any value at a row's start)
+__device__ __forceinline__ bool entry_bad(int32_t p, int32_t row_start, int32_t c, int32_t prev, int32_t k) {
+  return c < 0 || c >= k || (p > row_start && prev >= c);
 }
 
 // Short strips, one wave each: an LDS table of at least twice the entries.
@@ -314,18 +314,22 @@ __global__ __launch_bounds__(256) void k_an_strips(const int32_t *__restrict__ r
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    int32_t fresh_here = 0;
+    int32_t fresh_here = 0, next = p0 + lane < p1 ? colidx[p0 + lane] : 0, last = 0;
     for (int32_t q = p0; q < p1; q += 64) {  // wave-uniform
       const int32_t p = q + lane;
       const bool in = p < p1;
-      const int32_t c = in ? colidx[p] : 0;
+      const int32_t c = next;
+      if (p1 - p > 64) next = colidx[p + 64];  // behind this turn's work
       if constexpr (LB == 4) {
+        int32_t prev = __shfl_up(c, 1, 64);
+        if (lane == 0) prev = last;
+        last = __shfl(c, 63, 64);
         int r = 0;  // the last row starting at or before p
 #pragma unroll
         for (int st = B / 2; st >= 1; st >>= 1) r += __shfl(rp, r + st, 64) <= p ? st : 0;
         const int32_t rs = __shfl(rp, r, 64);
         if (in) {
-          sum.bad |= entry_bad(colidx, p, rs, c, k);
+          sum.bad |= entry_bad(p, rs, c, prev, k);
           sum.diag += c == s * B + r;
         }
       }
@@ -352,8 +356,8 @@ __global__ __launch_bounds__(256) void k_an_strips(const int32_t *__restrict__ r
   sum.template flush<LB, ALL>(agg, part);
 }
 
-// Middling strips, one workgroup of 512 threads each.  Longer ones are checked
-// here (every entry is read once, in order) and go to the list of long strips.
+// Middling strips, one workgroup of 512 threads each; longer ones go to the
+// list of long strips.
 template <int LB, bool ALL>
 __global__ __launch_bounds__(512) void k_an_strips_mid(const int32_t *__restrict__ rowptr,
                                                        const int32_t *__restrict__ colidx, int32_t m, int32_t k,
@@ -361,10 +365,8 @@ __global__ __launch_bounds__(512) void k_an_strips_mid(const int32_t *__restrict
                                                        int32_t *__restrict__ big, DevAgg *__restrict__ agg) {
   constexpr bool kFill = LB == 4 && ALL;
   constexpr int B = 1 << LB;
-  constexpr int lg = 13;
-  static_assert((1 << lg) >= 2 * kMid, "the table holds at most half its slots");
-  __shared__ uint32_t tab[1 << lg];
-  __shared__ uint32_t cnt[kFill ? (1 << lg) / 2 : 1];  // 16-bit counters: at most kMid entries
+  __shared__ uint32_t tab[2 * kMid];
+  __shared__ uint32_t cnt[kFill ? kMid : 1];  // 16-bit counters: at most kMid entries
   __shared__ int32_t rps[B + 1];
   __shared__ u64 part[8];
   __shared__ int32_t found;
@@ -376,12 +378,17 @@ __global__ __launch_bounds__(512) void k_an_strips_mid(const int32_t *__restrict
     __syncthreads();
     if (threadIdx.x <= B) rps[threadIdx.x] = rowptr[min(s * B + threadIdx.x, (int64_t)m)];
     if (threadIdx.x == 0) found = 0;
+    __syncthreads();
+    const int32_t p0 = rps[0], p1 = rps[B];
+    if (p1 - p0 > kMid) {  // workgroup-uniform
+      if (threadIdx.x == 0) big[atomicAdd(&agg->n_big[LB - 2], 1u)] = (int32_t)s;
+      continue;
+    }
+    const int lg = 33 - __builtin_clz((uint32_t)(p1 - p0) - 1u);  // more than kSmall entries: 2^lg at least twice them
     for (uint32_t i = threadIdx.x; i < (1u << lg); i += 512) tab[i] = UINT32_MAX;
     if constexpr (kFill)
       for (uint32_t i = threadIdx.x; i < (1u << lg) / 2; i += 512) cnt[i] = 0;
     __syncthreads();
-    const int32_t p0 = rps[0], p1 = rps[B];
-    const bool counts = p1 - p0 <= kMid;
     int32_t fresh_here = 0;
     for (int64_t pp = (int64_t)p0 + threadIdx.x; pp < p1; pp += 512) {
       const int32_t p = (int32_t)pp;
@@ -390,22 +397,14 @@ __global__ __launch_bounds__(512) void k_an_strips_mid(const int32_t *__restrict
         int r = 0;
 #pragma unroll
         for (int st = B / 2; st >= 1; st >>= 1) r += rps[r + st] <= p ? st : 0;
-        sum.bad |= entry_bad(colidx, p, rps[r], c, k);
+        sum.bad |= entry_bad(p, rps[r], c, p > p0 ? colidx[p - 1] : 0, k);
         sum.diag += c == s * B + r;
-      } else if (!counts) {
-        break;  // checked at b = 16
       }
-      if (counts) {
-        bool fresh;
-        const uint32_t h = table_slot(tab, (1u << lg) - 1, lg, (uint32_t)c >> LB, fresh);
-        fresh_here += fresh;
-        if constexpr (kFill) atomicAdd(&cnt[h >> 1], 1u << (16 * (h & 1)));
-        (void)h;
-      }
-    }
-    if (!counts) {
-      if (threadIdx.x == 0) big[atomicAdd(&agg->n_big[LB - 2], 1u)] = (int32_t)s;
-      continue;
+      bool fresh;
+      const uint32_t h = table_slot(tab, (1u << lg) - 1, lg, (uint32_t)c >> LB, fresh);
+      fresh_here += fresh;
+      if constexpr (kFill) atomicAdd(&cnt[h >> 1], 1u << (16 * (h & 1)));
+      (void)h;
     }
     sum.blocks += (u64)fresh_here;
     if constexpr (LB == 4) {
@@ -423,12 +422,17 @@ __global__ __launch_bounds__(512) void k_an_strips_mid(const int32_t *__restrict
   sum.template flush<LB, ALL>(agg, part);
 }
 
-// Long strips, one workgroup per window of kWindow columns: each row's entries
-// of the window by binary search, each block column one bit (with fill counts:
-// one 16-bit counter).  Rows are sorted by now unless the matrix is bad, in
-// which case every index is still checked.  big_blocks[t]: blocks of strip t.
+// Long strips, one workgroup of 1,024 threads per window of kWindow columns: each
+// row's entries of the window by binary search, each block column one bit (with
+// fill counts: one 16-bit counter).  big_blocks[t]: blocks of strip t.
+//
+// The windows take every entry of a row exactly once whether the row is sorted
+// or not, so the checks at b = 16 see every entry: the search for a smaller
+// column never ends further right (its test col[mid] < v holds for every larger
+// v too), one window's end is the next one's start by the same search, and the
+// first and last windows are widened to the row's ends.
 template <int LB, bool ALL>
-__global__ __launch_bounds__(256) void k_an_strips_big(const int32_t *__restrict__ rowptr,
+__global__ __launch_bounds__(1024) void k_an_strips_big(const int32_t *__restrict__ rowptr,
                                                        const int32_t *__restrict__ colidx, int32_t m, int32_t k,
                                                        int32_t dense_threshold, const int32_t *__restrict__ big,
                                                        int32_t *__restrict__ big_blocks, DevAgg *__restrict__ agg) {
@@ -437,8 +441,8 @@ __global__ __launch_bounds__(256) void k_an_strips_big(const int32_t *__restrict
   constexpr int kBlocks = kWindow >> LB;
   constexpr int kWords = kFill ? kBlocks / 2 : kBlocks / 32;
   __shared__ uint32_t words[kWords];
-  __shared__ int32_t lo[B], before[B + 1];
-  __shared__ u64 part[4];
+  __shared__ int32_t lo[2 * B], rs[B], before[B + 1];
+  __shared__ u64 part[16];
   __shared__ int32_t found;
   if (agg->bad_rows) return;
   StripSums sum;
@@ -446,32 +450,39 @@ __global__ __launch_bounds__(256) void k_an_strips_big(const int32_t *__restrict
   for (int64_t t = blockIdx.x; t < n; t += gridDim.x) {
     const int64_t s = big[t / nw], base = t % nw * kWindow;
     __syncthreads();
-    if (threadIdx.x < B) {
-      const int64_t r = s * B + threadIdx.x;
-      int32_t a = 0, b = 0;
-      if (r < m) {
-        a = lower_bound_dev(colidx, rowptr[r], rowptr[r + 1], base);
-        b = lower_bound_dev(colidx, a, rowptr[r + 1], base + kWindow);
+    if (threadIdx.x < 2 * B) {  // the window's first entry in each row, and the next window's
+      const int r = threadIdx.x % B, side = threadIdx.x / B;
+      const int64_t i = s * B + r;
+      int32_t a = 0;
+      if (i < m) {
+        const int32_t p0 = rowptr[i], p1 = rowptr[i + 1];
+        if (side == 0) rs[r] = p0;
+        a = side == 0 && base == 0            ? p0
+            : side == 1 && base + kWindow >= k ? p1
+                                               : lower_bound_dev(colidx, p0, p1, base + side * kWindow);
       }
       lo[threadIdx.x] = a;
-      before[threadIdx.x + 1] = b - a;
     }
+    if (threadIdx.x == 0) found = 0;
+    for (int i = threadIdx.x; i < kWords; i += 1024) words[i] = 0;
+    __syncthreads();
     if (threadIdx.x == 0) {
       before[0] = 0;
-      found = 0;
+      for (int i = 0; i < B; ++i) before[i + 1] = before[i] + lo[B + i] - lo[i];
     }
-    for (int i = threadIdx.x; i < kWords; i += 256) words[i] = 0;
-    __syncthreads();
-    if (threadIdx.x == 0)
-      for (int i = 1; i <= B; ++i) before[i] += before[i - 1];
     __syncthreads();
     const int32_t total = before[B];
     if (total == 0) continue;  // workgroup-uniform
-    for (int32_t i = threadIdx.x; i < total; i += 256) {
+    for (int32_t i = threadIdx.x; i < total; i += 1024) {
       int r = 0;
 #pragma unroll
       for (int st = B / 2; st >= 1; st >>= 1) r += before[r + st] <= i ? st : 0;
-      const int64_t d = (int64_t)colidx[lo[r] + (i - before[r])] - base;
+      const int32_t p = lo[r] + (i - before[r]), c = colidx[p];
+      if constexpr (LB == 4) {
+        sum.bad |= entry_bad(p, rs[r], c, p > rs[r] ? colidx[p - 1] : 0, k);
+        sum.diag += c == s * B + r;
+      }
+      const int64_t d = (int64_t)c - base;
       if (d < 0 || d >= kWindow) continue;  // an unsorted row
       const uint32_t blk = (uint32_t)d >> LB;
       if constexpr (kFill) atomicAdd(&words[blk >> 1], 1u << (16 * (blk & 1)));
@@ -479,7 +490,7 @@ __global__ __launch_bounds__(256) void k_an_strips_big(const int32_t *__restrict
     }
     __syncthreads();
     int32_t here = 0;
-    for (int i = threadIdx.x; i < kWords; i += 256) {
+    for (int i = threadIdx.x; i < kWords; i += 1024) {
       const uint32_t w = words[i];
       if constexpr (kFill) {
         here += ((w & 0xffffu) != 0) + ((w >> 16) != 0);
@@ -623,8 +634,8 @@ hipError_t launch_strips(const sd_csr_t *A, int32_t dense_threshold, int32_t *mi
   }
   if (A->nnz > kMid) {
     const int64_t nw = ((int64_t)A->k + kWindow - 1) / kWindow;
-    const uint32_t gb = (uint32_t)std::min<int64_t>((A->nnz / kMid + 1) * nw, 2048);
-    hipLaunchKernelGGL((k_an_strips_big<LB, ALL>), dim3(gb), dim3(256), 0, s, A->rowptr, A->colidx, A->m, A->k,
+    const uint32_t gb = (uint32_t)std::min<int64_t>((A->nnz / kMid + 1) * nw, 1024);
+    hipLaunchKernelGGL((k_an_strips_big<LB, ALL>), dim3(gb), dim3(1024), 0, s, A->rowptr, A->colidx, A->m, A->k,
                        dense_threshold, big, big_blocks, agg);
   }
   return hipGetLastError();
