@@ -54,8 +54,8 @@ hipError_t launch_csr_merge(const CsrOperand &A, const int32_t *coords, int32_t 
                             float *part, const DenseIO &io, hipStream_t s);
 
 // Block formats: bptr == nullptr selects Blocked-ELL with `width` slots per
-// block-row.  engine: 1 MFMA (any width: 64-, 32- and 16-column tiles, the
-// last one partial; 16-column tiles of single floats without vec4), 2 VALU.
+// block-row.  engine: 1 MFMA (any width, in column tiles of one size, the last
+// one partial; 16-column tiles of single floats without vec4), 2 VALU.
 // zero_block: index of a block with column -1 and zero values that follows the
 // stored blocks (the MFMA kernel fetches it for slots past a block-row's end).
 // zrow: io.n zero floats (16-byte aligned), the MFMA kernel's B operand for
@@ -180,9 +180,9 @@ hipError_t dev_median_reach(const int32_t *rowptr, const int32_t *colidx, int32_
 
 // Kernel attributes of the main kernel a plan will launch (for the
 // resource-bound legality check).
-// width: ELL/WIN slots per row.
+// width: ELL/WIN slots per row; block_rows: BSR / Blocked-ELL.
 hipError_t kernel_attributes(int32_t family, int32_t engine, int32_t n, int32_t vec4, int32_t rows_per_group,
-                             int32_t unroll, int32_t slices, int32_t col_tile, int32_t width,
+                             int32_t unroll, int32_t slices, int32_t col_tile, int32_t width, int32_t block_rows,
                              hipFuncAttributes *attr);
 
 }  // namespace sd

@@ -1060,9 +1060,9 @@ __global__ __launch_bounds__(256) void k_win_split(
 // consecutive floats of a B row, and the outputs of the NT n-tiles at one
 // output row are NT consecutive floats of a C row.
 // Accumulates the blocks q = first .. first + cnt - 1 of one block-row into
-// acc (a 16 x 16 NT NQ tile of C at columns col0 ..).  RAG (NT = NQ = 1): the
-// tile may run past the width n; those lanes read column n - 1 of B (so every
-// address is in range), and their output columns are never stored.
+// acc (a 16 x 16 NT NQ tile of C at columns col0 ..).  RAG: the tile may run past
+// the width n (a multiple of NT); those lanes read the last NT columns of B (so
+// every address is in range), and their output columns are never stored.
 // zrow: n zero floats owned by the plan, read in place of a B row by every
 // slot that has no B row (a row past K, a Blocked-ELL padding block, the zero
 // block past a block-row's end), so a non-finite B row never meets the zero
@@ -1107,14 +1107,11 @@ __device__ __forceinline__ void bsr_mfma_blocks(int64_t first, int64_t cnt, int6
         // address.  A row past K (last block-column) or a Blocked-ELL padding
         // block reads the zero row instead; its A values are the zero fill,
         // so it adds exactly zero.  The column is always in range: the MFMA
-        // path needs n % (16 NT NQ) == 0 (RAG clamps to column n - 1).
+        // path needs n % (16 NT NQ) == 0 (RAG clamps to the last NT columns).
         const bool ok = valid && krow < k;
         const float *__restrict__ src = ok ? B + (int64_t)krow * n : zrow;
-        if constexpr (RAG) {
-          b[s][qq] = src[min(col0 + c, n - 1)];
-        } else {
-          b[s][qq] = *reinterpret_cast<const BV *>(src + col0 + qq * 16 * NT + NT * c);
-        }
+        const int32_t col = col0 + qq * 16 * NT + NT * c;
+        b[s][qq] = *reinterpret_cast<const BV *>(src + (RAG ? min(col, n - NT) : col));
       }
     }
   };
@@ -1149,24 +1146,25 @@ __device__ __forceinline__ void bsr_mfma_blocks(int64_t first, int64_t cnt, int6
   }
 }
 
-// One wave per (block-row, 16 NT NQ columns), the column tiles starting at
-// col_base.
+// One wave per (block-row, 16 NT NQ columns).  tx column tiles of a block-row are
+// consecutive waves (blockIdx.y takes the next tx), so a workgroup's waves share
+// a block-row's values in L1.
 template <int NQ, int NT, bool ELL, bool RAG = false>
 __global__ __launch_bounds__(256) void k_bsr_mfma(int32_t mb, int32_t m, int32_t k,
                                                   const int32_t *__restrict__ bptr, int32_t width,
                                                   const int32_t *__restrict__ bcol,
                                                   const float *__restrict__ bval,
                                                   const float *__restrict__ B, const float *__restrict__ zrow,
-                                                  float *__restrict__ C, int32_t n, int32_t col_base,
+                                                  float *__restrict__ C, int32_t n, int32_t tx,
                                                   int64_t zero_block, int order) {
-  static_assert(!RAG || (NQ == 1 && NT == 1), "ragged tiles are one n-tile wide");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 15, g = lane >> 4;
   const uint32_t blk = wg_index(order);
-  const int32_t br = (int32_t)blk * kWaves + wave;
-  if (br >= mb) return;
-  const int32_t col0 = col_base + blockIdx.y * (16 * NT * NQ);
+  const uint32_t unit = blk * kWaves + wave;
+  const int32_t br = (int32_t)(unit / (uint32_t)tx);
+  const int32_t col0 = (int32_t)(blockIdx.y * (uint32_t)tx + unit % (uint32_t)tx) * (16 * NT * NQ);
+  if (br >= mb || col0 >= n) return;  // wave-uniform
   int64_t q0, q1;
   if (ELL) {
     q0 = (int64_t)br * width;
@@ -1183,11 +1181,11 @@ __global__ __launch_bounds__(256) void k_bsr_mfma(int32_t mb, int32_t m, int32_t
   bsr_mfma_blocks<NQ, NT, RAG>(q0, q1 - q0, zero_block, bcol, bval, B, zrow, k, n, col0, c, g, acc);
 #pragma unroll
   for (int qq = 0; qq < NQ; ++qq) {
-    if (col0 + qq * 16 * NT >= n) continue;
+    const int32_t col = col0 + qq * 16 * NT + NT * c;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int32_t row = br * 16 + 4 * g + v;
-      if (row < m && (!RAG || col0 + c < n)) {
+      if (row < m && (!RAG || col < n)) {
         typename VecOf<NT>::T o;
         if constexpr (NT == 1) {
           o = acc[qq][0][v];
@@ -1196,7 +1194,7 @@ __global__ __launch_bounds__(256) void k_bsr_mfma(int32_t mb, int32_t m, int32_t
           for (int t = 0; t < NT; ++t) o[t] = acc[qq][t][v];
         }
         __builtin_nontemporal_store(o, reinterpret_cast<typename VecOf<NT>::T *>(
-                                           C + (int64_t)row * n + col0 + qq * 16 * NT + NT * c));
+                                           C + (int64_t)row * n + col));
       }
     }
   }
@@ -1536,43 +1534,53 @@ hipError_t launch_win_split(const CsrOperand &A, const int32_t *light, int32_t n
   });
 }
 
-// MFMA kernel for a column range: NT n-tiles of 16 columns per wave (NQ = 2:
-// two 64-column tiles), RAG for a last, partial tile.
-template <typename F>
-hipError_t with_mfma_shape(int NQ, int NT, bool rag, bool ell, F &&f) {
-  if (rag) return ell ? f(&k_bsr_mfma<1, 1, true, true>) : f(&k_bsr_mfma<1, 1, false, true>);
-  if (NQ == 2) return ell ? f(&k_bsr_mfma<2, 4, true>) : f(&k_bsr_mfma<2, 4, false>);
-  switch (NT) {
-    case 4: return ell ? f(&k_bsr_mfma<1, 4, true>) : f(&k_bsr_mfma<1, 4, false>);
-    case 2: return ell ? f(&k_bsr_mfma<1, 2, true>) : f(&k_bsr_mfma<1, 2, false>);
-    case 1: return ell ? f(&k_bsr_mfma<1, 1, true>) : f(&k_bsr_mfma<1, 1, false>);
-  }
-  return hipErrorInvalidValue;
-}
-
-// Column ranges of one MFMA SpMM, in launch order: [c0, c1) with its shape.
-// With 16-byte aligned B and C (vec4): 64-column tiles over the largest
-// multiple of 64, then one 32-column tile, then 16-column tiles with a
-// partial last one.  Otherwise 16-column tiles of single floats throughout.
-struct MfmaPart {
-  int32_t c0, c1, NQ, NT;
+// Column tiles of one MFMA SpMM: every wave takes NQ NT n-tiles of 16 columns,
+// the last tile partial (rag) where the width is no multiple of them.  One launch
+// for the whole width: cut into 64-, 32- and 16-column launches, each streamed
+// the block values again and left the chip idle at its end (24,011 rows, 21
+// blocks of 16 per block-row, N = 100: 58 us in three launches, 31 in one;
+// 131,072 rows, 32 blocks, N = 24, 48, 100: 144, 162, 307 us against 81, 109,
+// 210).  The lines of the rule, in us at (64-column tiles / the other shape):
+//   16 and 32 columns: as narrow as the width (131,072 rows, N = 16: 65 with 16,
+//     77 with 32; N = 32: 78 with 32, 107 with 64);
+//   32-column tiles while 64-column ones leave SIMDs without a wave (1,024 SIMDs;
+//     500 block-rows, N = 64: 11.2 / 9.6; N = 96, 1,000 waves: 11.9 / 12.8);
+//   128 columns per wave, which halves the value loads, where no half of it is
+//     wasted and two waves per SIMD remain (8,192 block-rows, N = 256: 498 / 469,
+//     N = 100: 234 / 210, N = 160 (three 64-column tiles): 323 / 398; 1,501
+//     block-rows, N = 256: 61.4 / 58.5, N = 128 (1,501 waves): 31.6 / 36.0).
+struct MfmaShape {
+  int32_t NQ, NT, tiles;
   bool rag;
 };
-int mfma_parts(int32_t n, int32_t vec4, MfmaPart (&out)[3]) {
-  int np = 0;
-  if (!vec4) {
-    out[np++] = {0, n, 1, 1, n % 16 != 0};
-    return np;
+MfmaShape mfma_shape(int32_t mb, int32_t n, int32_t vec4) {
+  MfmaShape s{1, 1, 0, false};
+  if (vec4) {
+    const int64_t t64 = (n + 63) / 64, waves64 = mb * t64, waves128 = mb * ((t64 + 1) / 2);
+    s.NT = n <= 16 ? 1 : n <= 32 || waves64 < 768 ? 2 : 4;
+    if (s.NT == 4 && t64 % 2 == 0 && waves128 >= 2048) s.NQ = 2;
   }
-  const int32_t n64 = n - n % 64;
-  if (n64 > 0) out[np++] = {0, n64, n64 % 128 == 0 ? 2 : 1, 4, false};
-  int32_t c = n64;
-  if (n - c >= 32) {
-    out[np++] = {c, c + 32, 1, 2, false};
-    c += 32;
+  const int32_t w = 16 * s.NT * s.NQ;
+  s.tiles = (n + w - 1) / w;
+  s.rag = n % w != 0;
+  return s;
+}
+
+template <typename F>
+hipError_t with_mfma_shape(const MfmaShape &sh, bool ell, F &&f) {
+  auto pick = [&](auto nq, auto nt) -> hipError_t {
+    constexpr int NQ = decltype(nq)::value, NT = decltype(nt)::value;
+    if (sh.rag) return ell ? f(&k_bsr_mfma<NQ, NT, true, true>) : f(&k_bsr_mfma<NQ, NT, false, true>);
+    return ell ? f(&k_bsr_mfma<NQ, NT, true, false>) : f(&k_bsr_mfma<NQ, NT, false, false>);
+  };
+  using std::integral_constant;
+  if (sh.NQ == 2) return pick(integral_constant<int, 2>{}, integral_constant<int, 4>{});
+  switch (sh.NT) {
+    case 4: return pick(integral_constant<int, 1>{}, integral_constant<int, 4>{});
+    case 2: return pick(integral_constant<int, 1>{}, integral_constant<int, 2>{});
+    case 1: return pick(integral_constant<int, 1>{}, integral_constant<int, 1>{});
   }
-  if (n - c > 0) out[np++] = {c, n, 1, 1, (n - c) % 16 != 0};
-  return np;
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_bsr(int32_t mb, int32_t m, int32_t k, const int32_t *bptr, int32_t width, const int32_t *bcol,
@@ -1582,20 +1590,15 @@ hipError_t launch_bsr(int32_t mb, int32_t m, int32_t k, const int32_t *bptr, int
   if (nb == 0) return hipSuccess;
   const bool ell = bptr == nullptr;
   if (engine == 1) {
-    MfmaPart parts[3];
-    const int np = mfma_parts(io.n, io.vec4, parts);
-    for (int i = 0; i < np; ++i) {
-      const MfmaPart &pt = parts[i];
-      const int32_t tile = 16 * pt.NT * pt.NQ;
-      const uint32_t ny = (uint32_t)((pt.c1 - pt.c0 + tile - 1) / tile);
-      hipError_t e = with_mfma_shape(pt.NQ, pt.NT, pt.rag, ell, [&](auto kern) -> hipError_t {
-        hipLaunchKernelGGL(kern, dim3(nb, ny), dim3(256), 0, s, mb, m, k, bptr, width, bcol, bval, io.B, zrow, io.C,
-                           io.n, pt.c0, zero_block, io.order);
-        return hipGetLastError();
-      });
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    const MfmaShape sh = mfma_shape(mb, io.n, io.vec4);
+    int32_t ny = (sh.tiles + kWaves - 1) / kWaves, tx = (sh.tiles + ny - 1) / ny;
+    if ((int64_t)mb * tx * 64 > UINT32_MAX - 255) tx = 1, ny = sh.tiles;  // threads of a grid dimension
+    const uint32_t grid = (uint32_t)(((int64_t)mb * tx + kWaves - 1) / kWaves);
+    return with_mfma_shape(sh, ell, [&](auto kern) -> hipError_t {
+      hipLaunchKernelGGL(kern, dim3(grid, (uint32_t)ny), dim3(256), 0, s, mb, m, k, bptr, width, bcol, bval, io.B,
+                         zrow, io.C, io.n, tx, zero_block, io.order);
+      return hipGetLastError();
+    });
   }
   const Geometry geo = geometry_for(io.n, io.vec4, io.col_tile);
   return with_geometry(geo, [&](auto gg) -> hipError_t {
@@ -1611,7 +1614,7 @@ hipError_t launch_bsr(int32_t mb, int32_t m, int32_t k, const int32_t *bptr, int
 }
 
 hipError_t kernel_attributes(int32_t family, int32_t engine, int32_t n, int32_t vec4, int32_t rows_per_group,
-                             int32_t unroll, int32_t slices, int32_t col_tile, int32_t width,
+                             int32_t unroll, int32_t slices, int32_t col_tile, int32_t width, int32_t block_rows,
                              hipFuncAttributes *attr) {
   const int32_t G0 = geometry_for(n, vec4, col_tile).G;
   if ((family == 1 && fit_slices(slices, G0) > 1) || (family == 2 && G0 <= 8)) {
@@ -1637,12 +1640,9 @@ hipError_t kernel_attributes(int32_t family, int32_t engine, int32_t n, int32_t 
   }
   if (family == 4 || family == 5) {
     const bool ell = family == 5;
-    if (engine == 1) {  // the first (widest) part's kernel
-      MfmaPart parts[3];
-      if (mfma_parts(n, vec4, parts) == 0) return hipErrorInvalidValue;
-      return with_mfma_shape(parts[0].NQ, parts[0].NT, parts[0].rag, ell,
+    if (engine == 1)
+      return with_mfma_shape(mfma_shape(block_rows, n, vec4), ell,
                              [&](auto kern) -> hipError_t { return hipFuncGetAttributes(attr, (const void *)kern); });
-    }
     return with_geometry(geometry_for(n, vec4, col_tile), [&](auto gg) -> hipError_t {
       constexpr int G = decltype(gg)::G, VW = decltype(gg)::VW;
       const void *fn = ell ? (const void *)&k_bsr_valu<G, VW, true> : (const void *)&k_bsr_valu<G, VW, false>;

@@ -522,7 +522,7 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
   std::memset(&attr, 0, sizeof(attr));
   hipError_t e =
       sd::kernel_attributes(I.family, I.engine, n, vec4, I.rows_per_group, I.gather_unroll, I.row_slices, col_tile,
-                            (int32_t)I.ell_width, &attr);
+                            (int32_t)I.ell_width, (int32_t)I.block_rows, &attr);
   if (e != hipSuccess) return hip_fail(e);
   I.regs_per_thread = attr.numRegs;
   I.lds_bytes = (int32_t)attr.sharedSizeBytes;

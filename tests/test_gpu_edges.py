@@ -200,3 +200,19 @@ def test_transform_routes():
     assert torch.allclose(tang, X.detach() @ torch.ones_like(W), rtol=1e-5, atol=1e-4)
     many = torch.func.vmap(lambda w: gcn.transform(X.detach(), w))(torch.stack([W.detach(), 2 * W.detach()]))
     assert many.shape == (2, gcn._GRAD_ROWS, 12)
+
+
+@pytest.mark.parametrize("fam", ["bsr", "bell"])
+@pytest.mark.parametrize("mb", [3, 767, 768, 1100, 2050])
+@pytest.mark.parametrize("n", [4, 20, 36, 64, 68, 100, 128, 132, 200, 260])
+def test_mfma_column_tiles(fam, mb, n):
+    """Every column-tile shape of the MFMA block kernel with a whole and a partial
+    last tile: 16, 32 and 64 columns, and 128 from 2,048 waves on, workgroups
+    whose waves share a block-row and ones that end inside it."""
+    A = gen.block(mb, 40, 16, 2, 30, 0.9, mb)
+    A = gen.CSR(A.m - 5, A.k, A.rowptr[:A.m - 4], A.colidx[:A.rowptr[A.m - 5]], A.values[:A.rowptr[A.m - 5]])
+    B = gen.dense_uniform(A.k, n, seed=n)
+    C64, S = oracle.spmm(A, B)
+    print(f"case mfma tiles {fam} mb={mb} n={n}", flush=True)
+    with sd.sd_plan_ex(A, n, force=fam, engine="mfma") as plan:
+        assert_close(run(sd, plan, B, A.m), C64, S, f"tiles/{fam}/{mb}/{n}")
