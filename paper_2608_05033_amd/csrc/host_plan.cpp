@@ -399,6 +399,35 @@ void row_batch_for(const sd_stats_t &st, int64_t rows, int32_t G, int32_t cu_cou
   *unr = u;
 }
 
+// The lines, measured with B streamed from HBM and MALL (us, one row per lane
+// group at a time round-robin / streamed):
+//  * CSR_ROW, rows of 24 around a band, 300,000 rows.  The rows in flight on an
+//    XCD and the band around them have to fit its L2 (4 MiB): N = 64 and a window
+//    of 0.4, 2.4, 9.5 MB: 154 / 125, 158 / 132, 180 / 188; N = 96 and 7.3 MB: 243 /
+//    213.  A window wider than the rows of one XCD makes the XCDs fetch each
+//    other's rows: 120,000 rows, window 40,000, N = 40 (6 MB): 127 / 149.
+//    4 rows per group keep more rows in flight than 2 and balance better, while
+//    the window is small (7.3 MB: 213 with 2, 221 with 4) and workgroups many
+//    (120,000 rows of 55, N = 40: 119 with 2, 125 with 4).
+//    Few workgroups: 20,000 rows, N = 40: 22 / 27; 60,000: 48 / 45.
+//  * Short rows under wide lane groups leave a wave two or one of them, so they
+//    gain from streaming whatever they gather: 500,000 rows of 6 on random columns,
+//    N = 96: 233 / 205, N = 256: 521 / 457 (N = 64: 133 / 144).
+//  * Light rows of the split: R-MAT 2^20, N = 128: 931 / 895, N = 100: 994 / 954;
+//    2^18, N = 64: 119 / 126, where the last workgroups are too large a share.
+int32_t stream_for(int32_t family, int64_t rows, double row_mean, int32_t G, int64_t window_rows, int64_t row_bytes) {
+  if (G < 8) return 0;
+  const int64_t groups = kBlockThreads / G;
+  auto workgroups = [&](int64_t R) { return rows / (R * groups); };
+  if (family == SD_FMT_CSR_SPLIT) return workgroups(4) >= 16000 ? 4 : 0;
+  const int64_t window = window_rows * row_bytes;
+  if (8 * window_rows <= rows && window <= (15ll << 19)) {  // 7.5 MiB
+    if (workgroups(4) >= 4096 && window <= (4ll << 20)) return 4;
+    if (workgroups(2) >= 1500) return 2;
+  }
+  return G >= 32 && row_mean <= 8.0 && workgroups(4) >= 4096 ? 4 : 0;
+}
+
 int32_t slices_for(const sd_stats_t &st, int32_t family, int32_t n, int32_t G) {
   (void)n;
   if ((family != SD_FMT_CSR_ROW && family != SD_FMT_CSR_SPLIT) || G > 8) return 1;

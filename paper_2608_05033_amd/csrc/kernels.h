@@ -38,15 +38,16 @@ struct Geometry {
 Geometry geometry_for(int32_t n, int32_t vec4, int32_t col_tile = 0);
 
 // slices > 1 (G <= 8 only): S = slices lane groups share each row, each taking
-// every S-th nonzero (rows_per_group and unroll are then unused).
+// every S-th nonzero (rows_per_group and unroll are then unused).  Else stream > 0:
+// a workgroup's lane groups share stream rows each, taken as they become free.
 hipError_t launch_csr_rows(const CsrOperand &A, const DenseIO &io, int32_t rows_per_group, int32_t unroll,
-                           int32_t slices, hipStream_t s);
+                           int32_t slices, int32_t stream, hipStream_t s);
 
 // corder: the chunk processing order, a permutation of [0, nchunks).
 hipError_t launch_csr_split(const CsrOperand &A, const int32_t *light, int32_t nlight, const int32_t *chunks,
                             const int32_t *corder, int32_t nchunks, const int32_t *heavy_rows,
                             const int32_t *heavy_ptr, int32_t nheavy, float *ws, const DenseIO &io,
-                            int32_t rows_per_group, int32_t unroll, int32_t slices, hipStream_t s);
+                            int32_t rows_per_group, int32_t unroll, int32_t slices, int32_t stream, hipStream_t s);
 
 // Merge path over `units` pieces.  rows: 2 units int32 (carry rows, then head
 // rows); part: 2 units n floats (carry partials, then head partials).
@@ -182,7 +183,7 @@ hipError_t dev_median_reach(const int32_t *rowptr, const int32_t *colidx, int32_
 // resource-bound legality check).
 // width: ELL/WIN slots per row; block_rows: BSR / Blocked-ELL.
 hipError_t kernel_attributes(int32_t family, int32_t engine, int32_t n, int32_t vec4, int32_t rows_per_group,
-                             int32_t unroll, int32_t slices, int32_t col_tile, int32_t width, int32_t block_rows,
-                             hipFuncAttributes *attr);
+                             int32_t unroll, int32_t slices, int32_t stream, int32_t col_tile, int32_t width,
+                             int32_t block_rows, hipFuncAttributes *attr);
 
 }  // namespace sd

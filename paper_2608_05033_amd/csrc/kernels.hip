@@ -291,20 +291,118 @@ __device__ __forceinline__ void rows_wave(int64_t w0, const int32_t *__restrict_
   }
 }
 
+// A workgroup's rows [first, first + rows) of the row space (or of the list
+// positions), rows <= kStreamRows, taken in order by its lane groups as they
+// become free (a counter in LDS).  A group takes one batch of up to 8 gathers per
+// turn of whatever row it is at, and the next tile of entries - of the same row or
+// of the row it takes next - is loaded before the current tile's gathers: a row
+// start costs no memory round trip, no group waits for the longest row of its
+// wave, and the rows in flight stay adjacent (which is what L2 lives on).
+constexpr int kStreamRows = 256;
+struct StreamLds {
+  int32_t bounds[kStreamRows + 1], ids[kStreamRows];
+  int32_t next;
+};
+
+template <int G, int VW, bool LIST>
+__device__ __forceinline__ void rows_stream(StreamLds &lds, int64_t first, int rows,
+                                            const int32_t *__restrict__ rowptr,
+                                            const int32_t *__restrict__ colidx, const float *__restrict__ vals,
+                                            const int32_t *__restrict__ rowlist, const float *__restrict__ B,
+                                            float *__restrict__ C, int32_t n, int32_t col) {
+  using V = typename VecOf<VW>::T;
+  constexpr int UNR = G < 8 ? G : 8;
+  constexpr int GROUPS = 256 / G;
+  const int lane = threadIdx.x & 63;
+  const int glane = lane & (G - 1), gbase = lane & ~(G - 1);
+  const bool col_ok = col < n;
+  const float *__restrict__ Bl = B + col;
+  for (int t = threadIdx.x; t <= rows; t += 256) {
+    lds.bounds[t] = rowptr[first + t];
+    if (LIST && t < rows) lds.ids[t] = rowlist[first + t];
+  }
+  if (threadIdx.x == 0) lds.next = GROUPS;
+  __syncthreads();
+  int r = threadIdx.x / G, nr = rows;  // this row and the next one taken
+  if (r >= rows) return;
+  int32_t p = lds.bounds[r], e = lds.bounds[r + 1];
+  int32_t c, nc = 0, np = 0, ne = 0, off = 0, cnt = min(G, e - p);
+  float v, nv = 0.0f;
+  load_tile<G>(colidx, vals, p, e, glane, c, v);
+  V acc = (V)(0.0f);
+  while (r < rows) {
+    if (off == 0) {  // a new tile: request the one after it
+      if (e - p > G) {
+        np = p + G;
+        ne = e;
+      } else {
+        if (glane == 0) nr = atomicAdd(&lds.next, 1);
+        nr = __shfl(nr, gbase, 64);
+        np = ne = 0;
+        if (nr < rows) {
+          np = lds.bounds[nr];
+          ne = lds.bounds[nr + 1];
+        }
+      }
+      load_tile<G>(colidx, vals, np, ne, glane, nc, nv);
+    }
+    V bv[UNR];
+    float av[UNR];
+    int32_t ct[UNR];
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+      ct[u] = __shfl(c, gbase + off + u, 64);
+      av[u] = __shfl(v, gbase + off + u, 64);
+    }
+    __builtin_amdgcn_sched_barrier(0);  // broadcasts first, then the gathers back to back
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+      bv[u] = (V)(0.0f);
+      if (off + u < cnt && col_ok) bv[u] = load_v<VW>(Bl + (int64_t)ct[u] * n);
+    }
+#pragma unroll
+    for (int u = 0; u < UNR; ++u)
+      if (off + u < cnt) acc += av[u] * bv[u];
+    off += UNR;
+    if (off >= cnt) {
+      if (e - p <= G) {  // the row's last tile
+        const int64_t row = LIST ? (int64_t)lds.ids[r] : first + r;
+        if (col_ok) store_nt<VW>(C + row * n + col, acc);
+        acc = (V)(0.0f);
+        r = nr;
+      }
+      c = nc;
+      v = nv;
+      p = np;
+      e = ne;
+      cnt = min(G, e - p);
+      off = 0;
+    }
+  }
+}
+
 // --------------------------------------------------------------- CSR rows ---
+// J >= 1: J rows per lane group, batched (rows_wave).  J = 0: R rows per
+// workgroup, streamed (rows_stream).
 template <int G, int VW, int J, int UNR, bool LIST>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(J == 1 ? 6 : 1))) void k_csr_rows(const int32_t *__restrict__ rowptr,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(J <= 1 ? 6 : 1))) void k_csr_rows(const int32_t *__restrict__ rowptr,
                                                   const int32_t *__restrict__ colidx,
                                                   const float *__restrict__ vals,
                                                   const int32_t *__restrict__ rowlist, int32_t nrows,
                                                   const float *__restrict__ B, float *__restrict__ C, int32_t n,
-                                                  int order) {
-  constexpr int WR = (64 / G) * J;
+                                                  int order, int R) {
   const int wave = threadIdx.x >> 6;
   const uint32_t blk = wg_index(order);
-  const int64_t w0 = ((int64_t)blk * kWaves + wave) * WR;
   const int32_t col = blockIdx.y * (G * VW) + (threadIdx.x & (G - 1)) * VW;
-  rows_wave<G, VW, J, UNR, LIST>(w0, rowptr, colidx, vals, rowlist, nrows, B, C, n, col);
+  if constexpr (J == 0) {
+    __shared__ StreamLds lds;
+    const int64_t first = (int64_t)blk * R;
+    rows_stream<G, VW, LIST>(lds, first, (int)min((int64_t)R, nrows - first), rowptr, colidx, vals, rowlist, B, C, n,
+                             col);
+  } else {
+    const int64_t w0 = ((int64_t)blk * kWaves + wave) * ((64 / G) * J);
+    rows_wave<G, VW, J, UNR, LIST>(w0, rowptr, colidx, vals, rowlist, nrows, B, C, n, col);
+  }
 }
 
 // ------------------------------------------------------- heavy-row split ---
@@ -312,7 +410,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(J == 1 ? 6 
 // corder gives, and write their partial sums to ws[chunk][*]; the rest take
 // the light rows.
 template <int G, int VW, int J, int UNR>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(J == 1 ? 6 : 1))) void k_csr_split(const int32_t *__restrict__ rowptr,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(J <= 1 ? 6 : 1))) void k_csr_split(const int32_t *__restrict__ rowptr,
                                                    const int32_t *__restrict__ colidx,
                                                    const float *__restrict__ vals,
                                                    const int32_t *__restrict__ light, int32_t nlight,
@@ -320,7 +418,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(J == 1 ? 6 
                                                    const int32_t *__restrict__ corder,
                                                    uint32_t chunk_blocks, float *__restrict__ ws,
                                                    const float *__restrict__ B, float *__restrict__ C, int32_t n,
-                                                   int order) {
+                                                   int order, int R) {
   using V = typename VecOf<VW>::T;
   constexpr int RPW = 64 / G;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -350,8 +448,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(J == 1 ? 6 
     gather_rows<G, VW>(colidx, vals, p0, p1, c0, v0, B + col, n, col_ok, acc, glane, gbase);
     if (q < nchunks && col_ok) store_v<VW>(ws + q * n + col, acc);
   } else {
-    const int64_t w0 = ((int64_t)(blk - chunk_blocks) * kWaves + wave) * (RPW * J);
-    rows_wave<G, VW, J, UNR, true>(w0, rowptr, colidx, vals, light, nlight, B, C, n, col);
+    const int64_t lb = (int64_t)(blk - chunk_blocks);
+    if constexpr (J == 0) {
+      __shared__ StreamLds lds;
+      rows_stream<G, VW, true>(lds, lb * R, (int)min((int64_t)R, nlight - lb * R), rowptr, colidx, vals, light, B, C, n,
+                               col);
+    } else {
+      rows_wave<G, VW, J, UNR, true>((lb * kWaves + wave) * (RPW * J), rowptr, colidx, vals, light, nlight, B, C, n,
+                                     col);
+    }
   }
 }
 
@@ -1298,9 +1403,13 @@ inline uint32_t blocks_for(int64_t units, int G, int J = 1) {
 
 // Rows per lane group J in {1, 2, 4} and B-row gathers per row per round
 // UNR in {4, 8} (at most G); J * UNR <= 16 keeps the in-flight B data within
-// 64 VGPRs at VW = 4.
+// 64 VGPRs at VW = 4.  J = 0: the streaming kernels (G >= 8; wider lane groups
+// than planned, for a misaligned B or C, stream as well).
 template <int G, typename F>
 hipError_t with_row_batch(int J, int UNR, F &&f) {
+  if constexpr (G >= 8) {
+    if (J == 0) return f(std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{});
+  }
   constexpr int U8 = G < 8 ? G : 8;
   constexpr int U4 = G < 4 ? G : 4;
   if constexpr (G >= 4) {
@@ -1384,7 +1493,7 @@ Geometry geometry_for(int32_t n, int32_t vec4, int32_t col_tile) {
 }
 
 hipError_t launch_csr_rows(const CsrOperand &A, const DenseIO &io, int32_t rows_per_group, int32_t unroll,
-                           int32_t slices, hipStream_t s) {
+                           int32_t slices, int32_t stream, hipStream_t s) {
   const Geometry geo = geometry_for(io.n, io.vec4, io.col_tile);
   return with_geometry(geo, [&](auto gg) -> hipError_t {
     constexpr int G = decltype(gg)::G, VW = decltype(gg)::VW;
@@ -1398,12 +1507,13 @@ hipError_t launch_csr_rows(const CsrOperand &A, const DenseIO &io, int32_t rows_
         return hipGetLastError();
       });
     }
-    return with_row_batch<G>(rows_per_group, unroll, [&](auto jj, auto uu) -> hipError_t {
+    return with_row_batch<G>(stream > 0 ? 0 : rows_per_group, unroll, [&](auto jj, auto uu) -> hipError_t {
       constexpr int J = decltype(jj)::value, UNR = decltype(uu)::value;
-      const uint32_t nb = blocks_for(A.m, G, J);
+      const int R = stream * (256 / G);
+      const uint32_t nb = J == 0 ? (uint32_t)(((int64_t)A.m + R - 1) / R) : blocks_for(A.m, G, J);
       if (nb == 0) return hipSuccess;
       hipLaunchKernelGGL((k_csr_rows<G, VW, J, UNR, false>), dim3(nb, geo.coltiles), dim3(256), 0, s, A.rowptr,
-                         A.colidx, A.vals, nullptr, A.m, io.B, io.C, io.n, io.order);
+                         A.colidx, A.vals, nullptr, A.m, io.B, io.C, io.n, io.order, R);
       return hipGetLastError();
     });
   });
@@ -1412,7 +1522,7 @@ hipError_t launch_csr_rows(const CsrOperand &A, const DenseIO &io, int32_t rows_
 hipError_t launch_csr_split(const CsrOperand &A, const int32_t *light, int32_t nlight, const int32_t *chunks,
                             const int32_t *corder, int32_t nchunks, const int32_t *heavy_rows,
                             const int32_t *heavy_ptr, int32_t nheavy, float *ws, const DenseIO &io,
-                            int32_t rows_per_group, int32_t unroll, int32_t slices, hipStream_t s) {
+                            int32_t rows_per_group, int32_t unroll, int32_t slices, int32_t stream, hipStream_t s) {
   const Geometry geo = geometry_for(io.n, io.vec4, io.col_tile);
   return with_geometry(geo, [&](auto gg) -> hipError_t {
     constexpr int G = decltype(gg)::G, VW = decltype(gg)::VW;
@@ -1427,14 +1537,16 @@ hipError_t launch_csr_split(const CsrOperand &A, const int32_t *light, int32_t n
                          A.rowptr, A.colidx, A.vals, light, nlight, chunks, nchunks, corder, cb, ws, io.B, io.C,
                          io.n, io.order == 1 ? 1 : 0);
       return hipGetLastError();
-    }) : with_row_batch<G>(rows_per_group, unroll, [&](auto jj, auto uu) -> hipError_t {
+    }) : with_row_batch<G>(stream > 0 ? 0 : rows_per_group, unroll, [&](auto jj, auto uu) -> hipError_t {
       constexpr int J = decltype(jj)::value, UNR = decltype(uu)::value;
-      const uint32_t cb = blocks_for(nchunks, G), lb = blocks_for(nlight, G, J);
+      const int R = stream * (256 / G);
+      const uint32_t cb = blocks_for(nchunks, G);
+      const uint32_t lb = J == 0 ? (uint32_t)(((int64_t)nlight + R - 1) / R) : blocks_for(nlight, G, J);
       if (cb + lb == 0) return hipSuccess;
       const uint32_t grid = (io.order == 1 ? (cb + 7u) & ~7u : cb) + lb;
       hipLaunchKernelGGL((k_csr_split<G, VW, J, UNR>), dim3(grid, geo.coltiles), dim3(256), 0, s, A.rowptr,
                          A.colidx, A.vals, light, nlight, chunks, nchunks, corder, cb, ws, io.B, io.C, io.n,
-                         io.order == 1 ? 1 : 0);
+                         io.order == 1 ? 1 : 0, R);
       return hipGetLastError();
     });
     if (e != hipSuccess) return e;
@@ -1614,8 +1726,8 @@ hipError_t launch_bsr(int32_t mb, int32_t m, int32_t k, const int32_t *bptr, int
 }
 
 hipError_t kernel_attributes(int32_t family, int32_t engine, int32_t n, int32_t vec4, int32_t rows_per_group,
-                             int32_t unroll, int32_t slices, int32_t col_tile, int32_t width, int32_t block_rows,
-                             hipFuncAttributes *attr) {
+                             int32_t unroll, int32_t slices, int32_t stream, int32_t col_tile, int32_t width,
+                             int32_t block_rows, hipFuncAttributes *attr) {
   const int32_t G0 = geometry_for(n, vec4, col_tile).G;
   if ((family == 1 && fit_slices(slices, G0) > 1) || (family == 2 && G0 <= 8)) {
     return with_geometry(geometry_for(n, vec4, col_tile), [&](auto gg) -> hipError_t {
@@ -1651,7 +1763,7 @@ hipError_t kernel_attributes(int32_t family, int32_t engine, int32_t n, int32_t 
   }
   return with_geometry(geometry_for(n, vec4, col_tile), [&](auto gg) -> hipError_t {
     constexpr int G = decltype(gg)::G, VW = decltype(gg)::VW;
-    return with_row_batch<G>(rows_per_group, unroll, [&](auto jj, auto uu) -> hipError_t {
+    return with_row_batch<G>(stream > 0 ? 0 : rows_per_group, unroll, [&](auto jj, auto uu) -> hipError_t {
       constexpr int J = decltype(jj)::value, UNR = decltype(uu)::value;
       const void *fn = family == 2   ? (const void *)&k_csr_split<G, VW, J, UNR>
                        : family == 3 ? (const void *)&k_csr_merge<G, VW>

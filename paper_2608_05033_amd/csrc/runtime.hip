@@ -490,6 +490,18 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
       I.wg_chunk = S;
     }
   }
+  // One row per lane group with 8 gathers by default: streamed where that pays,
+  // CSR_ROW then with one contiguous range of rows per XCD.
+  if ((I.family == SD_FMT_CSR_ROW || I.family == SD_FMT_CSR_SPLIT) && o.rows_per_group == 0 && I.rows_per_group == 1 &&
+      o.gather_unroll == 0 && I.gather_unroll == 8 && I.row_slices == 1) {
+    if (I.family == SD_FMT_CSR_SPLIT) {
+      p->stream = sd::stream_for(I.family, I.n_light, 0.0, geo.G, 0, 0);
+    } else if (o.wg_order == 0 && I.wg_order != 3) {
+      p->stream = sd::stream_for(I.family, A.m, stats.row_mean, geo.G, 2 * I.reach,
+                                 4 * std::min<int64_t>(n, (int64_t)geo.G * geo.VW));
+      if (p->stream > 0) I.wg_order = 1;
+    }
+  }
 
 
   // ---- workload-scale analysis
@@ -521,7 +533,8 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
   hipFuncAttributes attr;
   std::memset(&attr, 0, sizeof(attr));
   hipError_t e =
-      sd::kernel_attributes(I.family, I.engine, n, vec4, I.rows_per_group, I.gather_unroll, I.row_slices, col_tile,
+      sd::kernel_attributes(I.family, I.engine, n, vec4, I.rows_per_group, I.gather_unroll, I.row_slices, p->stream,
+                            col_tile,
                             (int32_t)I.ell_width, (int32_t)I.block_rows, &attr);
   if (e != hipSuccess) return hip_fail(e);
   I.regs_per_thread = attr.numRegs;
@@ -875,13 +888,13 @@ int sd_spmm(sd_plan_t p, const float *B, float *C, void *stream) {
   hipError_t e = hipSuccess;
   switch (I.family) {
     case SD_FMT_CSR_ROW:
-      e = sd::launch_csr_rows(A, io, I.rows_per_group, I.gather_unroll, I.row_slices, s);
+      e = sd::launch_csr_rows(A, io, I.rows_per_group, I.gather_unroll, I.row_slices, p->stream, s);
       break;
     case SD_FMT_CSR_SPLIT:
       e = sd::launch_csr_split(A, p->d_light, (int32_t)I.n_light, p->d_chunks, p->d_corder, (int32_t)I.n_chunks,
                                p->d_heavy_rows,
                                p->d_heavy_ptr, (int32_t)I.n_heavy, p->d_ws, io, I.rows_per_group,
-                               I.gather_unroll, I.row_slices, s);
+                               I.gather_unroll, I.row_slices, p->stream, s);
       break;
     case SD_FMT_CSR_MERGE:
       e = sd::launch_csr_merge(A, p->d_coords, (int32_t)I.units, p->d_carry_row, p->d_ws, io, s);

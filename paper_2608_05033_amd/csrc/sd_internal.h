@@ -128,6 +128,10 @@ int64_t median_row_reach(const CsrView &A);
 // workgroups, so a row and its farthest typical neighbour run on the same XCD;
 // 0 if there is none (keep the plain round-robin).
 int32_t chunk_for_reach(int64_t reach, int64_t rows_per_wg);
+// Rows streamed per lane group of G lanes by the row kernels (0: one row per lane
+// group at a time, batched by the wave).  window_rows: rows of B around a row
+// that it typically uses; row_bytes: bytes of one in a column pass (CSR_ROW only).
+int32_t stream_for(int32_t family, int64_t rows, double row_mean, int32_t G, int64_t window_rows, int64_t row_bytes);
 // Row batching for the row kernels: rows per lane group J in {1, 2, 4}
 // (J <= G) and B-row gathers per row per batch UNR in {4, 8}.
 void row_batch_for(const sd_stats_t &st, int64_t rows, int32_t G, int32_t cu_count, int32_t req_J,
@@ -159,6 +163,7 @@ struct sd_plan_s {
   sd_plan_info_t info{};
   int32_t device = -1;  // -1: host only
   int32_t col_tile_req = 0;  // requested dense columns per lane group (0: whole width)
+  int32_t stream = 0;  // CSR_ROW / light rows of CSR_SPLIT: rows streamed per lane group (0: batched by the wave)
 
   // host arrays
   std::vector<int32_t> h_rowptr, h_colidx, h_coltag, h_light, h_chunks, h_corder, h_heavy_rows, h_heavy_ptr, h_coords,

@@ -216,3 +216,39 @@ def test_mfma_column_tiles(fam, mb, n):
     print(f"case mfma tiles {fam} mb={mb} n={n}", flush=True)
     with sd.sd_plan_ex(A, n, force=fam, engine="mfma") as plan:
         assert_close(run(sd, plan, B, A.m), C64, S, f"tiles/{fam}/{mb}/{n}")
+
+
+@pytest.mark.parametrize("shape", ["band", "short", "empty"])
+@pytest.mark.parametrize("n", [33, 64, 96, 130, 256, 300])
+def test_streamed_rows(shape, n):
+    """Rows taken by lane groups as they become free: a narrow band (rows of
+    several tiles, empty rows, a last workgroup that is not full), short rows on
+    any columns, and nearly all rows empty; with 32-bit lanes as well."""
+    rng = np.random.default_rng(n)
+    m = 66003
+    if shape == "band":
+        lens = rng.integers(0, 30, m)
+        lens[::501] = 150
+        lens[1000:1400] = 0
+        lens[-1] = 70
+        base = np.clip(np.arange(m) - 200, 0, m - 400)
+    else:
+        lens = rng.integers(0, 6, m) if shape == "short" else (rng.random(m) < 0.01).astype(int)
+        base = np.zeros(m, np.int64)
+    width = 400 if shape == "band" else m
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rows = np.repeat(np.arange(m), lens)
+    j = np.arange(rowptr[-1]) - rowptr[rows]
+    L = lens[rows]
+    lo, hi = j * width // L, (j + 1) * width // L
+    col = (base[rows] + lo + rng.integers(0, 1 << 30, rows.size) % np.maximum(1, hi - lo)).astype(np.int32)
+    A = gen.CSR(m, m, rowptr, col, rng.uniform(-1, 1, col.size).astype(np.float32))
+    B = gen.dense_uniform(m, n, seed=n)
+    C64, S = oracle.spmm(A, B)
+    print(f"case streamed rows {shape} n={n}", flush=True)
+    with sd.sd_plan_ex(A, n, force="csr_row") as plan, sd.sd_plan_ex(A, n, force="csr_row", wg_order=2) as other:
+        out = run(sd, plan, B, m)
+        assert_close(out, C64, S, f"streamed {shape} n={n}")
+        # a row is summed in the same order either way
+        assert np.array_equal(out.view(np.uint32), run(sd, other, B, m).view(np.uint32))
+        assert_close(run(sd, plan, B, m, misalign=True), C64, S, f"streamed misaligned {shape} n={n}")
