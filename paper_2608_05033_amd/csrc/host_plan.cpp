@@ -410,12 +410,14 @@ void row_batch_for(const sd_stats_t &st, int64_t rows, int32_t G, int32_t cu_cou
 //    the window is small (7.3 MB: 213 with 2, 221 with 4) and workgroups many
 //    (120,000 rows of 55, N = 40: 119 with 2, 125 with 4).
 //    Few workgroups: 20,000 rows, N = 40: 22 / 27; 60,000: 48 / 45.
-//  * Short rows under wide lane groups leave a wave two or one of them, so they
-//    gain from streaming whatever they gather: 500,000 rows of 6 on random columns,
-//    N = 96: 233 / 205, N = 256: 521 / 457 (N = 64: 133 / 144).
+//  * Short rows under wide lane groups leave a wave two or one of them, and gain
+//    from streaming on any columns while B is small: 150,000 rows of 6 on random
+//    columns, N = 80, 96, 192: 63.5 / 60.5, 65.9 / 62.2, 110 / 106 (N = 128: 77 / 78;
+//    500,000 rows, N = 128, B of 244 MB: 234 / 253).
 //  * Light rows of the split: R-MAT 2^20, N = 128: 931 / 895, N = 100: 994 / 954;
 //    2^18, N = 64: 119 / 126, where the last workgroups are too large a share.
-int32_t stream_for(int32_t family, int64_t rows, double row_mean, int32_t G, int64_t window_rows, int64_t row_bytes) {
+int32_t stream_for(int32_t family, int64_t rows, double row_mean, int32_t G, int64_t window_rows, int64_t row_bytes,
+                   int64_t b_bytes) {
   if (G < 8) return 0;
   const int64_t groups = kBlockThreads / G;
   auto workgroups = [&](int64_t R) { return rows / (R * groups); };
@@ -425,7 +427,24 @@ int32_t stream_for(int32_t family, int64_t rows, double row_mean, int32_t G, int
     if (workgroups(4) >= 4096 && window <= (4ll << 20)) return 4;
     if (workgroups(2) >= 1500) return 2;
   }
-  return G >= 32 && row_mean <= 8.0 && workgroups(4) >= 4096 ? 4 : 0;
+  return G >= 32 && row_mean <= 8.0 && workgroups(4) >= 4096 && b_bytes <= kMallBytes / 2 ? 4 : 0;
+}
+
+// 64-column passes halve what the gathers of a pass spread over, but every pass
+// reads the entries again, reads 256-byte pieces of B's rows, and a last pass
+// narrower than 64 leaves lanes idle.  Measured (us, 64-column passes / wider):
+//  * 64 < N < 128, all at once: 7-point Laplacian 101^3, N = 96: 390 / 248; rows of
+//    6, 500,000 of them, N = 80: 225 / 187; R-MAT 2^20, N = 80 and 96: 821 / 694,
+//    794 / 716 (N = 128: 929 / 974);
+//  * rows of up to 8 entries (one batch of gathers), 128 columns where that pads
+//    no more: Laplacian 101^3, N = 128 and 256: 393 / 343, 802 / 690 (64^3, N = 256,
+//    B within the Infinity Cache: 139 / 150); rows of 6 on average, 500,000,
+//    N = 128 and 256: 252 / 234, 505 / 455 (rows of 24: 300 / 312).
+int32_t wide_col_tile(const sd_stats_t &st, int32_t family, int32_t n, int64_t b_bytes) {
+  const bool rows = family == SD_FMT_CSR_ROW, ell = family == SD_FMT_ELL;
+  if (n < 128) return rows || ell || family == SD_FMT_CSR_SPLIT ? 0 : 64;
+  const bool wide = (ell && st.row_max <= 8 && b_bytes > kMallBytes) || (rows && st.row_mean <= 8.0);
+  return wide && (n % 128 == 0 || n % 128 > 64) ? 128 : 64;
 }
 
 int32_t slices_for(const sd_stats_t &st, int32_t family, int32_t n, int32_t G) {

@@ -202,13 +202,16 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
   // 64-column passes halve the gathered footprint per pass (measured on the
   // power-law workloads at N = 128: -10 to -14 %; no gain at N <= 64).
   int32_t col_tile = o.col_tile;
+  // wide_col_tile refines it once the family is known.
   if (col_tile == 0 && n > 64 && 4 * (int64_t)A.k * n > sd::kMallBytes / 2) col_tile = 64;
+  const int64_t b_bytes = 4 * (int64_t)A.k * n;
+  sd::PlanChoice pc = sd::choose_plan(stats, n, I.cu_count, sd::geometry_for(n, vec4, col_tile).G, o);
+  if (o.col_tile == 0 && col_tile > 0) col_tile = sd::wide_col_tile(stats, pc.family, n, b_bytes);
   const sd::Geometry geo = sd::geometry_for(n, vec4, col_tile);
   p->col_tile_req = col_tile;
   I.lanes_per_row = geo.G;
   I.col_tile = geo.G * geo.VW;
   I.col_passes = geo.coltiles;
-  sd::PlanChoice pc = sd::choose_plan(stats, n, I.cu_count, geo.G, o);
   if (pc.family < SD_FMT_CSR_ROW || pc.family > SD_FMT_SELL) return SD_ERR_INVALID_VALUE;
   if (pc.T < 1 || pc.c < 1 || pc.U < 1) return SD_ERR_INVALID_VALUE;
   if (pc.engine < SD_ENGINE_AUTO || pc.engine > SD_ENGINE_VALU) return SD_ERR_INVALID_VALUE;
@@ -495,10 +498,10 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
   if ((I.family == SD_FMT_CSR_ROW || I.family == SD_FMT_CSR_SPLIT) && o.rows_per_group == 0 && I.rows_per_group == 1 &&
       o.gather_unroll == 0 && I.gather_unroll == 8 && I.row_slices == 1) {
     if (I.family == SD_FMT_CSR_SPLIT) {
-      p->stream = sd::stream_for(I.family, I.n_light, 0.0, geo.G, 0, 0);
+      p->stream = sd::stream_for(I.family, I.n_light, 0.0, geo.G, 0, 0, b_bytes);
     } else if (o.wg_order == 0 && I.wg_order != 3) {
       p->stream = sd::stream_for(I.family, A.m, stats.row_mean, geo.G, 2 * I.reach,
-                                 4 * std::min<int64_t>(n, (int64_t)geo.G * geo.VW));
+                                 4 * std::min<int64_t>(n, (int64_t)geo.G * geo.VW), b_bytes);
       if (p->stream > 0) I.wg_order = 1;
     }
   }

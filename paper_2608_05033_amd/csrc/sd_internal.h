@@ -130,8 +130,13 @@ int64_t median_row_reach(const CsrView &A);
 int32_t chunk_for_reach(int64_t reach, int64_t rows_per_wg);
 // Rows streamed per lane group of G lanes by the row kernels (0: one row per lane
 // group at a time, batched by the wave).  window_rows: rows of B around a row
-// that it typically uses; row_bytes: bytes of one in a column pass (CSR_ROW only).
-int32_t stream_for(int32_t family, int64_t rows, double row_mean, int32_t G, int64_t window_rows, int64_t row_bytes);
+// that it typically uses; row_bytes: bytes of one in a column pass; b_bytes: all of
+// B (CSR_ROW only).
+int32_t stream_for(int32_t family, int64_t rows, double row_mean, int32_t G, int64_t window_rows, int64_t row_bytes,
+                   int64_t b_bytes);
+// Dense columns per lane group when B is larger than half the Infinity Cache and
+// n > 64 (0: the whole width).
+int32_t wide_col_tile(const sd_stats_t &st, int32_t family, int32_t n, int64_t b_bytes);
 // Row batching for the row kernels: rows per lane group J in {1, 2, 4}
 // (J <= G) and B-row gathers per row per batch UNR in {4, 8}.
 void row_batch_for(const sd_stats_t &st, int64_t rows, int32_t G, int32_t cu_count, int32_t req_J,
