@@ -4,8 +4,9 @@
 // kernels are short: above a few MB one hipMalloc or hipFree took 20-450 us
 // here, and a plan with its scratch makes about 20 of them (R-MAT 500 k
 // vertices, 8 M edges: 1.7 of the 3.6 ms of sd_plan_device + sd_spmm +
-// sd_plan_destroy).  Freed blocks are kept per device up to kKeep bytes and
-// handed out again, best fit within a quarter of the size asked for.
+// sd_plan_destroy).  Freed blocks are kept per device up to kKeep bytes, the
+// longest kept making room, and handed out again, best fit within a quarter of
+// the size asked for.
 //
 // A block may be handed to any stream, so nothing that uses it may be pending by
 // then: scratch is given back after its stream has drained (kIdle); a plan's
@@ -15,6 +16,7 @@
 // otherwise fail, returns the kept blocks to the device.
 #include <hip/hip_runtime.h>
 
+#include <cstdint>
 #include <map>
 #include <mutex>
 #include <unordered_map>
@@ -33,10 +35,32 @@ struct Block {
 struct Kept {
   void *p;
   bool in_flight;
+  uint64_t age;
 };
 struct DevicePool {
-  std::multimap<size_t, Kept> blocks;
+  std::multimap<size_t, Kept> blocks;                              // by size
+  std::map<uint64_t, std::multimap<size_t, Kept>::iterator> ages;  // the longest kept first
   size_t kept = 0;
+  uint64_t next_age = 0;
+
+  void add(size_t bytes, void *p, bool in_flight) {  // may throw: nothing is added then
+    auto it = blocks.emplace(bytes, Kept{p, in_flight, next_age});
+    try {
+      ages.emplace(next_age, it);
+    } catch (...) {
+      blocks.erase(it);
+      throw;
+    }
+    ++next_age;
+    kept += bytes;
+  }
+  void *take(std::multimap<size_t, Kept>::iterator it) {
+    void *p = it->second.p;
+    kept -= it->first;
+    ages.erase(it->second.age);
+    blocks.erase(it);
+    return p;
+  }
 };
 struct Pool {
   std::mutex mu;
@@ -60,9 +84,7 @@ size_t rounded(size_t bytes) {
 void release_kept(Pool &P, int device) {
   for (auto &d : P.dev) {
     if (device >= 0 && d.first != device) continue;
-    for (auto &b : d.second.blocks) (void)hipFree(b.second.p);
-    d.second.blocks.clear();
-    d.second.kept = 0;
+    while (!d.second.blocks.empty()) (void)hipFree(d.second.take(d.second.blocks.begin()));
   }
 }
 
@@ -89,11 +111,8 @@ hipError_t pool_alloc(void **out, size_t bytes) {
       }
     }
     if (fits) {
-      void *q = it->second.p;
-      P.live.emplace(q, Block{dev, it->first});  // may throw: before the block leaves the list
-      D.kept -= it->first;
-      D.blocks.erase(it);
-      *out = q;
+      P.live.emplace(it->second.p, Block{dev, it->first});  // may throw: before the block leaves the list
+      *out = D.take(it);
       return hipSuccess;
     }
     void *q = nullptr;
@@ -126,10 +145,10 @@ void pool_free(void *p, PoolState state) {
   const Block b = it->second;
   P.live.erase(it);
   DevicePool &D = P.dev[b.device];
-  if (state != kUnknown && D.kept + b.bytes <= kKeep) {
+  if (state != kUnknown && b.bytes <= kKeep) {
+    while (D.kept + b.bytes > kKeep) (void)hipFree(D.take(D.ages.begin()->second));
     try {
-      D.blocks.emplace(b.bytes, Kept{p, state == kInFlight});
-      D.kept += b.bytes;
+      D.add(b.bytes, p, state == kInFlight);
       return;
     } catch (const std::bad_alloc &) {
     }
