@@ -194,9 +194,8 @@ typedef enum {
   SD_FMT_SELL = 8
 } sd_format_t;
 
-/* BSR / BELL engine.  MFMA (fp32 matrix cores) serves any width: column tiles
- * of 64, 32 and 16 (the last one partial) with 16-byte aligned B and C, and
- * 16-column tiles of single floats otherwise.  VALU: one FMA per lane per
+/* BSR / BELL engine.  MFMA (fp32 matrix cores) serves any width, in column tiles
+ * of 16 to 128 (the last one partial).  VALU: one FMA per lane per
  * block entry. */
 typedef enum { SD_ENGINE_AUTO = 0, SD_ENGINE_MFMA = 1, SD_ENGINE_VALU = 2 } sd_engine_t;
 
@@ -303,9 +302,9 @@ int sd_plan_device(const sd_csr_t *A, int32_t n, const sd_plan_opts_t *opts, voi
  * B: device, rows_B x n row-major, leading dimension n (rows_B = k, or m for
  * a transpose plan).  C: device, rows_C x n row-major (rows_C = m, or k), fully
  * overwritten (no accumulation).  B and C must not overlap (checked:
- * SD_ERR_INVALID_VALUE).  B and C are used
- * with 128-bit accesses when both are 16-byte aligned and n % 4 == 0, else
- * with 32-bit accesses.  No allocation, no host synchronisation, no memset:
+ * SD_ERR_INVALID_VALUE).  B and C need the
+ * 4-byte alignment of their elements and no more; from n = 4 on they are used
+ * with 128-bit accesses whatever n and the pointers.  No allocation, no host synchronisation, no memset:
  * the call may be captured into a HIP graph and replayed (the plan's
  * workspace is fixed at plan time; replays on one plan must not overlap).
  * Errors: SD_ERR_INVALID_VALUE (null plan/pointers, overlapping B and C), SD_ERR_NO_DEVICE,

@@ -23,7 +23,7 @@ struct DenseIO {
   const float *B;
   float *C;
   int32_t n;
-  int32_t vec4;    // 1: B and C 16-byte aligned and n % 4 == 0
+  int32_t vec4;    // 1: four columns per lane (any n >= 4, any alignment), 0: one
   int32_t policy;  // B-gather cache policy: 0 normal, 1 tiered by the column tag, 2 non-temporal
   int32_t col_tile;  // dense columns per lane group (power of two >= 4), 0 = whole width
   int32_t order;     // workgroup order: 1 one contiguous range of rows per XCD, 0 hardware round-robin,
@@ -56,7 +56,7 @@ hipError_t launch_csr_merge(const CsrOperand &A, const int32_t *coords, int32_t 
 
 // Block formats: bptr == nullptr selects Blocked-ELL with `width` slots per
 // block-row.  engine: 1 MFMA (any width, in column tiles of one size, the last
-// one partial; 16-column tiles of single floats without vec4), 2 VALU.
+// one partial; 16-column tiles without vec4), 2 VALU.
 // zero_block: index of a block with column -1 and zero values that follows the
 // stored blocks (the MFMA kernel fetches it for slots past a block-row's end).
 // zrow: io.n zero floats (16-byte aligned), the MFMA kernel's B operand for

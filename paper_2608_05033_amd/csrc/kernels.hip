@@ -9,7 +9,12 @@
 //
 //  * A lane group of G lanes owns one sparse row (or chunk, or merge-path
 //    piece) and covers G*VW output columns, VW = 4 giving one 128-bit load of
-//    a B row per lane per nonzero.  64/G rows share a wave.
+//    a B row per lane per nonzero.  64/G rows share a wave.  Widths that are no
+//    multiple of 4 and pointers off 16 bytes use the same loads (they need 4-byte
+//    alignment only); the last lane takes the row's last 4 columns and stores
+//    those its neighbour does not.  One column per lane, as those cases ran
+//    before, issues four times the loads: 7-point Laplacian 60^3, N = 33: 77 us
+//    against 25; R-MAT 200 k vertices, 3 M edges, N = 101: 279 against 129.
 //  * The group loads G (column, value) pairs of its nonzero stream with one
 //    coalesced load per lane, then broadcasts them inside the group with
 //    ds_bpermute; up to 8 B-row loads are issued back to back
@@ -35,20 +40,29 @@ namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
+typedef float f2 __attribute__((ext_vector_type(2)));
+
+// T: a lane's registers.  M: the same in global memory, where rows of B and C of
+// any width and any float pointer give 4-byte alignment only; the hardware takes
+// its 8- and 16-byte accesses at any 4 bytes.
+typedef f4 f4_mem __attribute__((aligned(4)));
+typedef f2 f2_mem __attribute__((aligned(4)));
 template <int VW>
 struct VecOf;
 template <>
 struct VecOf<4> {
   using T = f4;
+  using M = f4_mem;
 };
 template <>
 struct VecOf<1> {
   using T = float;
+  using M = float;
 };
-typedef float f2 __attribute__((ext_vector_type(2)));
 template <>
 struct VecOf<2> {
   using T = f2;
+  using M = f2_mem;
 };
 
 // Element t of a 1-, 2- or 4-wide lane vector.
@@ -112,17 +126,34 @@ __device__ __forceinline__ bool split_block(int order, uint32_t chunk_blocks, ui
 
 template <int VW>
 __device__ __forceinline__ typename VecOf<VW>::T load_v(const float *p) {
-  return *reinterpret_cast<const typename VecOf<VW>::T *>(p);
+  return *reinterpret_cast<const typename VecOf<VW>::M *>(p);
 }
 
+// First column a lane loads (of B, or of partial sums): its own, or the last VW
+// columns of the row for the lane whose columns run past the width (it then
+// repeats some of its neighbour's work) and for lanes wholly past it.  VW <= n.
 template <int VW>
-__device__ __forceinline__ void store_nt(float *p, typename VecOf<VW>::T v) {
-  __builtin_nontemporal_store(v, reinterpret_cast<typename VecOf<VW>::T *>(p));
+__device__ __forceinline__ int32_t load_col(int32_t col, int32_t n) {
+  return min(col, n - VW);
 }
 
-template <int VW>
-__device__ __forceinline__ void store_v(float *p, typename VecOf<VW>::T v) {
-  *reinterpret_cast<typename VecOf<VW>::T *>(p) = v;
+// Stores the lane's columns of a row; col < n is the lane's own first column and
+// v starts at load_col(col, n).  Every column has one writer.
+template <int VW, bool NT>
+__device__ __forceinline__ void store_cols(float *row, int32_t col, int32_t n, typename VecOf<VW>::T v) {
+  if (VW == 1 || n % VW == 0 || col + VW <= n) {  // n % VW: the same for every lane
+    auto *p = reinterpret_cast<typename VecOf<VW>::M *>(row + col);
+    if constexpr (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
+  } else {
+    // the part of [n - VW, n) from col on
+#pragma unroll
+    for (int t = 1; t < VW; ++t)
+      if (n - VW + t >= col) {
+        if constexpr (NT) __builtin_nontemporal_store(elem(v, t), row + n - VW + t);
+        else row[n - VW + t] = elem(v, t);
+      }
+  }
 }
 
 // Gathers the lane's slice of B row (raw & 0x7fffffff).  policy 0: normal
@@ -134,9 +165,9 @@ __device__ __forceinline__ void store_v(float *p, typename VecOf<VW>::T v) {
 template <int VW>
 __device__ __forceinline__ typename VecOf<VW>::T gather_b(const float *__restrict__ Bl, int32_t raw, int32_t n,
                                                           int policy) {
-  using V = typename VecOf<VW>::T;
   const float *p = Bl + (int64_t)(raw & 0x7fffffff) * n;
-  if (policy == 2 || (policy == 1 && raw < 0)) return __builtin_nontemporal_load(reinterpret_cast<const V *>(p));
+  if (policy == 2 || (policy == 1 && raw < 0))
+    return __builtin_nontemporal_load(reinterpret_cast<const typename VecOf<VW>::M *>(p));
   return load_v<VW>(p);
 }
 
@@ -231,7 +262,7 @@ __device__ __forceinline__ void rows_wave(int64_t w0, const int32_t *__restrict_
   const int lane = threadIdx.x & 63;
   const int glane = lane & (G - 1), gbase = lane & ~(G - 1), gidx = lane / G;
   const bool col_ok = col < n;
-  const float *__restrict__ Bl = B + col;
+  const float *__restrict__ Bl = B + load_col<VW>(col, n);
   int32_t my_row = -1, my_p0 = 0, my_p1 = 0;
   if (lane < WR && w0 + lane < nrows) {
     // LIST: rowptr is indexed by list position (the heavy-split layout keeps
@@ -287,7 +318,7 @@ __device__ __forceinline__ void rows_wave(int64_t w0, const int32_t *__restrict_
       load_tile<G>(colidx, vals, p0[j] + UNR, p1[j], glane, cc, vv);
       gather_rows<G, VW>(colidx, vals, p0[j] + UNR, p1[j], cc, vv, Bl, n, col_ok, acc[j], glane, gbase);
     }
-    if (row[j] >= 0 && col_ok) store_nt<VW>(C + (int64_t)row[j] * n + col, acc[j]);
+    if (row[j] >= 0 && col_ok) store_cols<VW, true>(C + (int64_t)row[j] * n, col, n, acc[j]);
   }
 }
 
@@ -316,7 +347,7 @@ __device__ __forceinline__ void rows_stream(StreamLds &lds, int64_t first, int r
   const int lane = threadIdx.x & 63;
   const int glane = lane & (G - 1), gbase = lane & ~(G - 1);
   const bool col_ok = col < n;
-  const float *__restrict__ Bl = B + col;
+  const float *__restrict__ Bl = B + load_col<VW>(col, n);
   for (int t = threadIdx.x; t <= rows; t += 256) {
     lds.bounds[t] = rowptr[first + t];
     if (LIST && t < rows) lds.ids[t] = rowlist[first + t];
@@ -367,7 +398,7 @@ __device__ __forceinline__ void rows_stream(StreamLds &lds, int64_t first, int r
     if (off >= cnt) {
       if (e - p <= G) {  // the row's last tile
         const int64_t row = LIST ? (int64_t)lds.ids[r] : first + r;
-        if (col_ok) store_nt<VW>(C + row * n + col, acc);
+        if (col_ok) store_cols<VW, true>(C + row * n, col, n, acc);
         acc = (V)(0.0f);
         r = nr;
       }
@@ -445,8 +476,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(J <= 1 ? 6 
     int32_t c0;
     float v0;
     load_tile<G>(colidx, vals, p0, p1, glane, c0, v0);
-    gather_rows<G, VW>(colidx, vals, p0, p1, c0, v0, B + col, n, col_ok, acc, glane, gbase);
-    if (q < nchunks && col_ok) store_v<VW>(ws + q * n + col, acc);
+    gather_rows<G, VW>(colidx, vals, p0, p1, c0, v0, B + load_col<VW>(col, n), n, col_ok, acc, glane, gbase);
+    if (q < nchunks && col_ok) store_cols<VW, false>(ws + q * n, col, n, acc);
   } else {
     const int64_t lb = (int64_t)(blk - chunk_blocks);
     if constexpr (J == 0) {
@@ -541,7 +572,7 @@ __global__ __launch_bounds__(256) void k_split_fixup(const int32_t *__restrict__
   if (h >= nheavy) return;  // wave-uniform
   const int32_t col = blockIdx.y * (G * VW) + glane * VW;
   const bool col_ok = col < n;
-  const float *__restrict__ wl = ws + (col_ok ? col : 0);  // lanes past n read column 0 and never store
+  const float *__restrict__ wl = ws + load_col<VW>(col, n);
   const int32_t q1 = heavy_ptr[h + 1];
   V a0 = (V)(0.0f), a1 = (V)(0.0f), a2 = (V)(0.0f), a3 = (V)(0.0f);
   int32_t q = heavy_ptr[h] + s;
@@ -553,7 +584,7 @@ __global__ __launch_bounds__(256) void k_split_fixup(const int32_t *__restrict__
   }
   for (; q < q1; q += S) a0 += load_v<VW>(wl + (int64_t)q * n);
   const V acc = slice_reduce<G, S>((a0 + a1) + (a2 + a3));
-  if (s == 0 && col_ok) store_nt<VW>(C + (int64_t)heavy_rows[h] * n + col, acc);
+  if (s == 0 && col_ok) store_cols<VW, true>(C + (int64_t)heavy_rows[h] * n, col, n, acc);
 }
 
 template <int G, int VW, int S, int UNR>
@@ -575,9 +606,9 @@ __global__ __launch_bounds__(256) void k_csr_slices(const int32_t *__restrict__ 
     p0 = rowptr[r];
     p1 = rowptr[r + 1];
   }
-  V acc = slice_sum<G, VW, S, UNR>(colidx, vals, p0, p1, s, B + (col_ok ? col : 0), n);
+  V acc = slice_sum<G, VW, S, UNR>(colidx, vals, p0, p1, s, B + load_col<VW>(col, n), n);
   acc = slice_reduce<G, S>(acc);
-  if (r < nrows && s == 0 && col_ok) store_nt<VW>(C + r * n + col, acc);
+  if (r < nrows && s == 0 && col_ok) store_cols<VW, true>(C + r * n, col, n, acc);
 }
 
 // k_csr_split at narrow widths: a chunk takes a whole wave (64 / G slices;
@@ -601,7 +632,7 @@ __global__ __launch_bounds__(256) void k_split_slices(const int32_t *__restrict_
   if (!split_block(order, chunk_blocks, blk)) return;  // as k_csr_split
   const int32_t col = blockIdx.y * (G * VW) + glane * VW;
   const bool col_ok = col < n;
-  const float *__restrict__ Bl = B + (col_ok ? col : 0);
+  const float *__restrict__ Bl = B + load_col<VW>(col, n);
   if (blk < chunk_blocks) {
     constexpr int SC = 64 / G;
     const int sc = lane / G;
@@ -614,7 +645,7 @@ __global__ __launch_bounds__(256) void k_split_slices(const int32_t *__restrict_
       p1 = chunks[3 * q + 2];
     }
     V acc = slice_reduce<G, SC>(slice_sum<G, VW, SC, UNR>(colidx, vals, p0, p1, sc, Bl, n));
-    if (q < nchunks && sc == 0 && col_ok) store_v<VW>(ws + q * n + col, acc);
+    if (q < nchunks && sc == 0 && col_ok) store_cols<VW, false>(ws + q * n, col, n, acc);
   } else {
     const int64_t i = ((int64_t)(blk - chunk_blocks) * kWaves + wave) * RPW + lane / L;
     int32_t row = -1, p0 = 0, p1 = 0;
@@ -624,7 +655,7 @@ __global__ __launch_bounds__(256) void k_split_slices(const int32_t *__restrict_
       p1 = rowptr[i + 1];
     }
     V acc = slice_reduce<G, S>(slice_sum<G, VW, S, UNR>(colidx, vals, p0, p1, s, Bl, n));
-    if (row >= 0 && s == 0 && col_ok) store_nt<VW>(C + (int64_t)row * n + col, acc);
+    if (row >= 0 && s == 0 && col_ok) store_cols<VW, true>(C + (int64_t)row * n, col, n, acc);
   }
 }
 
@@ -664,7 +695,7 @@ __global__ __launch_bounds__(256) void k_csr_merge(const int32_t *__restrict__ r
   const int64_t u = ((int64_t)blk * kWaves + wave) * RPW + lane / G;
   const int32_t col = blockIdx.y * (G * VW) + glane * VW;
   const bool col_ok = col < n;
-  const float *__restrict__ Bl = B + col;
+  const float *__restrict__ Bl = B + load_col<VW>(col, n);
   int32_t i0 = 0, i1 = 0, j0 = 0, j1 = 0;
   if (u < units) {
     i0 = coords[2 * u];
@@ -698,9 +729,9 @@ __global__ __launch_bounds__(256) void k_csr_merge(const int32_t *__restrict__ r
   auto close_row = [&]() {
     if (col_ok) {
       if (head)
-        store_v<VW>(part + ((int64_t)units + u) * n + col, acc);
+        store_cols<VW, false>(part + ((int64_t)units + u) * n, col, n, acc);
       else
-        store_nt<VW>(C + (int64_t)i * n + col, acc);
+        store_cols<VW, true>(C + (int64_t)i * n, col, n, acc);
     }
     acc = (V)(0.0f);
     head = false;
@@ -774,7 +805,7 @@ __global__ __launch_bounds__(256) void k_csr_merge(const int32_t *__restrict__ r
       rows[u] = has ? i1 : -1;
       rows[units + u] = i0 < i1 && j0 > rowptr[i0] ? i0 : -1;
     }
-    if (has && col_ok) store_v<VW>(part + u * n + col, acc);
+    if (has && col_ok) store_cols<VW, false>(part + u * n, col, n, acc);
   }
 }
 
@@ -801,7 +832,7 @@ __global__ __launch_bounds__(256) void k_merge_fixup(const int32_t *__restrict__
   const int64_t u = ((int64_t)blockIdx.x * kWaves + wave) * S + s;
   const int32_t col = blockIdx.y * (G * VW) + glane * VW;
   const bool col_ok = col < n;
-  const float *__restrict__ pl = part + (col_ok ? col : 0);  // lanes past n read column 0 and never store
+  const float *__restrict__ pl = part + load_col<VW>(col, n);
   int32_t r = -1, end = 0;  // carries [u, end) go to row r
   if (u < units) {
     r = rows[u];
@@ -822,7 +853,7 @@ __global__ __launch_bounds__(256) void k_merge_fixup(const int32_t *__restrict__
     for (int t = 1; t < kAlone; ++t)
       if (u + t < end) sum += load_v<VW>(pl + (u + t) * n);
     sum = add_head(sum, r, end);
-    if (col_ok) store_nt<VW>(C + (int64_t)r * n + col, sum);
+    if (col_ok) store_cols<VW, true>(C + (int64_t)r * n, col, n, sum);
   }
   uint64_t pending = __ballot(r >= 0 && !alone && glane == 0);
   while (pending) {  // wave-uniform
@@ -840,7 +871,7 @@ __global__ __launch_bounds__(256) void k_merge_fixup(const int32_t *__restrict__
     }
     for (; q < e; q += S) a0 += load_v<VW>(pl + q * n);
     const V sum = add_head(slice_reduce<G, S>((a0 + a1) + (a2 + a3)), row, e);
-    if (s == 0 && col_ok) store_nt<VW>(C + (int64_t)row * n + col, sum);
+    if (s == 0 && col_ok) store_cols<VW, true>(C + (int64_t)row * n, col, n, sum);
   }
 }
 
@@ -864,7 +895,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
   const int32_t col = blockIdx.y * (G * VW) + glane * VW;
   const bool col_ok = col < n;
   const bool row_ok = r < m;
-  const float *__restrict__ Bl0 = B + (col_ok ? col : 0);  // lanes past n load column 0 and never store
+  const float *__restrict__ Bl0 = B + load_col<VW>(col, n);  // lanes past n load column 0 and never store
   V acc = (V)(0.0f);
   for (int32_t t = 0; t < W; t += G) {
     const int32_t cnt = min(G, W - t);  // the same for every lane
@@ -898,7 +929,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
         if (t0 + u < cnt) acc += av[u] * bv[u];
     }
   }
-  if (row_ok && col_ok) store_nt<VW>(C + r * n + col, acc);
+  if (row_ok && col_ok) store_cols<VW, true>(C + r * n, col, n, acc);
 }
 
 // ELL with rows pipelined per lane group (W <= G: one entry load per lane
@@ -922,7 +953,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
   int64_t r = (int64_t)blk * PASS_ROWS + wave * RPW + lane / G;
   const int32_t col = blockIdx.y * (G * VW) + glane * VW;
   const bool col_ok = col < n;
-  const float *__restrict__ Bl0 = B + (col_ok ? col : 0);  // lanes past n load column 0 and never store
+  const float *__restrict__ Bl0 = B + load_col<VW>(col, n);  // lanes past n load column 0 and never store
   int32_t c = -1;
   float v = 0.0f;
   if (r < m && glane < W) {
@@ -959,7 +990,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
       for (int u = 0; u < UNR; ++u)
         if (t0 + u < W) acc += av[u] * bv[u];
     }
-    if (r < m && col_ok) store_nt<VW>(C + r * n + col, acc);
+    if (r < m && col_ok) store_cols<VW, true>(C + r * n, col, n, acc);
     c = cn;
     v = vn;
     r = rn;
@@ -988,7 +1019,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
   const int64_t i = ((int64_t)blk * kWaves + wave) * RPW + lane / G;
   const int32_t col = blockIdx.y * (G * VW) + glane * VW;
   const bool col_ok = col < n;
-  const float *__restrict__ Bl0 = B + (col_ok ? col : 0);  // lanes past n load column 0 and never store
+  const float *__restrict__ Bl0 = B + load_col<VW>(col, n);  // lanes past n load column 0 and never store
   const bool row_ok = i < m;
   int64_t base = 0;
   int32_t W = 0, orow = 0;
@@ -1031,7 +1062,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
         if (t0 + u < cnt) acc += av[u] * bv[u];
     }
   }
-  if (row_ok && col_ok) store_nt<VW>(Cout + (int64_t)orow * n + col, acc);
+  if (row_ok && col_ok) store_cols<VW, true>(Cout + (int64_t)orow * n, col, n, acc);
 }
 
 // ---------------------------------------------------------- column windows ---
@@ -1078,12 +1109,12 @@ __global__ __launch_bounds__(256) void k_win_split(
     float v0;
     load_tile<G>(code, vals, p0, p1, glane, c0, v0);
     V acc = (V)(0.0f);
-    gather_rows<G, VW>(code, vals, p0, p1, c0, v0, B + col, n, col_ok, acc, glane, gbase);
-    if (t < nchunks && col_ok) store_v<VW>(ws + q * n + col, acc);
+    gather_rows<G, VW>(code, vals, p0, p1, c0, v0, B + load_col<VW>(col, n), n, col_ok, acc, glane, gbase);
+    if (t < nchunks && col_ok) store_cols<VW, false>(ws + q * n, col, n, acc);
     return;
   }
   const int64_t w = (int64_t)(blk - chunk_blocks);
-  const float *__restrict__ Bl0 = B + (col_ok ? col : 0);  // lanes past n load column 0 and never store
+  const float *__restrict__ Bl0 = B + load_col<VW>(col, n);  // lanes past n load column 0 and never store
 
   const int32_t s0 = wptr[w], D = wptr[w + 1] - s0;
   for (int32_t d0 = 0; d0 < D; d0 += GROUPS * STAGE) {
@@ -1149,7 +1180,7 @@ __global__ __launch_bounds__(256) void k_win_split(
           if (u0 + u < cnt) acc += av[u] * bv[u];
       }
     }
-    if (row_ok && col_ok) store_nt<VW>(C + (int64_t)crow * n + col, acc);
+    if (row_ok && col_ok) store_cols<VW, true>(C + (int64_t)crow * n, col, n, acc);
   }
 }
 
@@ -1166,8 +1197,8 @@ __global__ __launch_bounds__(256) void k_win_split(
 // output row are NT consecutive floats of a C row.
 // Accumulates the blocks q = first .. first + cnt - 1 of one block-row into
 // acc (a 16 x 16 NT NQ tile of C at columns col0 ..).  RAG: the tile may run past
-// the width n (a multiple of NT); those lanes read the last NT columns of B (so
-// every address is in range), and their output columns are never stored.
+// the width n; lanes whose columns do read the last NT columns of B instead (so
+// every address is in range).
 // zrow: n zero floats owned by the plan, read in place of a B row by every
 // slot that has no B row (a row past K, a Blocked-ELL padding block, the zero
 // block past a block-row's end), so a non-finite B row never meets the zero
@@ -1216,7 +1247,7 @@ __device__ __forceinline__ void bsr_mfma_blocks(int64_t first, int64_t cnt, int6
         const bool ok = valid && krow < k;
         const float *__restrict__ src = ok ? B + (int64_t)krow * n : zrow;
         const int32_t col = col0 + qq * 16 * NT + NT * c;
-        b[s][qq] = *reinterpret_cast<const BV *>(src + (RAG ? min(col, n - NT) : col));
+        b[s][qq] = load_v<NT>(src + (RAG ? load_col<NT>(col, n) : col));
       }
     }
   };
@@ -1298,8 +1329,10 @@ __global__ __launch_bounds__(256) void k_bsr_mfma(int32_t mb, int32_t m, int32_t
 #pragma unroll
           for (int t = 0; t < NT; ++t) o[t] = acc[qq][t][v];
         }
-        __builtin_nontemporal_store(o, reinterpret_cast<typename VecOf<NT>::T *>(
-                                           C + (int64_t)row * n + col));
+        if constexpr (RAG)
+          store_cols<NT, true>(C + (int64_t)row * n, col, n, o);
+        else
+          __builtin_nontemporal_store(o, reinterpret_cast<typename VecOf<NT>::M *>(C + (int64_t)row * n + col));
       }
     }
   }
@@ -1347,7 +1380,7 @@ __global__ __launch_bounds__(256) void k_bsr_valu(int32_t mb, int32_t m, int32_t
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
           const int32_t krow = bc * 16 + 4 * kq + kk;
-          b[kk] = krow < k ? load_v<VW>(B + (int64_t)krow * n + col) : (V)(0.0f);
+          b[kk] = krow < k ? load_v<VW>(B + (int64_t)krow * n + load_col<VW>(col, n)) : (V)(0.0f);
         }
 #pragma unroll
         for (int t = 0; t < RPL; ++t) {
@@ -1359,7 +1392,7 @@ __global__ __launch_bounds__(256) void k_bsr_valu(int32_t mb, int32_t m, int32_t
 #pragma unroll
     for (int t = 0; t < RPL; ++t) {
       const int32_t row = br * 16 + rg * RPL + t;
-      if (row < m) store_nt<VW>(C + (int64_t)row * n + col, acc[t]);
+      if (row < m) store_cols<VW, true>(C + (int64_t)row * n, col, n, acc[t]);
     }
   }
 }
@@ -1579,7 +1612,12 @@ hipError_t launch_csr_merge(const CsrOperand &A, const int32_t *coords, int32_t 
 
 hipError_t launch_ell(const int32_t *ecol, const float *eval, int32_t width, int32_t m, int32_t passes,
                       const DenseIO &io, hipStream_t s) {
-  const Geometry geo = geometry_for(io.n, io.vec4, io.col_tile);
+  // Long rows at narrow widths of no whole 4 columns: one column per lane, whose
+  // wider lane groups take fewer tiles per row (100,000 rows of 24, N = 5, 13, 17,
+  // 31: 18.3, 27.8, 34.2, 59.7 us against 19.9, 30.1, 37.3, 64.0 with four; rows
+  // of 7, N = 5, 17: 9.8, 31.2 against 7.3, 14.1).
+  const bool narrow = io.n % 4 != 0 && io.n < 32 && width > 16;
+  const Geometry geo = geometry_for(io.n, narrow ? 0 : io.vec4, io.col_tile);
   return with_geometry(geo, [&](auto gg) -> hipError_t {
     constexpr int G = decltype(gg)::G, VW = decltype(gg)::VW;
     if (passes >= 1 && width <= G) {

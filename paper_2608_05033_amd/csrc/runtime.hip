@@ -197,7 +197,7 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
   I.device = p->device;
 
   // ---- family and parameters
-  const int32_t vec4 = (n % 4 == 0) ? 1 : 0;
+  const int32_t vec4 = n >= 4 ? 1 : 0;
   // K tiles: when the dense operand is larger than half the Infinity Cache,
   // 64-column passes halve the gathered footprint per pass (measured on the
   // power-law workloads at N = 128: -10 to -14 %; no gain at N <= 64).
@@ -467,7 +467,9 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
     sd::row_batch_for(stats, I.family == SD_FMT_CSR_ROW ? A.m : I.n_light, geo.G, I.cu_count, o.rows_per_group,
                       o.gather_unroll, &I.rows_per_group, &I.gather_unroll);
     // narrow widths: lane groups that share a row
-    if (o.row_slices > 1 && (geo.G > 8 || geo.G * o.row_slices > 64)) return SD_ERR_UNSUPPORTED;
+    // (what is accepted is counted in lanes of one column where n % 4 != 0)
+    const int32_t Gs = sd::geometry_for(n, n % 4 == 0, col_tile).G;
+    if (o.row_slices > 1 && (Gs > 8 || Gs * o.row_slices > 64)) return SD_ERR_UNSUPPORTED;
     I.row_slices = o.row_slices > 0 ? o.row_slices : sd::slices_for(stats, I.family, n, geo.G);
     if (I.row_slices > 1) {
       I.rows_per_group = 1;
@@ -883,7 +885,7 @@ int sd_spmm(sd_plan_t p, const float *B, float *C, void *stream) {
   io.B = B;
   io.C = C;
   io.n = (int32_t)I.n;
-  io.vec4 = (I.n % 4 == 0) && ((reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(C)) % 16 == 0);
+  io.vec4 = I.n >= 4 ? 1 : 0;
   io.policy = I.cache_policy == 2 ? 1 : I.cache_policy == 3 ? 2 : 0;
   io.col_tile = p->col_tile_req;
   io.order = I.wg_order == 1 ? 1 : I.wg_order == 3 ? std::max(2, I.wg_chunk) : 0;

@@ -252,3 +252,34 @@ def test_streamed_rows(shape, n):
         # a row is summed in the same order either way
         assert np.array_equal(out.view(np.uint32), run(sd, other, B, m).view(np.uint32))
         assert_close(run(sd, plan, B, m, misalign=True), C64, S, f"streamed misaligned {shape} n={n}")
+
+
+ODD_FAMILIES = [("csr_row", {}), ("csr_row", {"row_slices": 1}), ("csr_split", {"heavy_threshold": 40, "chunk_nnz": 17}),
+                ("csr_merge", {"units": 301}), ("bsr", {"engine": "mfma"}), ("bell", {"engine": "valu"}), ("ell", {}),
+                ("ell", {"rows_per_group": 4}), ("win", {"heavy_threshold": 200}), ("sell", {})]
+
+
+@pytest.mark.parametrize("fam,opts", ODD_FAMILIES, ids=[f"{f}-{i}" for i, (f, _) in enumerate(ODD_FAMILIES)])
+@pytest.mark.parametrize("n", [4, 5, 6, 7, 9, 15, 17, 31, 33, 50, 63, 65, 101, 130, 255, 257])
+@pytest.mark.parametrize("off", [0, 1, 2, 3])
+def test_odd_widths(fam, opts, n, off):
+    """Four columns per lane at widths that leave the last lane fewer, with B and C
+    at every 4-byte offset, rows of up to three column passes, and nothing
+    written outside C."""
+    rng = np.random.default_rng(5)
+    lens = rng.integers(0, 40, 301)
+    lens[::50] = 250
+    A = gen.random_rows(301, 260, np.minimum(lens, 260).astype(np.int32), seed=1)
+    B = gen.dense_uniform(A.k, n, seed=n)
+    C64, S = oracle.spmm(A, B)
+    Bs = torch.empty(A.k * n + off, device="cuda")
+    Bs[off:] = torch.from_numpy(B.reshape(-1))
+    Cs = torch.full((A.m * n + 16,), -7.0, device="cuda")
+    first = 8 + off
+    Cd = Cs[first:first + A.m * n].view(A.m, n)
+    print(f"case odd {fam} {opts} n={n} off={off}", flush=True)
+    with sd.sd_plan_ex(A, n, force=fam, **opts) as plan:
+        sd.sd_spmm(plan, Bs[off:], Cd, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+    assert_close(Cd.cpu().numpy(), C64, S, f"odd {fam} n={n} off={off}")
+    assert bool((Cs[:first] == -7.0).all()) and bool((Cs[first + A.m * n:] == -7.0).all())
