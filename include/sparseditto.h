@@ -25,7 +25,6 @@
  *                   measured plan choices kept and reused across processes
  *   sd_plan_info / sd_plan_export / sd_plan_destroy / sd_status_string / sd_last_error
  *   sd_release_memory
- *   sd_gemm_tn[_workspace]  weight gradients of the dense transforms between products
  *
  * Conventions shared by every call:
  *   - Every function, except those of type void and the two that return a
@@ -463,19 +462,6 @@ int sd_plan_cache_load(const char *path);
 /* Frees the plan's host and device memory.  NULL is a no-op.  The caller must
  * make sure no sd_spmm on this plan is still running (synchronise its stream). */
 void sd_plan_destroy(sd_plan_t plan);
-
-/* C = X^T Y, the weight gradient of a dense transform over many rows: X (rows x p)
- * and Y (rows x q) device, fp32 row-major with leading dimensions ldx >= p and
- * ldy >= q; C device, p x q row-major, fully overwritten.  Computed in fp32 on the
- * matrix cores over ranges of rows whose partial sums go to `workspace` (device,
- * sd_gemm_tn_workspace bytes; its contents before the call do not matter) and
- * are added in a fixed order: the same inputs give the same bits.  Enqueued on
- * `stream`; no allocation and no synchronisation.
- * Errors: SD_ERR_INVALID_VALUE (null pointers, sizes below 1, a workspace that is
- * too small), SD_ERR_OVERFLOW, SD_ERR_HIP. */
-int sd_gemm_tn_workspace(int64_t rows, int32_t p, int32_t q, size_t *bytes);
-int sd_gemm_tn(const float *X, int64_t ldx, const float *Y, int64_t ldy, int64_t rows, int32_t p, int32_t q,
-               float *C, void *workspace, size_t workspace_bytes, void *stream);
 
 /* Device memory that destroyed plans and finished conversions leave is kept for
  * later plans, at most 1 GiB per device.  This returns what is kept to the

@@ -146,8 +146,6 @@ def _load():
     lib.sd_plan_export.argtypes = [_P, _i32, _P, ctypes.c_size_t]
     lib.sd_plan_destroy.argtypes = [_P]
     lib.sd_plan_destroy.restype = None
-    lib.sd_gemm_tn_workspace.argtypes = [_i64, _i32, _i32, ctypes.POINTER(ctypes.c_size_t)]
-    lib.sd_gemm_tn.argtypes = [_P, _i64, _P, _i64, _i64, _i32, _i32, _P, _P, ctypes.c_size_t, _P]
     lib.sd_release_memory.argtypes = []
     lib.sd_release_memory.restype = None
     lib.sd_plan_cache_clear.argtypes = []
@@ -160,14 +158,14 @@ def _load():
     lib.sd_last_error.argtypes = []
     lib.sd_last_error.restype = ctypes.c_char_p
     for f in ("sd_analyze", "sd_analyze_device", "sd_plan", "sd_plan_ex", "sd_spmm", "sd_plan_info", "sd_plan_export_size",
-              "sd_plan_export", "sd_plan_device", "sd_gemm_tn_workspace", "sd_gemm_tn", "sd_plan_cache_size", "sd_plan_cache_save", "sd_plan_cache_load"):
+              "sd_plan_export", "sd_plan_device", "sd_plan_cache_size", "sd_plan_cache_save", "sd_plan_cache_load"):
         getattr(lib, f).restype = ctypes.c_int
     return lib
 
 
 _lib = _load()
 EXPORTED = ("sd_analyze", "sd_analyze_device", "sd_plan", "sd_plan_ex", "sd_plan_device", "sd_spmm", "sd_spmm_merge_noalloc", "sd_plan_info", "sd_plan_export_size",
-            "sd_plan_export", "sd_plan_destroy", "sd_plan_cache_clear", "sd_plan_cache_size", "sd_plan_cache_save", "sd_plan_cache_load", "sd_release_memory", "sd_gemm_tn_workspace", "sd_gemm_tn", "sd_status_string", "sd_last_error")
+            "sd_plan_export", "sd_plan_destroy", "sd_plan_cache_clear", "sd_plan_cache_size", "sd_plan_cache_save", "sd_plan_cache_load", "sd_release_memory", "sd_status_string", "sd_last_error")
 
 
 def _check(status: int, where: str):
@@ -362,23 +360,6 @@ def sd_plan_export(plan: Plan, what: int) -> np.ndarray:
 
 def sd_plan_destroy(plan: Plan) -> None:
     plan.destroy()
-
-
-def sd_gemm_tn_workspace(rows: int, p: int, q: int) -> int:
-    """Bytes of workspace sd_gemm_tn needs."""
-    n = ctypes.c_size_t()
-    _check(_lib.sd_gemm_tn_workspace(int(rows), int(p), int(q), ctypes.byref(n)), "sd_gemm_tn_workspace")
-    return n.value
-
-
-def sd_gemm_tn(X, ldx: int, Y, ldy: int, rows: int, p: int, q: int, C, workspace, workspace_bytes: int,
-               stream=None) -> None:
-    """C = X^T Y on `stream`: X rows x p, Y rows x q, C p x q (device pointers
-    or float32 tensors, row-major with leading dimensions ldx and ldy)."""
-    if stream is not None and not isinstance(stream, int):
-        stream = int(stream.cuda_stream)
-    _check(_lib.sd_gemm_tn(_devptr(X), int(ldx), _devptr(Y), int(ldy), int(rows), int(p), int(q), _devptr(C),
-                           _devptr(workspace), int(workspace_bytes), stream), "sd_gemm_tn")
 
 
 def sd_release_memory() -> None:

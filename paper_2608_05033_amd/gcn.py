@@ -3,9 +3,8 @@
 The paper's application study (Sec. "Evaluation", GCN paragraph) trains a
 two-layer GCN on a normalised adjacency Â with four sparse aggregations per
 epoch: Â·(X W1) and Â·(H1 W2) forward, Âᵀ·G at both widths backward. Only the
-aggregation is replaced, and the weight gradients of the dense transforms (tall
-products X^T dC, which the library's GEMM runs on a handful of workgroups);
-everything else is ordinary torch operations.
+aggregation is replaced; the dense transforms, activation, loss and optimiser
+are ordinary torch operations.
 
 Each aggregation is `spmm(B, fwd, bwd)`: C = Â·B with plan `fwd`, and in the
 backward pass dB = Âᵀ·dC with the transpose plan `bwd` (A is not assumed
@@ -15,7 +14,7 @@ from __future__ import annotations
 
 import torch
 
-from . import Plan, sd_gemm_tn, sd_gemm_tn_workspace, sd_plan_device, sd_plan_ex, sd_spmm
+from . import Plan, sd_plan_device, sd_plan_ex, sd_spmm
 
 
 class _SpMM(torch.autograd.Function):
@@ -43,61 +42,6 @@ class _SpMM(torch.autograd.Function):
 def spmm(B: torch.Tensor, fwd: Plan, bwd: Plan) -> torch.Tensor:
     """C = Â·B; its gradient with respect to B is Âᵀ·dC (plan `bwd`)."""
     return _SpMM.apply(B, fwd, bwd)
-
-
-def _weight_grad(X: torch.Tensor, dC: torch.Tensor) -> torch.Tensor:
-    """X^T dC by sd_gemm_tn."""
-    X = X if X.stride(1) == 1 and X.stride(0) >= X.shape[1] else X.contiguous()
-    dC = dC.contiguous()
-    (rows, p), q = X.shape, dC.shape[1]
-    dW = torch.empty((p, q), dtype=torch.float32, device=X.device)
-    size = sd_gemm_tn_workspace(rows, p, q)
-    work = torch.empty(size, dtype=torch.uint8, device=X.device)
-    with torch.cuda.device(X.device):
-        sd_gemm_tn(X, X.stride(0), dC, q, rows, p, q, dW, work, size, torch.cuda.current_stream(X.device))
-    return dW
-
-
-class _Transform(torch.autograd.Function):
-    """X W, with its weight gradient by sd_gemm_tn.  A backward pass that is
-    itself differentiated (create_graph) uses torch's products throughout."""
-
-    @staticmethod
-    def forward(ctx, X, W):
-        ctx.save_for_backward(X, W)
-        return X @ W
-
-    @staticmethod
-    def backward(ctx, dC):
-        X, W = ctx.saved_tensors
-        dX = dC @ W.t() if ctx.needs_input_grad[0] else None
-        dW = None
-        if ctx.needs_input_grad[1]:
-            dW = X.t() @ dC if torch.is_grad_enabled() else _weight_grad(X, dC)
-        return dX, dW
-
-
-# Rows from which sd_gemm_tn beat torch's X^T dC at every width up to 256
-# measured (128 x 128: 21 against 56 us at 10,000 rows, 116 against 487 at
-# 262,144; 32 x 7: 22 against 36 and 61 against 350).  At 3,000 rows the two are
-# within 4 us either way, and at width 602 within a tenth at a million rows.
-_GRAD_ROWS, _GRAD_WIDTH = 8192, 256
-
-
-def transform(X: torch.Tensor, W: torch.Tensor) -> torch.Tensor:
-    """X @ W.  Many fp32 rows on the GPU take the native weight gradient; every
-    other case (other types and devices, few rows, wide layers, autocast,
-    function transforms, forward-mode or compiled tracing) is torch's own."""
-    if (X.dim() == 2 and W.dim() == 2 and X.is_cuda and W.is_cuda and X.device == W.device
-            and X.dtype == W.dtype == torch.float32 and type(X) in (torch.Tensor, torch.nn.Parameter)
-            and X.layout == W.layout == torch.strided and W.requires_grad and torch.is_grad_enabled()
-            and X.shape[1] == W.shape[0] and X.shape[0] >= _GRAD_ROWS
-            and 1 <= W.shape[0] <= _GRAD_WIDTH and 1 <= W.shape[1] <= _GRAD_WIDTH
-            and not torch.is_autocast_enabled() and not torch.compiler.is_compiling()
-            and not torch._C._are_functorch_transforms_active()
-            and torch.autograd.forward_ad._current_level < 0):
-        return _Transform.apply(X, W)
-    return X @ W
 
 
 class AggregationPlans:
@@ -154,8 +98,8 @@ class GCN2(torch.nn.Module):
         self.agg = AggregationPlans(A, sorted({hidden, classes}), **plan_opts)
 
     def forward(self, X: torch.Tensor) -> torch.Tensor:
-        H1 = torch.relu(self.agg(transform(X, self.W1)))
-        return self.agg(transform(H1, self.W2))
+        H1 = torch.relu(self.agg(X @ self.W1))
+        return self.agg(H1 @ self.W2)
 
 
 def train_epoch(model: GCN2, X, labels, opt) -> torch.Tensor:

@@ -131,77 +131,6 @@ def test_memory_reuse_in_flight():
             sd.sd_release_memory()
 
 
-@pytest.mark.parametrize("rows", [0, 1, 15, 16, 17, 127, 129, 5000])
-@pytest.mark.parametrize("p,q", [(1, 1), (7, 3), (64, 64), (65, 4), (128, 64), (36, 100), (130, 257)])
-@pytest.mark.parametrize("pad", [0, 1, 4])
-def test_gemm_tn(rows, p, q, pad):
-    """X^T Y at tile and row-range edges, with padded rows (aligned and not),
-    against fp64.  A sum of n products in any order is within n u S of the exact
-    one, u = 2^-24 and S the sum of the products' magnitudes."""
-    g = torch.Generator(device="cuda").manual_seed(rows + 31 * p + q)
-    X = torch.randn(rows, p + pad, device="cuda", generator=g)[:, :p]
-    Y = torch.randn(rows, q + pad, device="cuda", generator=g)[:, :q]
-    C = torch.full((p, q), float("nan"), device="cuda")
-    size = sd.sd_gemm_tn_workspace(rows, p, q)
-    work = torch.full((size // 4,), float("nan"), device="cuda")
-    print(f"case gemm_tn rows={rows} p={p} q={q} pad={pad}", flush=True)
-    sd.sd_gemm_tn(X, p + pad, Y, q + pad, rows, p, q, C, work, size, torch.cuda.current_stream())
-    want = X.double().cpu().t() @ Y.double().cpu()
-    S = X.double().abs().cpu().t() @ Y.double().abs().cpu()
-    assert bool(((C.double().cpu() - want).abs() <= (rows + 1) * 2.0 ** -24 * S).all())
-
-
-def test_gemm_tn_rejects():
-    x = torch.zeros(64, 8, device="cuda")
-    with pytest.raises(sd.SparseDittoError) as e:  # workspace too small
-        sd.sd_gemm_tn(x, 8, x, 8, 64, 8, 8, torch.empty(8, 8, device="cuda"), x, 4)
-    assert e.value.status == sd.SD_ERR_INVALID_VALUE
-    with pytest.raises(sd.SparseDittoError) as e:  # leading dimension below the width
-        sd.sd_gemm_tn(x, 4, x, 8, 64, 8, 8, torch.empty(8, 8, device="cuda"), x, 1 << 20)
-    assert e.value.status == sd.SD_ERR_INVALID_VALUE
-
-
-def test_transform_routes():
-    """The native weight gradient equals torch's, a differentiated backward pass
-    still works, and every other form is torch's own product."""
-    from paper_2608_05033_amd import gcn
-
-    g = torch.Generator(device="cuda").manual_seed(0)
-    X = torch.randn(gcn._GRAD_ROWS, 24, device="cuda", generator=g, requires_grad=True)
-    W = torch.randn(24, 12, device="cuda", generator=g, requires_grad=True)
-    V = torch.randn(gcn._GRAD_ROWS, 12, device="cuda", generator=g)
-    y = gcn.transform(X, W)
-    assert "Transform" in type(y.grad_fn).__name__
-    dx, dw = torch.autograd.grad((y * V).sum(), (X, W))
-    rx, rw = torch.autograd.grad(((X @ W) * V).sum(), (X, W))
-    S = X.detach().abs().t() @ V.abs()
-    assert torch.equal(dx, rx) and bool(((dw - rw).abs() <= 2 * gcn._GRAD_ROWS * 2.0 ** -24 * S).all())
-    # expanded and strided operands
-    E = torch.ones((), device="cuda").expand(gcn._GRAD_ROWS, 12)
-    Xt = torch.randn(24, gcn._GRAD_ROWS, device="cuda", generator=g).t()
-    (dw,) = torch.autograd.grad((gcn.transform(Xt, W) * E).sum(), (W,))
-    assert bool(((dw - Xt.t() @ E).abs() <= 2 * gcn._GRAD_ROWS * 2.0 ** -24 * (Xt.abs().t() @ E)).all())
-    # second derivatives
-    (gw,) = torch.autograd.grad((gcn.transform(X, W) ** 2).sum(), W, create_graph=True)
-    (hx,) = torch.autograd.grad(gw.sum(), X)
-    (gr,) = torch.autograd.grad(((X @ W) ** 2).sum(), W, create_graph=True)
-    (hr,) = torch.autograd.grad(gr.sum(), X)
-    assert torch.allclose(hx, hr, rtol=1e-4, atol=1e-3)
-    # torch's own product elsewhere
-    small = gcn.transform(X[:100], W)
-    half = gcn.transform(X.half(), W.half())
-    cpu = gcn.transform(X.cpu(), W.cpu())
-    with torch.autocast("cuda", dtype=torch.bfloat16):
-        cast = gcn.transform(X, W)
-    assert cast.dtype == torch.bfloat16
-    for t in (small, half, cpu, cast):
-        assert "Transform" not in type(t.grad_fn).__name__
-    tang = torch.func.jvp(lambda w: gcn.transform(X.detach(), w), (W.detach(),), (torch.ones_like(W),))[1]
-    assert torch.allclose(tang, X.detach() @ torch.ones_like(W), rtol=1e-5, atol=1e-4)
-    many = torch.func.vmap(lambda w: gcn.transform(X.detach(), w))(torch.stack([W.detach(), 2 * W.detach()]))
-    assert many.shape == (2, gcn._GRAD_ROWS, 12)
-
-
 @pytest.mark.parametrize("fam", ["bsr", "bell"])
 @pytest.mark.parametrize("mb", [3, 767, 768, 1100, 2050])
 @pytest.mark.parametrize("n", [4, 20, 36, 64, 68, 100, 128, 132, 200, 260])
