@@ -212,3 +212,21 @@ def test_odd_widths(fam, opts, n, off):
         torch.cuda.synchronize()
     assert_close(Cd.cpu().numpy(), C64, S, f"odd {fam} n={n} off={off}")
     assert bool((Cs[:first] == -7.0).all()) and bool((Cs[first + A.m * n:] == -7.0).all())
+
+
+@pytest.mark.parametrize("fam", ["bsr", "bell"])
+@pytest.mark.parametrize("k", [17, 16 * 32, 16 * 33 + 1, 16 * 65536, 16 * 65536 + 1, 2500003])
+def test_block_conversion_windows(fam, k):
+    """Device block conversion equals the host's where a block-row's columns end on
+    a word, a window, or reach over several windows; empty block-rows and rows."""
+    lens = np.array([0] * 16 + [min(k, 40)] * 20 + [0, 1, min(k, 300)] + [0] * 20 + [min(k, 7)] * 3, np.int32)
+    A = gen.random_rows(lens.size, k, lens, seed=k % 1000)
+    A.colidx[A.rowptr[17:37] - 1] = k - 1  # the last column in every row of two block-rows
+    print(f"case block conversion {fam} k={k}", flush=True)
+    with sd.sd_plan_ex(A, 8, force=fam) as host, \
+            sd.sd_plan_device(*_device_csr(A), A.m, A.k, A.nnz, 8, force=fam) as dev:
+        assert dev.info["device_built"] == 1
+        for what in (sd.SD_EXPORT_BLOCK_COL, sd.SD_EXPORT_BLOCK_VAL) + ((sd.SD_EXPORT_BLOCK_PTR,) if fam == "bsr" else ()):
+            assert sd.sd_plan_export(host, what).tobytes() == sd.sd_plan_export(dev, what).tobytes(), what
+        B = gen.dense_uniform(k, 8, seed=1)
+        assert run(sd, host, B, A.m).tobytes() == run(sd, dev, B, A.m).tobytes()  # the zero block as well
