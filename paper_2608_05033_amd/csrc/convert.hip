@@ -580,15 +580,197 @@ __global__ __launch_bounds__(256) void k_move_chunks(const int32_t *__restrict__
   }
 }
 
-// Stable radix sort of (key, value) pairs by the low `bits` bits.
-hipError_t sort_pairs(Scratch &sc, int slot, const int32_t *keys, int32_t *keys_out, const int32_t *vals,
-                      int32_t *vals_out, int n, int bits, hipStream_t s) {
-  size_t tmp = 0;
-  hipError_t e = hipcub::DeviceRadixSort::SortPairs(nullptr, tmp, keys, keys_out, vals, vals_out, n, 0, bits, s);
-  if (e == hipSuccess) e = pool_alloc(&sc.p[slot], std::max<size_t>(tmp, 1));
-  if (e == hipSuccess)
-    e = hipcub::DeviceRadixSort::SortPairs(sc.p[slot], tmp, keys, keys_out, vals, vals_out, n, 0, bits, s);
-  return e;
+// ---- stable sort of up to two lists of (key, value) pairs, keys below 2^bits
+// A radix sort of 10 bits a pass, three launches a pass for both lists together:
+// digits counted per tile, one wave per digit scans the tiles, and each tile's waves
+// rank their pairs by ballots and write them.  Launches bound it at these sizes:
+// analysis, plan and one product of a graph with 486 k light rows and 87 k chunks
+// take 663 us, against 781 with hipCUB's sort, which merges up to 1 M pairs in 24
+// launches for the two lists; a plan with 1.03 M light rows 0.70 ms against 0.82.
+// Longer lists go to hipCUB's single-sweep passes: a plan with 2.2 M light rows
+// takes 2.1 ms either way.
+constexpr int kSortTile = 4096, kSortBits = 10, kSortDigits = 1 << kSortBits;
+constexpr int64_t kSortMax = 1 << 20;
+
+struct SortJob {
+  const int32_t *key, *val;
+  int32_t *key_out, *val_out;
+  int32_t *count;  // [digits][tiles], then [digits] totals
+  int32_t n, tiles;
+};
+struct SortJobs {
+  SortJob j[2];
+};
+
+__global__ __launch_bounds__(256) void k_sort_count(SortJobs jobs, int shift, int digits) {
+  __shared__ int32_t cnt[kSortDigits];
+  const SortJob j = jobs.j[blockIdx.y];
+  const int32_t tile = (int32_t)blockIdx.x;
+  if (tile >= j.tiles) return;  // the whole workgroup
+  for (int d = threadIdx.x; d < digits; d += 256) cnt[d] = 0;
+  __syncthreads();
+  const int64_t i0 = (int64_t)tile * kSortTile;
+#pragma unroll
+  for (int t = 0; t < kSortTile / 256; ++t) {
+    const int64_t i = i0 + t * 256 + threadIdx.x;
+    if (i < j.n) atomicAdd(&cnt[((uint32_t)j.key[i] >> shift) & (uint32_t)(digits - 1)], 1);
+  }
+  __syncthreads();
+  for (int d = threadIdx.x; d < digits; d += 256) j.count[(int64_t)d * j.tiles + tile] = cnt[d];
+}
+
+// A wave per digit: its tiles' counts to the sums before them, and its total.
+__global__ __launch_bounds__(256) void k_sort_scan(SortJobs jobs, int digits) {
+  const SortJob j = jobs.j[blockIdx.y];
+  const int d = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (d >= digits) return;
+  int32_t *c = j.count + (int64_t)d * j.tiles;
+  int32_t run = 0;
+  for (int32_t t0 = 0; t0 < j.tiles; t0 += 64) {
+    const int32_t t = t0 + lane, v = t < j.tiles ? c[t] : 0;
+    int32_t x = v;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int32_t y = __shfl_up(x, o, 64);
+      if (lane >= o) x += y;
+    }
+    if (t < j.tiles) c[t] = run + x - v;
+    run += __shfl(x, 63, 64);
+  }
+  if (lane == 0) j.count[(int64_t)digits * j.tiles + d] = run;
+}
+
+__global__ __launch_bounds__(256) void k_sort_place(SortJobs jobs, int shift, int bits) {
+  __shared__ int32_t at[4][kSortDigits];  // per wave: its pairs of a digit, then where the next one goes
+  __shared__ int32_t wsum[4];
+  const SortJob j = jobs.j[blockIdx.y];
+  const int32_t tile = (int32_t)blockIdx.x;
+  if (tile >= j.tiles) return;  // the whole workgroup
+  const int digits = 1 << bits, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int kRounds = kSortTile / 256;
+  const int64_t i0 = (int64_t)tile * kSortTile + wave * (kSortTile / 4) + lane;
+  int32_t key[kRounds], val[kRounds];
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const bool in = i0 + r * 64 < j.n;
+    key[r] = in ? j.key[i0 + r * 64] : 0;
+    val[r] = in ? j.val[i0 + r * 64] : 0;
+  }
+  for (int d = threadIdx.x; d < kSortDigits; d += 256) at[0][d] = at[1][d] = at[2][d] = at[3][d] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r)
+    if (i0 + r * 64 < j.n) atomicAdd(&at[wave][((uint32_t)key[r] >> shift) & (uint32_t)(digits - 1)], 1);
+  // the digits' starts: a thread sums four digits' totals
+  int32_t tot[4], mine = 0;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int d = (int)threadIdx.x * 4 + t;
+    tot[t] = d < digits ? j.count[(int64_t)digits * j.tiles + d] : 0;
+    mine += tot[t];
+  }
+  int32_t x = mine;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int32_t y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) wsum[wave] = x;
+  __syncthreads();
+  int32_t start = x - mine;
+  for (int w = 0; w < wave; ++w) start += wsum[w];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int d = (int)threadIdx.x * 4 + t;
+    if (d < digits) {
+      int32_t b = start + j.count[(int64_t)d * j.tiles + tile];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const int32_t c = at[w][d];
+        at[w][d] = b;
+        b += c;
+      }
+    }
+    start += tot[t];
+  }
+  __syncthreads();
+  // a wave's rounds in turn: lanes of one digit take consecutive places in lane order
+  const uint64_t below = ((uint64_t)1 << lane) - 1;
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const bool in = i0 + r * 64 < j.n;
+    const uint32_t dg = ((uint32_t)key[r] >> shift) & (uint32_t)(digits - 1);
+    uint64_t same = __ballot(in);
+    for (int b = 0; b < bits; ++b) {
+      const bool bit = (dg >> b) & 1;
+      const uint64_t ones = __ballot(bit);
+      same &= bit ? ones : ~ones;
+    }
+    const int leader = in ? __ffsll((unsigned long long)same) - 1 : lane;
+    int32_t first = 0;
+    if (in && lane == leader) first = atomicAdd(&at[wave][dg], __popcll(same));
+    first = __shfl(first, leader, 64);
+    if (in) {
+      const int32_t to = first + __popcll(same & below);
+      j.key_out[to] = key[r];
+      j.val_out[to] = val[r];
+    }
+  }
+}
+
+// Sorts each job's (key, val) into (key_out, val_out); jobs with n = 0 are skipped.
+// Scratch in sc.p[slot], sc.p[slot + 1].
+hipError_t sort_pairs(Scratch &sc, int slot, const SortJob *job, int bits, hipStream_t s) {
+  hipError_t e;
+  SortJobs own{};
+  int n_own = 0;
+  size_t words = 0;
+  const int passes = (bits + kSortBits - 1) / kSortBits, per = (bits + passes - 1) / passes;
+  const int digits = 1 << per;
+  for (int q = 0; q < 2; ++q) {
+    if (job[q].n == 0) continue;
+    if (job[q].n > kSortMax) {
+      size_t tmp = 0;
+      if ((e = hipcub::DeviceRadixSort::SortPairs(nullptr, tmp, job[q].key, job[q].key_out, job[q].val,
+                                                  job[q].val_out, job[q].n, 0, bits, s)) != hipSuccess ||
+          (e = pool_alloc(&sc.p[slot + 1 + q], std::max<size_t>(tmp, 1))) != hipSuccess ||
+          (e = hipcub::DeviceRadixSort::SortPairs(sc.p[slot + 1 + q], tmp, job[q].key, job[q].key_out, job[q].val,
+                                                  job[q].val_out, job[q].n, 0, bits, s)) != hipSuccess)
+        return e;
+      continue;
+    }
+    SortJob &o = own.j[n_own++] = job[q];
+    o.tiles = (o.n + kSortTile - 1) / kSortTile;
+    words += (size_t)digits * (o.tiles + 1) + 2 * (size_t)o.n;
+  }
+  if (n_own == 0) return hipSuccess;
+  if ((e = pool_alloc(&sc.p[slot], sizeof(int32_t) * words)) != hipSuccess) return e;
+  int32_t *w = static_cast<int32_t *>(sc.p[slot]);
+  int32_t *other[2][2];  // the pairs that the passes write in turn with the outputs
+  int32_t tiles = 0;
+  for (int q = 0; q < n_own; ++q) {
+    SortJob &o = own.j[q];
+    o.count = w;
+    other[q][0] = w + (size_t)digits * (o.tiles + 1);
+    other[q][1] = other[q][0] + o.n;
+    w = other[q][1] + o.n;
+    tiles = std::max(tiles, o.tiles);
+  }
+  for (int p = 0; p < passes; ++p) {
+    SortJobs now = own;
+    for (int q = 0; q < n_own; ++q) {
+      SortJob &o = now.j[q];
+      if ((passes - 1 - p) % 2) {  // the last pass writes the outputs
+        o.key_out = other[q][0];
+        o.val_out = other[q][1];
+      }
+      own.j[q].key = o.key_out;  // the next pass reads them
+      own.j[q].val = o.val_out;
+    }
+    hipLaunchKernelGGL(k_sort_count, dim3((uint32_t)tiles, (uint32_t)n_own), dim3(256), 0, s, now, p * per, digits);
+    hipLaunchKernelGGL(k_sort_scan, dim3((uint32_t)((digits + 3) / 4), (uint32_t)n_own), dim3(256), 0, s, now, digits);
+    hipLaunchKernelGGL(k_sort_place, dim3((uint32_t)tiles, (uint32_t)n_own), dim3(256), 0, s, now, p * per, per);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace
@@ -650,16 +832,13 @@ hipError_t dev_split(const int32_t *rowptr, const int32_t *colidx, const float *
     hipLaunchKernelGGL(k_move_chunks, dim3((uint32_t)((n_chunks + 3) / 4)), dim3(256), 0, s, colidx, vals,
                        out->chunks, from, n_chunks, out->colidx, out->vals);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (by_mid && (e = sort_pairs(sc, 2, ckey, ckey2, cidx, out->corder, (int)n_chunks, bits, s)) != hipSuccess)
-      return e;
   }
-  if (by_last) {
+  if (by_last)
     hipLaunchKernelGGL(k_last_col_keys, dim3(grid_for(n_light)), dim3(256), 0, s, rowptr, colidx, k, lraw, n_light,
                        lkey);
-    if ((e = hipGetLastError()) != hipSuccess ||
-        (e = sort_pairs(sc, 3, lkey, lkey2, lraw, out->light, (int)n_light, bits, s)) != hipSuccess)
-      return e;
-  }
+  const SortJob jobs[2] = {{ckey, cidx, ckey2, out->corder, nullptr, by_mid ? (int32_t)n_chunks : 0, 0},
+                           {lkey, lraw, lkey2, out->light, nullptr, by_last ? (int32_t)n_light : 0, 0}};
+  if ((e = hipGetLastError()) != hipSuccess || (e = sort_pairs(sc, 5, jobs, bits, s)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_light_lengths, dim3(grid_for(n_light + 1)), dim3(256), 0, s, rowptr, out->light, n_light, lkey);
   size_t tmp = 0;
   if ((e = hipGetLastError()) != hipSuccess ||

@@ -230,3 +230,30 @@ def test_block_conversion_windows(fam, k):
             assert sd.sd_plan_export(host, what).tobytes() == sd.sd_plan_export(dev, what).tobytes(), what
         B = gen.dense_uniform(k, 8, seed=1)
         assert run(sd, host, B, A.m).tobytes() == run(sd, dev, B, A.m).tobytes()  # the zero block as well
+
+
+@pytest.mark.parametrize("m, k", [(2, 1), (4095, 5), (4096, 1023), (4097, 1024), (12293, 1 << 20), (70001, 1 << 28),
+                                  (1 << 20, 3000), ((1 << 20) + 1, 3000)])
+def test_split_order_sort(m, k):
+    """The device's orders of light rows and chunks equal the host's: tiles full and
+    not, one to three digit passes, many equal columns, the longest list sorted here
+    and one more."""
+    lens = np.full(m, 1, np.int32)
+    lens[::7] = 0
+    if k > 40:
+        lens[::max(1, m // 5000)] = 33  # heavy from 8: five chunks of at most 8
+    A = gen.random_rows(m, k, lens, seed=m % 1000)
+    if k >= 1 << 20:  # columns that repeat, over the whole range
+        one = lens[np.repeat(np.arange(m), lens)] == 1
+        A.colidx[one] = (A.colidx[one] // (k // 97)) * (k // 97) + 5
+    print(f"case split order sort m={m} k={k}", flush=True)
+    opts = dict(force="csr_split", heavy_threshold=8, chunk_nnz=8, light_order="last_col", chunk_order="mid_col")
+    with sd.sd_plan_ex(A, 8, **opts) as host, \
+            sd.sd_plan_device(*_device_csr(A), A.m, A.k, A.nnz, 8, **opts) as dev:
+        assert dev.info["device_built"] == 1
+        for what in range(1, 21):
+            try:
+                a = sd.sd_plan_export(host, what)
+            except sd.SparseDittoError:
+                continue
+            assert a.tobytes() == sd.sd_plan_export(dev, what).tobytes(), what
