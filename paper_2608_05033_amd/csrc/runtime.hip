@@ -467,9 +467,7 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
     sd::row_batch_for(stats, I.family == SD_FMT_CSR_ROW ? A.m : I.n_light, geo.G, I.cu_count, o.rows_per_group,
                       o.gather_unroll, &I.rows_per_group, &I.gather_unroll);
     // narrow widths: lane groups that share a row
-    // (what is accepted is counted in lanes of one column where n % 4 != 0)
-    const int32_t Gs = sd::geometry_for(n, n % 4 == 0, col_tile).G;
-    if (o.row_slices > 1 && (Gs > 8 || Gs * o.row_slices > 64)) return SD_ERR_UNSUPPORTED;
+    if (o.row_slices > 1 && (geo.G > 8 || geo.G * o.row_slices > 64)) return SD_ERR_UNSUPPORTED;
     I.row_slices = o.row_slices > 0 ? o.row_slices : sd::slices_for(stats, I.family, n, geo.G);
     if (I.row_slices > 1) {
       I.rows_per_group = 1;
@@ -1343,8 +1341,8 @@ int search_plan(const sd_csr_t *A, int32_t n, const sd_plan_opts_t &o, sd_plan_t
   if (stats.row_max >= 64) add(SD_FMT_CSR_SPLIT, 64, 64, 0, 0);
   add_orders(SD_FMT_CSR_MERGE, 0);
   // narrow widths: rows shared by S lane groups (G lanes cover the width)
-  const int32_t G = best->info.col_tile / (n % 4 == 0 ? 4 : 1);
-  if (G >= 1 && G <= 8 && stats.nnz > 0) {
+  const int32_t G = sd::geometry_for(n, n >= 4, best->col_tile_req).G;
+  if (G <= 8 && stats.nnz > 0) {
     for (int32_t S = 1; S <= 64 / G; S *= 2) {
       add(SD_FMT_CSR_ROW, 0, 0, 0, 0, 0, S);
       if (stats.row_max >= 512) add(SD_FMT_CSR_SPLIT, 512, 2048, 0, 0, 0, S);

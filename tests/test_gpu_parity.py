@@ -426,6 +426,30 @@ def test_measured_plan_search(mname):
     sd.sd_plan_cache_clear()
 
 
+def assert_same_plan(again: dict, first: dict):
+    """What the cache rebuilt is what the search timed.  `reach` is computed under
+    the default workgroup order only, and a recorded order is explicit."""
+    skip = ("search_cache_hit", "search_candidates", "search_best_ms", "search_rule_ms", "reach")
+    assert {f: v for f, v in again.items() if f not in skip} == {f: v for f, v in first.items() if f not in skip}
+
+
+@pytest.mark.parametrize("mname", ["rmat", "laplace"])
+@pytest.mark.parametrize("n", [5, 9, 17, 31])
+def test_search_cache_hit_at_odd_widths(mname, n):
+    """A choice recorded at a width of no whole 4 columns (rows shared by lane
+    groups there) is accepted and rebuilt."""
+    A = matrix(mname)
+    B = gen.dense_normal(A.k, n, seed=n)
+    sd.sd_plan_cache_clear()
+    try:
+        with sd.sd_plan_ex(A, n, search=True) as first, sd.sd_plan_ex(A, n, search=True) as again:
+            assert again.info["search_cache_hit"] == 1
+            assert_same_plan(again.info, first.info)
+            assert run(sd, again, B, A.m).tobytes() == run(sd, first, B, A.m).tobytes()
+    finally:
+        sd.sd_plan_cache_clear()
+
+
 def test_search_choice_saved_and_loaded(tmp_path):
     """A measured choice written to a cache file and loaded into an empty
     cache (as a new process would) is reused without timing: same plan, same

@@ -332,8 +332,8 @@ def test_block_engine_choice():
 
 
 def _lanes(n):
-    """Lanes per row covering a width of n floats (128-bit accesses when n % 4 == 0)."""
-    lanes = -(-n // 4) if n % 4 == 0 else n
+    """Lanes per row covering a width of n floats (four columns per lane from n = 4 on)."""
+    lanes = -(-n // 4) if n >= 4 else n
     g = 1
     while g < lanes and g < 64:
         g *= 2
@@ -357,6 +357,22 @@ def test_row_slices_option(fam, n, S):
         assert p.info["lanes_per_row"] == G * S
         if S > 1:
             assert p.info["rows_per_group"] == 1
+
+
+@pytest.mark.parametrize("fam", ["csr_row", "csr_split"])
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 9, 10, 13, 17, 30, 31, 32, 33, 64])
+def test_planned_values_are_accepted_as_options(fam, n):
+    """A plan's own slice count and split sizes, passed back as options (as the
+    search's recorded choices are), give the same plan at every width."""
+    A = MATS["rmat"]()
+    with sd.sd_plan_ex(A, n, force=fam, placement=HOST) as p:
+        first = dict(p.info)
+    back = dict(row_slices=first["row_slices"])
+    if fam == "csr_split":
+        assert first["row_slices"] > 1 or n > 32
+        back.update(heavy_threshold=first["heavy_threshold"], chunk_nnz=first["chunk_nnz"])
+    with sd.sd_plan_ex(A, n, force=fam, placement=HOST, **back) as p:
+        assert p.info == first
 
 
 def test_row_slices_invalid_and_other_families():
