@@ -369,7 +369,9 @@ typedef struct {
   int32_t row_slices;      /* CSR_ROW / CSR_SPLIT: lane groups sharing a row (1 = none) */
   int32_t light_order;     /* CSR_SPLIT: light-row order used (1 ascending, 2 by last column) */
   int32_t chunk_order;     /* CSR_SPLIT: chunk order used (1 chunk list, 2 by middle column) */
-  int32_t reserved[1];
+  int32_t stream_rows;     /* CSR_ROW / light rows of CSR_SPLIT: rows per lane group that a
+                              workgroup's lane groups take as they become free (0 = the rows
+                              of a wave run together).  Under wg_order 0 only for CSR_ROW */
   int64_t hot_columns;     /* tiered policy: columns whose B rows are gathered with normal loads */
   int64_t hot_nnz;         /* nonzeros in those columns */
   int64_t ell_width;       /* ELL: slots per row (= longest row) */

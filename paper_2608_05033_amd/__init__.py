@@ -108,7 +108,7 @@ _INFO_FIELDS = [
     ("block_threads", _i32), ("max_threads", _i32), ("regs_per_thread", _i32), ("lds_bytes", _i32),
     ("max_lds_bytes", _i32), ("legal", _i32), ("rows_per_group", _i32), ("lanes_per_row", _i32),
     ("gather_unroll", _i32), ("cache_policy", _i32), ("row_slices", _i32), ("light_order", _i32),
-    ("chunk_order", _i32), ("reserved", _i32 * 1),
+    ("chunk_order", _i32), ("stream_rows", _i32),
     ("hot_columns", _i64), ("hot_nnz", _i64), ("ell_width", _i64),
     ("search_candidates", _i32), ("search_cache_hit", _i32), ("search_best_ms", _dbl), ("search_rule_ms", _dbl),
     ("col_tile", _i32), ("col_passes", _i32), ("window_rows", _i32), ("window_max", _i32),

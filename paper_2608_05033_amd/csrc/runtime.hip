@@ -498,11 +498,11 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
   if ((I.family == SD_FMT_CSR_ROW || I.family == SD_FMT_CSR_SPLIT) && o.rows_per_group == 0 && I.rows_per_group == 1 &&
       o.gather_unroll == 0 && I.gather_unroll == 8 && I.row_slices == 1) {
     if (I.family == SD_FMT_CSR_SPLIT) {
-      p->stream = sd::stream_for(I.family, I.n_light, 0.0, geo.G, 0, 0, b_bytes);
+      I.stream_rows = sd::stream_for(I.family, I.n_light, 0.0, geo.G, 0, 0, b_bytes);
     } else if (o.wg_order == 0 && I.wg_order != 3) {
-      p->stream = sd::stream_for(I.family, A.m, stats.row_mean, geo.G, 2 * I.reach,
+      I.stream_rows = sd::stream_for(I.family, A.m, stats.row_mean, geo.G, 2 * I.reach,
                                  4 * std::min<int64_t>(n, (int64_t)geo.G * geo.VW), b_bytes);
-      if (p->stream > 0) I.wg_order = 1;
+      if (I.stream_rows > 0) I.wg_order = 1;
     }
   }
 
@@ -536,7 +536,7 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
   hipFuncAttributes attr;
   std::memset(&attr, 0, sizeof(attr));
   hipError_t e =
-      sd::kernel_attributes(I.family, I.engine, n, vec4, I.rows_per_group, I.gather_unroll, I.row_slices, p->stream,
+      sd::kernel_attributes(I.family, I.engine, n, vec4, I.rows_per_group, I.gather_unroll, I.row_slices, I.stream_rows,
                             col_tile,
                             (int32_t)I.ell_width, (int32_t)I.block_rows, &attr);
   if (e != hipSuccess) return hip_fail(e);
@@ -891,13 +891,13 @@ int sd_spmm(sd_plan_t p, const float *B, float *C, void *stream) {
   hipError_t e = hipSuccess;
   switch (I.family) {
     case SD_FMT_CSR_ROW:
-      e = sd::launch_csr_rows(A, io, I.rows_per_group, I.gather_unroll, I.row_slices, p->stream, s);
+      e = sd::launch_csr_rows(A, io, I.rows_per_group, I.gather_unroll, I.row_slices, I.stream_rows, s);
       break;
     case SD_FMT_CSR_SPLIT:
       e = sd::launch_csr_split(A, p->d_light, (int32_t)I.n_light, p->d_chunks, p->d_corder, (int32_t)I.n_chunks,
                                p->d_heavy_rows,
                                p->d_heavy_ptr, (int32_t)I.n_heavy, p->d_ws, io, I.rows_per_group,
-                               I.gather_unroll, I.row_slices, p->stream, s);
+                               I.gather_unroll, I.row_slices, I.stream_rows, s);
       break;
     case SD_FMT_CSR_MERGE:
       e = sd::launch_csr_merge(A, p->d_coords, (int32_t)I.units, p->d_carry_row, p->d_ws, io, s);
@@ -1315,10 +1315,12 @@ int search_plan(const sd_csr_t *A, int32_t n, const sd_plan_opts_t &o, sd_plan_t
     q.wg_order = order;
     q.wg_chunk = chunk;
     q.row_slices = slices;
+    // an explicit order makes CSR_ROW a plan of its own where the default one streams
+    const bool default_only = fam == SD_FMT_CSR_ROW && best->info.stream_rows > 0;
     if (fam == best->info.family && (fam != SD_FMT_CSR_SPLIT || (T == best->info.heavy_threshold &&
                                                               c == best->info.chunk_nnz)) &&
         (engine == 0 || engine == best->info.engine) &&
-        (order == 0 || (order == best->info.wg_order && (order != 3 || chunk == best->info.wg_chunk))) &&
+        (order == 0 || (!default_only && order == best->info.wg_order && (order != 3 || chunk == best->info.wg_chunk))) &&
         (slices == 0 || slices == best->info.row_slices))
       return;  // the reference itself
     cands.push_back(q);
@@ -1394,7 +1396,9 @@ int search_plan(const sd_csr_t *A, int32_t n, const sd_plan_opts_t &o, sd_plan_t
   chosen.heavy_threshold = (int32_t)best->info.heavy_threshold;
   chosen.chunk_nnz = (int32_t)best->info.chunk_nnz;
   chosen.units = (int32_t)best->info.units;
-  chosen.wg_order = best->info.wg_order;
+  // CSR_ROW streams its rows under the default order only, so that is what is recorded
+  const bool streamed_rows = best->info.family == SD_FMT_CSR_ROW && best->info.stream_rows > 0;
+  chosen.wg_order = streamed_rows ? 0 : best->info.wg_order;
   chosen.wg_chunk = best->info.wg_chunk;
   chosen.sell_sigma = best->info.sell_sigma;
   chosen.window_rows = best->info.window_rows;

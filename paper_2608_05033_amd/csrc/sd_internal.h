@@ -168,7 +168,6 @@ struct sd_plan_s {
   sd_plan_info_t info{};
   int32_t device = -1;  // -1: host only
   int32_t col_tile_req = 0;  // requested dense columns per lane group (0: whole width)
-  int32_t stream = 0;  // CSR_ROW / light rows of CSR_SPLIT: rows streamed per lane group (0: batched by the wave)
 
   // host arrays
   std::vector<int32_t> h_rowptr, h_colidx, h_coltag, h_light, h_chunks, h_corder, h_heavy_rows, h_heavy_ptr, h_coords,

@@ -450,6 +450,46 @@ def test_search_cache_hit_at_odd_widths(mname, n):
         sd.sd_plan_cache_clear()
 
 
+def test_search_keeps_streamed_rows(tmp_path):
+    """Ragged rows around a narrow band: the rule streams them, the same rows
+    unstreamed in the same workgroup order are another candidate, and the recorded
+    choice rebuilds the plan that was timed."""
+    rng = np.random.default_rng(3)
+    m, n, band = 200003, 64, 820
+    lens = rng.integers(8, 41, m)
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rows = np.repeat(np.arange(m), lens)
+    step = band // lens[rows]
+    cols = np.clip(rows - band // 2, 0, m - band) + (np.arange(rows.size) - rowptr[rows]) * step
+    cols += rng.integers(0, 1 << 30, rows.size) % step
+    A = gen.CSR(m, m, rowptr, cols.astype(np.int32), rng.uniform(-1, 1, rows.size).astype(np.float32))
+    dev = [torch.from_numpy(x).cuda() for x in (A.rowptr, A.colidx, A.values)]
+    opts = dict(force="csr_row")
+    with sd.sd_plan_device(*dev, m, m, A.nnz, n, **opts) as rule, \
+            sd.sd_plan_device(*dev, m, m, A.nnz, n, wg_order=1, **opts) as plain:
+        assert rule.info["stream_rows"] > 0 and rule.info["wg_order"] == 1
+        assert plain.info["stream_rows"] == 0 and plain.info["wg_order"] == 1
+    with sd.sd_plan_device(*dev, m, m, A.nnz, n) as rule:
+        assert rule.family == "csr_row" and rule.info["stream_rows"] > 0
+    sd.sd_plan_cache_clear()
+    try:
+        with sd.sd_plan_device(*dev, m, m, A.nnz, n, search=True) as first:
+            info = dict(first.info)
+        print(f"search chose {first.family} stream_rows={info['stream_rows']}", flush=True)
+        path = tmp_path / "choices.bin"
+        sd.sd_plan_cache_save(path)
+        with sd.sd_plan_device(*dev, m, m, A.nnz, n, search=True) as again:
+            assert again.info["search_cache_hit"] == 1
+            assert_same_plan(again.info, info)
+        sd.sd_plan_cache_clear()
+        sd.sd_plan_cache_load(path)
+        with sd.sd_plan_device(*dev, m, m, A.nnz, n, search=True) as loaded:
+            assert loaded.info["search_cache_hit"] == 1
+            assert_same_plan(loaded.info, info)
+    finally:
+        sd.sd_plan_cache_clear()
+
+
 def test_search_choice_saved_and_loaded(tmp_path):
     """A measured choice written to a cache file and loaded into an empty
     cache (as a new process would) is reused without timing: same plan, same
