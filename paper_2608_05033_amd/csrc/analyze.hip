@@ -314,22 +314,24 @@ __global__ __launch_bounds__(256) void k_an_strips(const int32_t *__restrict__ r
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    int32_t fresh_here = 0, next = p0 + lane < p1 ? colidx[p0 + lane] : 0, last = 0;
-    for (int32_t q = p0; q < p1; q += 64) {  // wave-uniform
-      const int32_t p = q + lane;
-      const bool in = p < p1;
+    // positions are unsigned: those past a strip that ends near entry 2^31 pass INT32_MAX
+    const uint32_t end = (uint32_t)p1;
+    int32_t fresh_here = 0, next = lane < E ? colidx[p0 + lane] : 0, last = 0;
+    for (uint32_t q = (uint32_t)p0; q < end; q += 64) {  // wave-uniform
+      const uint32_t p = q + lane;
+      const bool in = p < end;
       const int32_t c = next;
-      if (p1 - p > 64) next = colidx[p + 64];  // behind this turn's work
+      if (p + 64 < end) next = colidx[p + 64];  // behind this turn's work
       if constexpr (LB == 4) {
         int32_t prev = __shfl_up(c, 1, 64);
         if (lane == 0) prev = last;
         last = __shfl(c, 63, 64);
         int r = 0;  // the last row starting at or before p
 #pragma unroll
-        for (int st = B / 2; st >= 1; st >>= 1) r += __shfl(rp, r + st, 64) <= p ? st : 0;
+        for (int st = B / 2; st >= 1; st >>= 1) r += (uint32_t)__shfl(rp, r + st, 64) <= p ? st : 0;
         const int32_t rs = __shfl(rp, r, 64);
         if (in) {
-          sum.bad |= entry_bad(p, rs, c, prev, k);
+          sum.bad |= entry_bad((int32_t)p, rs, c, prev, k);
           sum.diag += c == s * B + r;
         }
       }
@@ -473,7 +475,8 @@ __global__ __launch_bounds__(1024) void k_an_strips_big(const int32_t *__restric
     __syncthreads();
     const int32_t total = before[B];
     if (total == 0) continue;  // workgroup-uniform
-    for (int32_t i = threadIdx.x; i < total; i += 1024) {
+    for (int64_t ii = threadIdx.x; ii < total; ii += 1024) {  // rows in no order: up to all entries
+      const int32_t i = (int32_t)ii;
       int r = 0;
 #pragma unroll
       for (int st = B / 2; st >= 1; st >>= 1) r += before[r + st] <= i ? st : 0;

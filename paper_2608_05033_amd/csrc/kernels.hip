@@ -705,16 +705,16 @@ __global__ __launch_bounds__(256) void k_csr_merge(const int32_t *__restrict__ r
   }
   // the piece ends row i0, which began in an earlier piece
   bool head = i0 < i1 && j0 > rowptr[i0];
-  // ends of rows [rb, rb + T); rows from i1 on do not end in this piece.  Positions
-  // are unsigned: the last tile of a stream of almost 2^31 entries ends past INT32_MAX.
+  // ends of rows [rb, rb + T); rows from i1 on do not end in this piece.  Positions and
+  // rows are unsigned: the last tile of almost 2^31 of either ends past INT32_MAX.
   constexpr uint32_t kNoEnd = UINT32_MAX;
   int32_t i = i0, rb = i0;
   uint32_t rend[EPL];
   auto load_ends = [&]() {
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {
-      const int32_t r = rb + e * G + glane;
-      rend[e] = r < i1 ? (uint32_t)rowptr[r + 1] : kNoEnd;
+      const uint32_t r = (uint32_t)rb + e * G + glane;
+      rend[e] = r < (uint32_t)i1 ? (uint32_t)rowptr[r + 1] : kNoEnd;
     }
   };
   auto end_of = [&](int32_t r) {  // group-uniform r in [rb, rb + T)

@@ -257,3 +257,47 @@ def test_split_order_sort(m, k):
             except sd.SparseDittoError:
                 continue
             assert a.tobytes() == sd.sd_plan_export(dev, what).tobytes(), what
+
+
+def test_analysis_of_the_most_entries():
+    """2^31 - 1 entries: a short strip that ends at the last of them is checked and
+    counted like any other, and a column out of range in it is found."""
+    k, full = 65536, 32768
+    lens = torch.full((full + 16,), k, dtype=torch.int64)
+    lens[full - 1] = k - 201
+    lens[full:full + 8], lens[full + 8:] = 13, 12
+    rowptr = torch.cat([torch.zeros(1, dtype=torch.int64), torch.cumsum(lens, 0)])
+    nnz = int(rowptr[-1])
+    assert nnz == 2 ** 31 - 1
+    cols = torch.arange(nnz, dtype=torch.int32, device="cuda").remainder_(k)
+    cols[nnz - 200:] = torch.cat([torch.arange(int(n)) * 5000 for n in lens[full:]]).int().cuda()
+    vals = torch.ones(nnz, device="cuda")
+    rp = rowptr.int().cuda()
+    print("case analysis of 2^31 - 1 entries", flush=True)
+    st = sd.sd_analyze_device(rp, cols, vals, full + 16, k, nnz)
+    assert st["nnz"] == nnz and st["row_max"] == k and st["row_min"] == 12 and st["row_q50"] == k
+    assert st["nnzb16"] == (full // 16) * (k // 16) + 13
+    assert st["nnzb8"] == (full // 8) * (k // 8) + 13 + 12
+    assert st["nnzb4"] == (full // 4) * (k // 4) + 2 * 13 + 2 * 12
+    assert st["bell16_width"] == k // 16 and st["diag_nnz"] == full and st["col_deg_max"] == full + 16
+    cols[nnz - 1] = k
+    with pytest.raises(sd.SparseDittoError) as e:
+        sd.sd_analyze_device(rp, cols, vals, full + 16, k, nnz)
+    assert e.value.status == sd.SD_ERR_INVALID_CSR
+
+
+def test_merge_path_of_the_most_rows():
+    """2^31 - 1 rows, nearly all empty: the last piece's tile of row ends passes the
+    largest row number."""
+    m, n = 2 ** 31 - 1, 1
+    rp = torch.full((m + 1,), 2, dtype=torch.int32, device="cuda")
+    rp[0], rp[1:6], rp[m] = 0, 1, 3  # one entry in rows 0, 5 and m - 1
+    cols = torch.tensor([1, 0, 2], dtype=torch.int32, device="cuda")
+    vals = torch.tensor([2.0, 3.0, 5.0], device="cuda")
+    B = torch.tensor([[7.0], [11.0], [13.0]], device="cuda")
+    C = torch.full((m, n), -7.0, device="cuda")
+    print("case merge path of 2^31 - 1 rows", flush=True)
+    sd.sd_spmm_merge_noalloc(rp, cols, vals, m, 3, 3, n, B, C)
+    torch.cuda.synchronize()
+    assert [float(C[r, 0]) for r in (0, 5, m - 1)] == [22.0, 21.0, 65.0]
+    assert int(torch.count_nonzero(C)) == 3
