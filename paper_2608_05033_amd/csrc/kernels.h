@@ -34,6 +34,7 @@ struct DenseIO {
 // per lane, coltiles column tiles of G*VW columns.
 struct Geometry {
   int32_t G, VW, coltiles;
+  bool odd;  // n is no multiple of VW
 };
 Geometry geometry_for(int32_t n, int32_t vec4, int32_t col_tile = 0);
 

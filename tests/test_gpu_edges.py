@@ -301,3 +301,19 @@ def test_merge_path_of_the_most_rows():
     torch.cuda.synchronize()
     assert [float(C[r, 0]) for r in (0, 5, m - 1)] == [22.0, 21.0, 65.0]
     assert int(torch.count_nonzero(C)) == 3
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 12, 31])
+def test_split_stores_of_small_and_large_outputs(n):
+    """Light rows of the narrow split below and above the size of C from which they
+    are stored past L2 (2 MiB), whole widths and odd ones."""
+    m, k = 60013, 4000
+    lens = np.random.default_rng(n).integers(0, 9, m)
+    lens[::3001] = 900
+    A = gen.random_rows(m, k, lens.astype(np.int32), seed=n)
+    B = gen.dense_uniform(k, n, seed=n)
+    C64, S = oracle.spmm(A, B)
+    print(f"case split stores n={n}", flush=True)
+    with sd.sd_plan_ex(A, n, force="csr_split") as plan:
+        assert plan.info["n_light"] > 59000 and plan.info["n_heavy"] > 10
+        assert_close(run(sd, plan, B, m), C64, S, f"split stores n={n}")
