@@ -693,10 +693,17 @@ __global__ __launch_bounds__(256) void k_split_slices(const int32_t *__restrict_
 // The piece's nonzeros are one contiguous stream, so they are taken in tiles
 // and in batches of 8 gathers whatever rows they belong to (the next tile is
 // loaded behind the current gathers), and a row is closed when the running
-// position reaches its end.  The row ends come from a tile held across the
-// group's lanes: closing a row waits on a lane permute, not on memory.  Walking
-// row by row instead left each short row its own bounds -> entries -> gathers
-// chain.
+// position reaches its end.  Walking row by row instead left each short row its
+// own bounds -> entries -> gathers chain.
+//
+// The lane groups of a wave close their rows at different places of a batch, so a
+// close may run up to 8 times a batch, each time for a few lanes: it waits on
+// nothing.  The next row's end is at hand, the one after it requested from a tile
+// held across the group's lanes, the next tile loaded ahead.  A close that fetched
+// the end it needs made rows of equal length slower than walking them row by row
+// (us, row by row / fetched / at hand, 60,000 rows of 12, N = 8, 16, 32: 27.1 / 35.6 /
+// 30.1, 27.9 / 36.2 / 31.2, 27.2 / 35.5 / 28.1; R-MAT 100 k vertices, 2 M edges, N = 64:
+// 139 / 70 / 57).  Two batches in flight on top cost 0 to 8 %.
 template <int G, int VW, bool ODD>
 __global__ __launch_bounds__(256) void k_csr_merge(const int32_t *__restrict__ rowptr,
                                                    const int32_t *__restrict__ colidx,
@@ -724,43 +731,47 @@ __global__ __launch_bounds__(256) void k_csr_merge(const int32_t *__restrict__ r
     j1 = coords[2 * u + 3];
   }
   // the piece ends row i0, which began in an earlier piece
-  bool head = i0 < i1 && j0 > rowptr[i0];
-  // ends of rows [rb, rb + T); rows from i1 on do not end in this piece.  Positions and
-  // rows are unsigned: the last tile of almost 2^31 of either ends past INT32_MAX.
+  const bool head = i0 < i1 && j0 > rowptr[i0];
+  // Ends of the rows from i0 on, a tile of T held across the group's lanes and the next
+  // one loaded ahead; rows from i1 on do not end in this piece.  Positions and rows are
+  // unsigned: the last tile of almost 2^31 of either ends past INT32_MAX.
   constexpr uint32_t kNoEnd = UINT32_MAX;
-  int32_t i = i0, rb = i0;
-  uint32_t rend[EPL];
-  auto load_ends = [&]() {
+  uint32_t ends[EPL], ends2[EPL], ahead = (uint32_t)i0 + T;
+  auto load_ends = [&](uint32_t first, uint32_t(&x)[EPL]) {
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {
-      const uint32_t r = (uint32_t)rb + e * G + glane;
-      rend[e] = r < (uint32_t)i1 ? (uint32_t)rowptr[r + 1] : kNoEnd;
+      const uint32_t r = first + e * G + glane;
+      x[e] = r < (uint32_t)i1 ? (uint32_t)rowptr[r + 1] : kNoEnd;
     }
   };
-  auto end_of = [&](int32_t r) {  // group-uniform r in [rb, rb + T)
-    uint32_t v = rend[0];
+  auto end_at = [&](int k) {  // group-uniform k in [0, T)
+    uint32_t v = ends[0];
 #pragma unroll
-    for (int e = 1; e < EPL; ++e) v = (r - rb) / G == e ? rend[e] : v;
-    return G == 1 ? v : __shfl(v, gbase + ((r - rb) & (G - 1)), 64);
+    for (int e = 1; e < EPL; ++e) v = k / G == e ? ends[e] : v;
+    return G == 1 ? v : __shfl(v, gbase + (k & (G - 1)), 64);
   };
   V acc = (V)(0.0f);
-  load_ends();
-  uint32_t end = end_of(i);
+  load_ends((uint32_t)i0, ends);
+  load_ends(ahead, ends2);
+  // the row at hand ends at end, the one after it (place k of the tile) at next: closing a
+  // row waits on neither memory nor a lane permute
+  int k = 1;
+  uint32_t end = end_at(0), next = end_at(1);
+  float *dst = head ? part + ((int64_t)units + u) * n : C + (int64_t)i0 * n, *crow = C + ((int64_t)i0 + 1) * n;
   auto close_row = [&]() {
-    if (col_ok) {
-      if (head)
-        store_cols<VW, ODD, false>(part + ((int64_t)units + u) * n, col, n, acc);
-      else
-        store_cols<VW, ODD, true>(C + (int64_t)i * n, col, n, acc);
-    }
+    if (col_ok) store_cols<VW, ODD, true>(dst, col, n, acc);
+    dst = crow;
+    crow += n;
     acc = (V)(0.0f);
-    head = false;
-    ++i;
-    if (i - rb == T) {
-      rb = i;
-      load_ends();
+    end = next;
+    if (++k == T) {
+      k = 0;
+      ahead += T;
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) ends[e] = ends2[e];
+      load_ends(ahead, ends2);
     }
-    end = end_of(i);
+    next = end_at(k);
   };
   const uint32_t pe = (uint32_t)j1;
   while (end == (uint32_t)j0) close_row();
@@ -823,7 +834,7 @@ __global__ __launch_bounds__(256) void k_csr_merge(const int32_t *__restrict__ r
     const bool has = i1 < m && j1 > max(j0, rowptr[i1]);
     if (glane == 0 && blockIdx.y == 0) {
       rows[u] = has ? i1 : -1;
-      rows[units + u] = i0 < i1 && j0 > rowptr[i0] ? i0 : -1;
+      rows[units + u] = head ? i0 : -1;
     }
     if (has && col_ok) store_cols<VW, ODD, false>(part + u * n, col, n, acc);
   }
