@@ -17,6 +17,7 @@ struct CsrOperand {
   const float *vals;
   int32_t m;  // rows of the operand (= rows of C)
   int32_t k;  // columns of the operand (= rows of B)
+  int64_t nnz;
 };
 
 struct DenseIO {
@@ -54,6 +55,8 @@ hipError_t launch_csr_split(const CsrOperand &A, const int32_t *light, int32_t n
 // rows); part: 2 units n floats (carry partials, then head partials).
 hipError_t launch_csr_merge(const CsrOperand &A, const int32_t *coords, int32_t units, int32_t *rows,
                             float *part, const DenseIO &io, hipStream_t s);
+// LDS per workgroup of the merge path, taken to bound its workgroups per CU (0: none).
+size_t merge_lds_bytes(const Geometry &geo, int32_t m, int64_t nnz, int32_t n);
 
 // Block formats: bptr == nullptr selects Blocked-ELL with `width` slots per
 // block-row.  engine: 1 MFMA (any width, in column tiles of one size, the last

@@ -704,7 +704,10 @@ __global__ __launch_bounds__(256) void k_split_slices(const int32_t *__restrict_
 // (us, row by row / fetched / at hand, 60,000 rows of 12, N = 8, 16, 32: 27.1 / 35.6 /
 // 30.1, 27.9 / 36.2 / 31.2, 27.2 / 35.5 / 28.1; R-MAT 100 k vertices, 2 M edges, N = 64:
 // 139 / 70 / 57).  Two batches in flight on top cost 0 to 8 %.
-template <int G, int VW, bool ODD>
+//
+// LONG (G = 64: one piece per wave): batches in which no row ends go without the
+// test for a row's end behind every entry.
+template <int G, int VW, bool ODD, bool LONG>
 __global__ __launch_bounds__(256) void k_csr_merge(const int32_t *__restrict__ rowptr,
                                                    const int32_t *__restrict__ colidx,
                                                    const float *__restrict__ vals,
@@ -811,6 +814,16 @@ __global__ __launch_bounds__(256) void k_csr_merge(const int32_t *__restrict__ r
         }
       }
       __builtin_amdgcn_sched_barrier(0);  // broadcasts first, then the gathers back to back
+      if (LONG && __all(p + t0 + 8 <= pe && end >= p + t0 + 8)) {  // 8 entries of the row at hand
+        if (col_ok) {
+#pragma unroll
+          for (int q = 0; q < 8; ++q) bv[q] = gather_b<VW>(Bl, ct[q], n, policy);
+#pragma unroll
+          for (int q = 0; q < 8; ++q) acc += av[q] * bv[q];
+        }
+        while (end == p + t0 + 8) close_row();
+        continue;
+      }
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
         bv[q] = (V)(0.0f);
@@ -1622,6 +1635,27 @@ hipError_t launch_csr_split(const CsrOperand &A, const int32_t *light, int32_t n
   });
 }
 
+// Long rows, where a merge-path piece takes a whole wave (n > 128).  Batches without
+// a row's end are told apart from 32 nonzeros a row on (us, not / so, rows around a
+// band: 2,500 rows of 54, N = 180: 20.0 / 17.9; 9,000 of 130, N = 180: 72.2 / 63.0).
+bool merge_long_rows(const Geometry &geo, int32_t m, int64_t nnz) { return geo.G == 64 && nnz >= 32 * (int64_t)m; }
+
+// From 0.9 GB of gathered B rows on, LDS keeps such rows to two workgroups per CU: the
+// pieces at work then lie in a quarter of the matrix, whose B rows L2 holds better (with
+// the above, us: 18,000 rows of 54, N = 256: 120 / 97; 30,000 of 54, N = 180: 137 / 119;
+// 60,000 of 130, N = 180: 712 / 575; 18,000 of 54, N = 180, 0.7 GB, loses: all that fit
+// 1.21, two 1.03 times the speed of walking row by row).  So do odd widths that use
+// every lane, whose rows of B straddle more lines than their neighbours' (n = 31, 63: 60,000
+// rows of 130 1.00 / 1.45 and 0.72 / 0.89, 300,000 of 24 0.86 / 1.00 and 0.90 / 0.99 times
+// that speed; n = 47 1.30 / 0.96).  R-MAT graphs lose (100 k vertices, 21 a row, N = 180:
+// 1.85 / 1.49); they have fewer nonzeros a row, and only m and nnz are known here.
+size_t merge_lds_bytes(const Geometry &geo, int32_t m, int64_t nnz, int32_t n) {
+  const double gathered = 4.0 * (double)nnz * n;
+  if (merge_long_rows(geo, m, nnz)) return gathered >= 0.9e9 ? 65536 : 0;
+  const bool last_lane_odd = geo.odd && geo.coltiles == 1 && n > (geo.G - 1) * geo.VW;
+  return last_lane_odd && nnz >= 24 * (int64_t)m && gathered >= 0.7e9 ? 65536 : 0;
+}
+
 hipError_t launch_csr_merge(const CsrOperand &A, const int32_t *coords, int32_t units, int32_t *rows,
                             float *part, const DenseIO &io, hipStream_t s) {
   const Geometry geo = geometry_for(io.n, io.vec4, io.col_tile);
@@ -1633,9 +1667,17 @@ hipError_t launch_csr_merge(const CsrOperand &A, const int32_t *coords, int32_t 
     // From 8 lanes a row on, whole widths run the odd ones' code: 1 to 5 % faster
     // (R-MAT 0.4 M vertices, 3.2 M edges, N = 32 and 96: 85 / 90, 200 / 232 us).
     constexpr bool ODD = odd || (VW == 4 && G >= 8);
-    hipLaunchKernelGGL((k_csr_merge<G, VW, ODD>), dim3(nb, geo.coltiles), dim3(256), 0, s, A.rowptr, A.colidx, A.vals,
-                       coords, units, A.m, rows, part, io.B, io.C, io.n, io.policy, io.order);
-    hipError_t e = hipGetLastError();
+    const size_t lds = merge_lds_bytes(geo, A.m, A.nnz, io.n);
+    auto launch = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(nb, geo.coltiles), dim3(256), lds, s, A.rowptr, A.colidx, A.vals, coords, units,
+                         A.m, rows, part, io.B, io.C, io.n, io.policy, io.order);
+      return hipGetLastError();
+    };
+    hipError_t e;
+    if (G == 64 && merge_long_rows(geo, A.m, A.nnz))
+      e = launch(&k_csr_merge<G, VW, ODD, G == 64>);
+    else
+      e = launch(&k_csr_merge<G, VW, ODD, false>);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_merge_fixup<G, VW, ODD>), dim3(nb, geo.coltiles), dim3(256), 0, s, A.rowptr, coords, rows, part,
                        units, io.C, io.n);
@@ -1845,7 +1887,7 @@ hipError_t kernel_attributes(int32_t family, int32_t engine, int32_t n, int32_t 
     return with_row_batch<G>(stream > 0 ? 0 : rows_per_group, unroll, [&](auto jj, auto uu) -> hipError_t {
       constexpr int J = decltype(jj)::value, UNR = decltype(uu)::value;
       const void *fn = family == 2   ? (const void *)&k_csr_split<G, VW, ODD, J, UNR>
-                       : family == 3 ? (const void *)&k_csr_merge<G, VW, ODD || (VW == 4 && G >= 8)>
+                       : family == 3 ? (const void *)&k_csr_merge<G, VW, ODD || (VW == 4 && G >= 8), false>
                                      : (const void *)&k_csr_rows<G, VW, ODD, J, UNR, false>;
       return hipFuncGetAttributes(attr, fn);
     });

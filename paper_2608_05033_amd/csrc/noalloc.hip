@@ -105,7 +105,7 @@ extern "C" int sd_spmm_merge_noalloc(const sd_csr_t *A, int32_t n, int32_t units
   io.policy = 0;
   io.col_tile = 0;
   io.order = 0;  // the merge plan's default: the hardware's round-robin
-  const sd::CsrOperand Aop{A->rowptr, A->colidx, A->values, A->m, A->k};
+  const sd::CsrOperand Aop{A->rowptr, A->colidx, A->values, A->m, A->k, A->nnz};
   e = sd::launch_csr_merge(Aop, coords, (int32_t)U, rows, part, io, s);
   if (e != hipSuccess) return sd::report_hip_error(e);
   return SD_OK;

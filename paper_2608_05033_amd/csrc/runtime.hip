@@ -542,6 +542,7 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
   if (e != hipSuccess) return hip_fail(e);
   I.regs_per_thread = attr.numRegs;
   I.lds_bytes = (int32_t)attr.sharedSizeBytes;
+  if (I.family == SD_FMT_CSR_MERGE) I.lds_bytes += (int32_t)sd::merge_lds_bytes(geo, A.m, A.nnz, n);
   if (I.family == SD_FMT_WIN) I.lds_bytes += (int32_t)sd::window_lds_bytes(n, vec4, col_tile, I.window_max);
   I.legal = (I.block_threads <= I.max_threads && I.block_threads <= attr.maxThreadsPerBlock &&
              (int64_t)attr.numRegs * I.block_threads <= regs_per_cu && I.lds_bytes <= I.max_lds_bytes)
@@ -887,7 +888,7 @@ int sd_spmm(sd_plan_t p, const float *B, float *C, void *stream) {
   io.policy = I.cache_policy == 2 ? 1 : I.cache_policy == 3 ? 2 : 0;
   io.col_tile = p->col_tile_req;
   io.order = I.wg_order == 1 ? 1 : I.wg_order == 3 ? std::max(2, I.wg_chunk) : 0;
-  sd::CsrOperand A{p->d_rowptr, p->d_colidx, p->d_vals, (int32_t)I.m, (int32_t)I.k};
+  sd::CsrOperand A{p->d_rowptr, p->d_colidx, p->d_vals, (int32_t)I.m, (int32_t)I.k, I.nnz};
   hipError_t e = hipSuccess;
   switch (I.family) {
     case SD_FMT_CSR_ROW:

@@ -317,3 +317,33 @@ def test_split_stores_of_small_and_large_outputs(n):
     with sd.sd_plan_ex(A, n, force="csr_split") as plan:
         assert plan.info["n_light"] > 59000 and plan.info["n_heavy"] > 10
         assert_close(run(sd, plan, B, m), C64, S, f"split stores n={n}")
+
+
+@pytest.mark.parametrize("n", [63, 129, 180, 256, 300])
+@pytest.mark.parametrize("rows", [(40, 31), (40, 33), (2000, 500), (4000, 300), (9000, 350)])
+def test_merge_long_rows(n, rows):
+    """The merge path's batches without a row's end: means just under and over 32,
+    rows that end on batch edges, empty rows between long ones, and (the last) enough
+    gathered bytes for two workgroups per CU."""
+    m, mean = rows
+    lens = np.full(m, mean)
+    lens[1::7], lens[2::7] = 8 * (mean // 8), 0
+    lens[3::7] += mean
+    lens[0], lens[-1] = 64, 1
+    A = gen.random_rows(m, 1500, lens.astype(np.int32), seed=n)
+    B = gen.dense_uniform(A.k, n, seed=n)
+    C64, S = oracle.spmm(A, B)
+    csr = _device_csr(A)
+    Bd, Cd = torch.from_numpy(B).cuda(), torch.full((m, n), float("nan"), device="cuda")
+    for units in (0, 1, 37, 999):
+        print(f"case merge long rows n={n} rows={rows} units={units}", flush=True)
+        Cd.fill_(float("nan"))
+        sd.sd_spmm_merge_noalloc(*csr, m, A.k, A.nnz, n, Bd, Cd, units=units)
+        torch.cuda.synchronize()
+        assert_close(Cd.cpu().numpy(), C64, S, f"merge long n={n} {rows} units={units}")
+    with sd.sd_plan_ex(A, n, force="csr_merge") as plan:
+        if n > 128:
+            assert (plan.info["lds_bytes"] == 65536) == (4.0 * A.nnz * n >= 0.9e9 and A.nnz >= 32 * m)
+        elif m == 9000:
+            assert plan.info["lds_bytes"] == 65536
+        assert_close(run(sd, plan, B, m), C64, S, f"merge long plan n={n} {rows}")
