@@ -447,6 +447,78 @@ int32_t wide_col_tile(const sd_stats_t &st, int32_t family, int32_t n, int64_t b
   return wide && (n % 128 == 0 || n % 128 > 64) ? 128 : 64;
 }
 
+// Four columns per lane issue a quarter of the loads, and pay while there are waves
+// enough; one column per lane spreads a row over four times the lanes, so four times
+// the waves, longer tiles of entries and (below 8 lanes) 8 gathers in flight instead
+// of 2 or 4.  Time with one column over time with four, n % 4 != 0:
+//  * CSR_ROW: rows shared by lane groups (n <= 15) 1.2 to 3; not shared 0.6 to 1.0.
+//    n = 17 .. 31: 9,000 rows (1,125 waves) 0.75 to 0.92, 18,000 0.8 to 1.0, 30,000 rows
+//    of 6, 14, 24, 54: 1.2, 1.1, 1.0, 0.85, 60,000: 1.2, 1.0, 0.9, 0.86, from 96,000
+//    rows on, streamed, 1.1 to 1.7.  n = 33 .. 63: 9,000 rows (2,250 waves) 0.85 to 1.06,
+//    18,000 0.95 to 1.4; n = 65 .. 127: 2,500 rows (1,250 waves) 0.82 to 1.03, 9,000 1.0
+//    to 1.3.
+//  * CSR_SPLIT: n = 33 .. 63, 4,500 vertices (1,125 waves) 0.8 to 0.9, 9,000 1.04 to 1.1;
+//    any other 1.0 to 2.
+//  * ELL, by the columns a row spans times the bytes of a row of B (MB), rows of 7 to
+//    16: n <= 7: 0.1 1.2, 0.3 to 0.6 0.9 to 1.1, 1 to 10 0.8 to 0.95; n <= 15: up to 3.3
+//    1.0 to 1.7, 4 to 20 0.85 to 0.97; n <= 31: up to 7 1.0 to 2.3, 8 to 45 0.9 to 1.0;
+//    rows of 3 cross at four times that, of 5 a little later, of 24 and 40 earlier; wider
+//    0.95 to 3.  12,000 rows of 16 to 40, n = 9 .. 15 (750 waves): 0.8 to 0.94.
+//  * SELL: as ELL for short rows; 9,000 rows of 24: n = 17 .. 31 0.79, 33 .. 63 0.97,
+//    wider 1.2; 12,000 rows of 16: n <= 15 0.73 to 0.9, then 1.1 to 1.7; a graph with a row
+//    of 40,000: n <= 31 0.33 to 0.6, n = 33 .. 63 0.7, wider 1.05 to 1.35.
+//  * windows and blocks without matrix cores: n <= 7 0.7 to 0.94 (7-point stencil 1.2), wider
+//    0.9 to 3.4.
+bool four_columns(const sd_stats_t &st, int32_t family, int32_t engine, int32_t n, int32_t G, int32_t row_slices) {
+  if (n < 4) return false;
+  if (n % 4 == 0) return true;
+  const double waves = (double)st.m * G / 64.0, MiB = 1048576.0;
+  // ELL and short SELL rows: the stretch of B that a row reaches over, against L2
+  auto reach_fits = [&](double width) {
+    if (G >= 16) return true;
+    if (G <= 4 && width >= 16.0 && waves < 1000.0) return false;
+    if (G == 2 && width > 8.0) return false;
+    const double limit = G == 2 ? 0.5 : (G == 8 ? 6.0 : 3.0) * (width <= 4.0 ? 4.0 : width <= 6.0 ? 1.3 : width < 20.0 ? 1.1 : 0.9);
+    return st.row_span_mean * 4.0 * n <= limit * MiB;
+  };
+  switch (family) {
+    case SD_FMT_CSR_ROW:
+      if ((row_slices > 0 ? row_slices : slices_for(st, family, n, G)) > 1) return true;
+      if (G <= 4 || waves < 2400.0) return false;
+      return G > 8 || st.row_mean <= 16.0 || st.m >= 96000;
+    case SD_FMT_CSR_SPLIT:
+      return G <= 8 || waves >= 2000.0;
+    case SD_FMT_CSR_MERGE:
+      return four_columns_merge(st.m, st.nnz, n, G);
+    case SD_FMT_ELL:
+      return reach_fits((double)st.row_max);
+    case SD_FMT_SELL:
+      if (st.row_mean <= 8.0) return reach_fits(st.row_mean);
+      if (G <= 4 || (G == 8 && (st.row_mean > 16.0 || waves < 1500.0))) return false;
+      return G >= 32 || (double)st.row_max <= 16.0 * st.row_mean;
+    case SD_FMT_WIN:
+      return G > 2 || st.row_mean <= 8.0;
+    default:
+      return engine != SD_ENGINE_VALU || G > 2;
+  }
+}
+
+// One column per lane over four, rows around a band and R-MAT graphs (us), by the mean
+// row and the path's length: n <= 15: 0.6 to 1.0 (rows of 130, 16 M steps: 1.2 at n = 5, 0.87
+// at 15); n = 17 .. 31: rows of 6 to 14 0.65 to 0.95, of 24 from 0.7 M on 0.9 to 1.1, 2.1 M
+// (a graph) 1.15 to 1.3, of 54 and 130 0.9 to 1.4 from 0.6 M on; n = 33 .. 63: rows of 6 0.65 to
+// 0.95, of 12 and 24 from 0.4 M on 1.0 to 1.3, of 9 at 3 M 1.0 to 1.2; n = 65 .. 127: 0.16 M
+// 0.8 to 0.95, 0.2 M 1.0 to 1.2; wider: 0.03 M 0.85, 0.06 M 0.97.
+bool four_columns_merge(int64_t m, int64_t nnz, int32_t n, int32_t G) {
+  if (n < 4) return false;
+  if (n % 4 == 0) return true;
+  const int64_t path = m + nnz;
+  if (G <= 4) return false;
+  if (G == 8) return nnz >= 16 * m && path >= 600000;
+  if (G == 16) return (nnz >= 12 * m && path >= 400000) || (nnz >= 8 * m && path >= 2000000);
+  return path >= (G == 32 ? 180000 : 60000);
+}
+
 int32_t slices_for(const sd_stats_t &st, int32_t family, int32_t n, int32_t G) {
   (void)n;
   if ((family != SD_FMT_CSR_ROW && family != SD_FMT_CSR_SPLIT) || G > 8) return 1;

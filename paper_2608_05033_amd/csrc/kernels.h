@@ -24,7 +24,7 @@ struct DenseIO {
   const float *B;
   float *C;
   int32_t n;
-  int32_t vec4;    // 1: four columns per lane (any n >= 4, any alignment), 0: one
+  int32_t vec4;    // 1: four columns per lane (n >= 4), 0: one; any alignment
   int32_t policy;  // B-gather cache policy: 0 normal, 1 tiered by the column tag, 2 non-temporal
   int32_t col_tile;  // dense columns per lane group (power of two >= 4), 0 = whole width
   int32_t order;     // workgroup order: 1 one contiguous range of rows per XCD, 0 hardware round-robin,

@@ -1647,12 +1647,13 @@ bool merge_long_rows(const Geometry &geo, int32_t m, int64_t nnz) { return geo.G
 // 1.21, two 1.03 times the speed of walking row by row).  So do odd widths that use
 // every lane, whose rows of B straddle more lines than their neighbours' (n = 31, 63: 60,000
 // rows of 130 1.00 / 1.45 and 0.72 / 0.89, 300,000 of 24 0.86 / 1.00 and 0.90 / 0.99 times
-// that speed; n = 47 1.30 / 0.96).  R-MAT graphs lose (100 k vertices, 21 a row, N = 180:
-// 1.85 / 1.49); they have fewer nonzeros a row, and only m and nnz are known here.
+// that speed; n = 47 1.30 / 0.96; n = 125, 18,000 rows of 130: 89 / 120 us).  R-MAT
+// graphs lose (100 k vertices, 21 a row, N = 180: 1.85 / 1.49); they have fewer nonzeros
+// a row, and only m and nnz are known here.
 size_t merge_lds_bytes(const Geometry &geo, int32_t m, int64_t nnz, int32_t n) {
   const double gathered = 4.0 * (double)nnz * n;
   if (merge_long_rows(geo, m, nnz)) return gathered >= 0.9e9 ? 65536 : 0;
-  const bool last_lane_odd = geo.odd && geo.coltiles == 1 && n > (geo.G - 1) * geo.VW;
+  const bool last_lane_odd = geo.odd && geo.G <= 16 && geo.coltiles == 1 && n > (geo.G - 1) * geo.VW;
   return last_lane_odd && nnz >= 24 * (int64_t)m && gathered >= 0.7e9 ? 65536 : 0;
 }
 
@@ -1687,12 +1688,7 @@ hipError_t launch_csr_merge(const CsrOperand &A, const int32_t *coords, int32_t 
 
 hipError_t launch_ell(const int32_t *ecol, const float *eval, int32_t width, int32_t m, int32_t passes,
                       const DenseIO &io, hipStream_t s) {
-  // Long rows at narrow widths of no whole 4 columns: one column per lane, whose
-  // wider lane groups take fewer tiles per row (100,000 rows of 24, N = 5, 13, 17,
-  // 31: 18.3, 27.8, 34.2, 59.7 us against 19.9, 30.1, 37.3, 64.0 with four; rows
-  // of 7, N = 5, 17: 9.8, 31.2 against 7.3, 14.1).
-  const bool narrow = io.n % 4 != 0 && io.n < 32 && width > 16;
-  const Geometry geo = geometry_for(io.n, narrow ? 0 : io.vec4, io.col_tile);
+  const Geometry geo = geometry_for(io.n, io.vec4, io.col_tile);
   return with_geometry(geo, [&](auto gg) -> hipError_t {
     constexpr int G = decltype(gg)::G, VW = decltype(gg)::VW;
     constexpr bool ODD = decltype(gg)::ODD;

@@ -74,7 +74,7 @@ extern "C" int sd_spmm_merge_noalloc(const sd_csr_t *A, int32_t n, int32_t units
   if (ds.status != hipSuccess || !ds.ptr) return sd::report_hip_error(ds.status != hipSuccess ? ds.status
                                                                                              : hipErrorInvalidSymbol);
 
-  const int32_t vec4 = n >= 4;
+  const int32_t vec4 = sd::four_columns_merge(A->m, A->nnz, n, sd::geometry_for(n, 1, 0).G) ? 1 : 0;
   const sd::Geometry geo = sd::geometry_for(n, vec4, 0);
   const int64_t total = (int64_t)A->m + A->nnz;
   int64_t U = units;

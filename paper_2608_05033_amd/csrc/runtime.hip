@@ -197,7 +197,6 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
   I.device = p->device;
 
   // ---- family and parameters
-  const int32_t vec4 = n >= 4 ? 1 : 0;
   // K tiles: when the dense operand is larger than half the Infinity Cache,
   // 64-column passes halve the gathered footprint per pass (measured on the
   // power-law workloads at N = 128: -10 to -14 %; no gain at N <= 64).
@@ -205,10 +204,16 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
   // wide_col_tile refines it once the family is known.
   if (col_tile == 0 && n > 64 && 4 * (int64_t)A.k * n > sd::kMallBytes / 2) col_tile = 64;
   const int64_t b_bytes = 4 * (int64_t)A.k * n;
+  int32_t vec4 = n >= 4 ? 1 : 0;
   sd::PlanChoice pc = sd::choose_plan(stats, n, I.cu_count, sd::geometry_for(n, vec4, col_tile).G, o);
+  if (vec4 && !sd::four_columns(stats, pc.family, pc.engine, n, sd::geometry_for(n, 1, col_tile).G, o.row_slices)) {
+    vec4 = 0;
+    pc = sd::choose_plan(stats, n, I.cu_count, sd::geometry_for(n, vec4, col_tile).G, o);
+  }
   if (o.col_tile == 0 && col_tile > 0) col_tile = sd::wide_col_tile(stats, pc.family, n, b_bytes);
   const sd::Geometry geo = sd::geometry_for(n, vec4, col_tile);
   p->col_tile_req = col_tile;
+  p->vec4 = vec4;
   I.lanes_per_row = geo.G;
   I.col_tile = geo.G * geo.VW;
   I.col_passes = geo.coltiles;
@@ -884,7 +889,7 @@ int sd_spmm(sd_plan_t p, const float *B, float *C, void *stream) {
   io.B = B;
   io.C = C;
   io.n = (int32_t)I.n;
-  io.vec4 = I.n >= 4 ? 1 : 0;
+  io.vec4 = p->vec4;
   io.policy = I.cache_policy == 2 ? 1 : I.cache_policy == 3 ? 2 : 0;
   io.col_tile = p->col_tile_req;
   io.order = I.wg_order == 1 ? 1 : I.wg_order == 3 ? std::max(2, I.wg_chunk) : 0;
@@ -1344,7 +1349,7 @@ int search_plan(const sd_csr_t *A, int32_t n, const sd_plan_opts_t &o, sd_plan_t
   if (stats.row_max >= 64) add(SD_FMT_CSR_SPLIT, 64, 64, 0, 0);
   add_orders(SD_FMT_CSR_MERGE, 0);
   // narrow widths: rows shared by S lane groups (G lanes cover the width)
-  const int32_t G = sd::geometry_for(n, n >= 4, best->col_tile_req).G;
+  const int32_t G = sd::geometry_for(n, n >= 4 ? 1 : 0, best->col_tile_req).G;
   if (G <= 8 && stats.nnz > 0) {
     for (int32_t S = 1; S <= 64 / G; S *= 2) {
       add(SD_FMT_CSR_ROW, 0, 0, 0, 0, 0, S);

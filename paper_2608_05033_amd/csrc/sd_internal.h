@@ -134,6 +134,12 @@ int32_t chunk_for_reach(int64_t reach, int64_t rows_per_wg);
 // B (CSR_ROW only).
 int32_t stream_for(int32_t family, int64_t rows, double row_mean, int32_t G, int64_t window_rows, int64_t row_bytes,
                    int64_t b_bytes);
+// Whether a lane takes four dense columns or one, by which a family's kernels are
+// faster.  G: lanes that cover the width, or a column pass of it, with four; below n = 4
+// it is one, and whole multiples of 4 take four.  row_slices: requested (0: the
+// planner's).  The merge path has only its sizes to go by.
+bool four_columns(const sd_stats_t &st, int32_t family, int32_t engine, int32_t n, int32_t G, int32_t row_slices);
+bool four_columns_merge(int64_t m, int64_t nnz, int32_t n, int32_t G);
 // Dense columns per lane group when B is larger than half the Infinity Cache and
 // n > 64 (0: the whole width).
 int32_t wide_col_tile(const sd_stats_t &st, int32_t family, int32_t n, int64_t b_bytes);
@@ -168,6 +174,7 @@ struct sd_plan_s {
   sd_plan_info_t info{};
   int32_t device = -1;  // -1: host only
   int32_t col_tile_req = 0;  // requested dense columns per lane group (0: whole width)
+  int32_t vec4 = 0;          // 1: four dense columns per lane, 0: one
 
   // host arrays
   std::vector<int32_t> h_rowptr, h_colidx, h_coltag, h_light, h_chunks, h_corder, h_heavy_rows, h_heavy_ptr, h_coords,

@@ -188,17 +188,9 @@ ODD_FAMILIES = [("csr_row", {}), ("csr_row", {"row_slices": 1}), ("csr_split", {
                 ("ell", {"rows_per_group": 4}), ("win", {"heavy_threshold": 200}), ("sell", {})]
 
 
-@pytest.mark.parametrize("fam,opts", ODD_FAMILIES, ids=[f"{f}-{i}" for i, (f, _) in enumerate(ODD_FAMILIES)])
-@pytest.mark.parametrize("n", [4, 5, 6, 7, 9, 15, 17, 31, 33, 50, 63, 65, 101, 130, 255, 257])
-@pytest.mark.parametrize("off", [0, 1, 2, 3])
-def test_odd_widths(fam, opts, n, off):
-    """Four columns per lane at widths that leave the last lane fewer, with B and C
-    at every 4-byte offset, rows of up to three column passes, and nothing
-    written outside C."""
-    rng = np.random.default_rng(5)
-    lens = rng.integers(0, 40, 301)
-    lens[::50] = 250
-    A = gen.random_rows(301, 260, np.minimum(lens, 260).astype(np.int32), seed=1)
+def _odd_product(A, fam, opts, n, off, lanes=None):
+    """One product with B and C `off` floats past a 16-byte boundary: right, and
+    nothing written outside C."""
     B = gen.dense_uniform(A.k, n, seed=n)
     C64, S = oracle.spmm(A, B)
     Bs = torch.empty(A.k * n + off, device="cuda")
@@ -206,12 +198,47 @@ def test_odd_widths(fam, opts, n, off):
     Cs = torch.full((A.m * n + 16,), -7.0, device="cuda")
     first = 8 + off
     Cd = Cs[first:first + A.m * n].view(A.m, n)
-    print(f"case odd {fam} {opts} n={n} off={off}", flush=True)
     with sd.sd_plan_ex(A, n, force=fam, **opts) as plan:
+        if lanes:
+            assert plan.info["lanes_per_row"] // max(1, plan.info["row_slices"]) == lanes
         sd.sd_spmm(plan, Bs[off:], Cd, torch.cuda.current_stream())
         torch.cuda.synchronize()
     assert_close(Cd.cpu().numpy(), C64, S, f"odd {fam} n={n} off={off}")
     assert bool((Cs[:first] == -7.0).all()) and bool((Cs[first + A.m * n:] == -7.0).all())
+
+
+@pytest.mark.parametrize("fam,opts", ODD_FAMILIES, ids=[f"{f}-{i}" for i, (f, _) in enumerate(ODD_FAMILIES)])
+@pytest.mark.parametrize("n", [4, 5, 6, 7, 9, 15, 17, 31, 33, 50, 63, 65, 101, 130, 255, 257])
+@pytest.mark.parametrize("off", [0, 1, 2, 3])
+def test_odd_widths(fam, opts, n, off):
+    """Widths that leave the last lane fewer columns, in one column per lane or four as
+    the plan picks for a small matrix, with B and C at every 4-byte offset, rows of up
+    to three column passes, and nothing written outside C."""
+    rng = np.random.default_rng(5)
+    lens = rng.integers(0, 40, 301)
+    lens[::50] = 250
+    A = gen.random_rows(301, 260, np.minimum(lens, 260).astype(np.int32), seed=1)
+    print(f"case odd {fam} {opts} n={n} off={off}", flush=True)
+    _odd_product(A, fam, opts, n, off)
+
+
+@pytest.mark.parametrize("fam,mean", [("csr_row", 7), ("csr_split", 7), ("ell", 4), ("sell", 4), ("csr_merge", 36)])
+@pytest.mark.parametrize("n", [5, 7, 9, 15, 17, 18, 19, 31, 33, 63, 65, 101, 127, 130, 255])
+def test_odd_widths_four_columns(fam, mean, n):
+    """Four columns per lane at widths of no whole 4, with rows enough for the plan to
+    pick them."""
+    m = 24011
+    lens = np.random.default_rng(n).integers(0, 2 * mean + 1, m)
+    if fam == "csr_split":
+        lens[::4000] = 700
+    A = gen.random_rows(m, 900, lens.astype(np.int32), seed=n)
+    four = 1
+    while four < min(64, -(-n // 4)):
+        four *= 2
+    if fam == "csr_merge" and n < 16:
+        four *= 4  # one column per lane there
+    print(f"case odd four {fam} n={n}", flush=True)
+    _odd_product(A, fam, {}, n, n % 4, lanes=four)
 
 
 @pytest.mark.parametrize("fam", ["bsr", "bell"])

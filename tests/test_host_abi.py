@@ -508,6 +508,39 @@ def test_planner_rules():
         assert p.family == "csr_row"
 
 
+def test_planner_lane_width():
+    """Lanes per row at widths of no whole 4 columns (a heuristic reading, set by
+    measurement; parity unpinned): four columns per lane where there are waves enough,
+    one where rows are few, long or reach over much of B.  The plan describes the lanes
+    that it launches with."""
+    def lanes(A, n, **kw):
+        with sd.sd_plan_ex(A, n, placement=HOST, **kw) as p:
+            S = max(1, p.info["row_slices"])
+            G = p.info["lanes_per_row"] // S
+            assert p.info["col_tile"] in (G, 4 * G) and p.info["col_passes"] == -(-n // p.info["col_tile"])
+            return G
+
+    rng = np.random.default_rng(0)
+    few = gen.random_rows(3000, 3000, rng.integers(30, 80, 3000), seed=1)
+    many = gen.random_rows(100000, 400, rng.integers(2, 12, 100000), seed=1)
+    for n, one, four in ((5, 8, 2), (15, 16, 4), (27, 32, 8), (63, 64, 16)):
+        assert lanes(few, n, force="csr_row", row_slices=1) == one, n
+        if n > 16:
+            assert lanes(few, n, force="csr_row") == one and lanes(many, n, force="csr_row") == four, n
+        else:  # rows shared by lane groups
+            assert lanes(few, n, force="csr_row") == four, n
+        assert lanes(few, n, force="csr_row", row_slices=2 if n < 32 else 1) == (four if n < 32 else one), n
+    lap = gen.laplacian3d(30, 30, 30)
+    wide = gen.uniform_rows(2000, 200000, 24, 0)
+    assert [lanes(lap, n, force="ell") for n in (5, 13, 17, 31)] == [2, 4, 8, 8]
+    assert [lanes(wide, n, force="ell") for n in (5, 13, 17, 31)] == [8, 16, 32, 32]
+    assert [lanes(wide, n, force="ell") for n in (4, 12, 32, 33, 101)] == [1, 4, 8, 16, 32]
+    assert [lanes(few, n, force="sell") for n in (7, 31, 101)] == [8, 32, 32]
+    assert [lanes(few, n, force="win") for n in (7, 9)] == [8, 4]
+    assert [lanes(few, n, force="bsr", engine="valu") for n in (7, 9)] == [8, 4]
+    assert [lanes(few, n, force="csr_merge") for n in (7, 31, 47, 101, 150)] == [8, 32, 64, 64, 64]
+
+
 def test_planner_slices_at_narrow_widths():
     """Narrow widths (a heuristic reading, set by measurement; parity unpinned):
     heavy-split light rows get 8 lanes (16 at G = 8), the row kernel about one
