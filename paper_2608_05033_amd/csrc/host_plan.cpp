@@ -399,23 +399,29 @@ void row_batch_for(const sd_stats_t &st, int64_t rows, int32_t G, int32_t cu_cou
   *unr = u;
 }
 
-// The lines, measured with B streamed from HBM and MALL (us, one row per lane
-// group at a time round-robin / streamed):
-//  * CSR_ROW, rows of 24 around a band, 300,000 rows.  The rows in flight on an
-//    XCD and the band around them have to fit its L2 (4 MiB): N = 64 and a window
-//    of 0.4, 2.4, 9.5 MB: 154 / 125, 158 / 132, 180 / 188; N = 96 and 7.3 MB: 243 /
-//    213.  A window wider than the rows of one XCD makes the XCDs fetch each
-//    other's rows: 120,000 rows, window 40,000, N = 40 (6 MB): 127 / 149.
+// The lines (us, one row per lane group at a time round-robin / streamed; or the first
+// over the second):
+//  * CSR_ROW around a band.  The stretch of B that the rows in flight reach over has to
+//    be held by L2 well enough (4 MiB an XCD; the streamed rows of one XCD are
+//    adjacent, those of the round-robin are not).  300,000 rows of 24, N = 64 and a
+//    window of 0.4, 2.4, 9.5 MB: 154 / 125, 158 / 132, 180 / 188; N = 96 and 7.3 MB: 243 /
+//    213.  By the length of the rows: rows of 9 at 7.7 MB 1.06 to 1.24, of 24 0.97 to
+//    1.03, of 54 0.90 to 0.95, of 130 0.86 to 0.89; at 6.1 MB of 54 1.02 to 1.13, of 130 0.94 and
+//    1.01; at 5.1 MB both 1.02 to 1.03.  A window wider than the rows of one XCD makes the XCDs fetch
+//    each other's rows: 120,000 rows, window 40,000, N = 40 (6 MB): 127 / 149.
 //    4 rows per group keep more rows in flight than 2 and balance better, while
 //    the window is small (7.3 MB: 213 with 2, 221 with 4) and workgroups many
 //    (120,000 rows of 55, N = 40: 119 with 2, 125 with 4).
-//    Few workgroups: 20,000 rows, N = 40: 22 / 27; 60,000: 48 / 45.
+//    Few workgroups: 20,000 rows, N = 40: 22 / 27; 60,000: 48 / 45.  Rows of 130 need
+//    more (1,875 workgroups of two rows a group: N = 40, 64, 96, 128: 0.92, 0.98, 0.89, 0.96;
+//    3,750: 0.98 to 1.04; N = 32, 8 lanes a row, 1.14), rows of 54 under whole waves too (2,250: N = 180 0.93).
 //  * Short rows under wide lane groups leave a wave two or one of them, and gain
 //    from streaming on any columns while B is small: 150,000 rows of 6 on random
 //    columns, N = 80, 96, 192: 63.5 / 60.5, 65.9 / 62.2, 110 / 106 (N = 128: 77 / 78;
 //    500,000 rows, N = 128, B of 244 MB: 234 / 253).
-//  * Light rows of the split: R-MAT 2^20, N = 128: 931 / 895, N = 100: 994 / 954;
-//    2^18, N = 64: 119 / 126, where the last workgroups are too large a share.
+//  * Light rows of the split, R-MAT graphs by workgroups of four rows a group: 900 to
+//    2,000 0.71 to 0.85, 4,000 0.91 to 1.0, 8,000 0.92 to 1.0, 11,000 to 14,000 0.95 to 1.02,
+//    from 16,000 on 1.0 to 1.06.
 int32_t stream_for(int32_t family, int64_t rows, double row_mean, int32_t G, int64_t window_rows, int64_t row_bytes,
                    int64_t b_bytes) {
   if (G < 8) return 0;
@@ -423,9 +429,11 @@ int32_t stream_for(int32_t family, int64_t rows, double row_mean, int32_t G, int
   auto workgroups = [&](int64_t R) { return rows / (R * groups); };
   if (family == SD_FMT_CSR_SPLIT) return workgroups(4) >= 16000 ? 4 : 0;
   const int64_t window = window_rows * row_bytes;
-  if (8 * window_rows <= rows && window <= (15ll << 19)) {  // 7.5 MiB
+  const int64_t most = (row_mean <= 40.0 ? 15ll : row_mean <= 80.0 ? 13ll : 11ll) << 19;  // 7.5, 6.5, 5.5 MiB
+  const int64_t least = row_mean > 40.0 && G == 64 ? 3000 : row_mean > 80.0 && G >= 16 ? 2000 : 1500;
+  if (8 * window_rows <= rows && window <= most) {
     if (workgroups(4) >= 4096 && window <= (4ll << 20)) return 4;
-    if (workgroups(2) >= 1500) return 2;
+    if (workgroups(2) >= least) return 2;
   }
   return G >= 32 && row_mean <= 8.0 && workgroups(4) >= 4096 && b_bytes <= kMallBytes / 2 ? 4 : 0;
 }

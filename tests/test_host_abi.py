@@ -541,6 +541,33 @@ def test_planner_lane_width():
     assert [lanes(few, n, force="csr_merge") for n in (7, 31, 47, 101, 150)] == [8, 32, 64, 64, 64]
 
 
+def test_planner_streamed_rows():
+    """Which CSR_ROW plans stream their rows (a heuristic reading, set by measurement;
+    parity unpinned): rows around a band whose stretch of B fits, workgroups enough;
+    long rows less and later; never under an explicit order, batch or width of 4 or less."""
+    def stream(A, n, **kw):
+        with sd.sd_plan_ex(A, n, force="csr_row", placement=HOST, **kw) as p:
+            assert p.info["wg_order"] == 1 or p.info["stream_rows"] == 0 or kw
+            return p.info["stream_rows"]
+
+    def band(m, mean, width):
+        lens = np.random.default_rng(m).integers(mean // 2, mean + mean // 2 + 1, m)
+        rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        rows = np.repeat(np.arange(m), lens)
+        step = width // lens[rows]
+        cols = np.clip(rows - width // 2, 0, m - width) + (np.arange(rows.size) - rowptr[rows]) * step
+        return gen.CSR(m, m, rowptr, cols.astype(np.int32), np.ones(cols.size, np.float32))
+
+    A = band(100000, 12, 2000)
+    assert stream(A, 64) == 2 and stream(A, 128) == 2 and stream(A, 256) == 4 and stream(A, 16) == 0
+    for kw in (dict(wg_order=2), dict(wg_order=1), dict(rows_per_group=1), dict(gather_unroll=8)):
+        assert stream(A, 64, **kw) == 0
+    assert stream(band(100000, 12, 20000), 64) == 0      # wider than the rows of one XCD
+    assert stream(band(30000, 12, 1200), 96) == 2 and stream(band(30000, 100, 1200), 96) == 0  # 1,875 workgroups
+    assert stream(band(18000, 24, 1200), 180) == 2 and stream(band(18000, 54, 1200), 180) == 0
+    assert stream(band(60000, 24, 7000), 256) == 2 and stream(band(60000, 100, 7000), 256) == 0  # 6.8 MiB
+
+
 def test_planner_slices_at_narrow_widths():
     """Narrow widths (a heuristic reading, set by measurement; parity unpinned):
     heavy-split light rows get 8 lanes (16 at G = 8), the row kernel about one
