@@ -468,7 +468,9 @@ void sd_plan_destroy(sd_plan_t plan);
 /* Device memory that destroyed plans and finished conversions leave is kept for
  * later plans, at most 1 GiB per device.  This returns what is kept to the
  * device; plans in use are not touched.  An allocation of the library that
- * would fail does the same by itself before it gives up. */
+ * would fail does the same by itself before it gives up.  To be called, with
+ * every plan destroyed, before a hipDeviceReset, which takes the kept memory
+ * away as well. */
 void sd_release_memory(void);
 
 /* Static strings; never NULL. */

@@ -12,13 +12,18 @@
 // then: scratch is given back after its stream has drained (kIdle); a plan's
 // memory may still be read by products its caller has in flight (kInFlight),
 // and is handed out again only after a device synchronisation, which hipFree
-// would have made at once.  sd_release_memory, or an allocation that would
-// otherwise fail, returns the kept blocks to the device.
+// would have made at once, and only where no idle block fits.  sd_release_memory,
+// or an allocation that would otherwise fail, returns the kept blocks to the
+// device.
+//
+// The lock covers the lists alone: no HIP call is made under it, so a thread
+// that waits for its device holds up neither another device's threads nor its own's.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 #include <map>
 #include <mutex>
+#include <new>
 #include <unordered_map>
 
 #include "kernels.h"
@@ -34,32 +39,57 @@ struct Block {
 };
 struct Kept {
   void *p;
-  bool in_flight;
   uint64_t age;
 };
 struct DevicePool {
-  std::multimap<size_t, Kept> blocks;                              // by size
-  std::map<uint64_t, std::multimap<size_t, Kept>::iterator> ages;  // the longest kept first
+  using Blocks = std::multimap<size_t, Kept>;  // by size
+  struct Place {
+    bool in_flight;
+    Blocks::iterator it;
+  };
+  Blocks idle, in_flight;
+  std::map<uint64_t, Place> ages;  // the longest kept first
   size_t kept = 0;
   uint64_t next_age = 0;
 
-  void add(size_t bytes, void *p, bool in_flight) {  // may throw: nothing is added then
-    auto it = blocks.emplace(bytes, Kept{p, in_flight, next_age});
+  void add(size_t bytes, void *p, bool flying) {  // may throw: nothing is added then
+    Blocks &to = flying ? in_flight : idle;
+    auto it = to.emplace(bytes, Kept{p, next_age});
     try {
-      ages.emplace(next_age, it);
+      ages.emplace(next_age, Place{flying, it});
     } catch (...) {
-      blocks.erase(it);
+      to.erase(it);
       throw;
     }
     ++next_age;
     kept += bytes;
   }
-  void *take(std::multimap<size_t, Kept>::iterator it) {
-    void *p = it->second.p;
-    kept -= it->first;
-    ages.erase(it->second.age);
-    blocks.erase(it);
+  void *take(Place at) {
+    void *p = at.it->second.p;
+    kept -= at.it->first;
+    ages.erase(at.it->second.age);
+    (at.in_flight ? in_flight : idle).erase(at.it);
     return p;
+  }
+  // The smallest block of `size` to 5/4 `size` bytes, an idle one if there is one.
+  bool find(size_t size, Place *at) {
+    for (bool flying : {false, true}) {
+      Blocks &from = flying ? in_flight : idle;
+      auto it = from.lower_bound(size);
+      if (it == from.end() || it->first > size + size / 4) continue;
+      *at = {flying, it};
+      return true;
+    }
+    return false;
+  }
+  // What was kept before `age` is no longer in flight.
+  void drained(uint64_t age) {
+    for (auto it = in_flight.begin(); it != in_flight.end();) {
+      auto here = it++;
+      if (here->second.age >= age) continue;
+      const uint64_t a = here->second.age;
+      ages[a] = {false, idle.insert(in_flight.extract(here))};
+    }
   }
 };
 struct Pool {
@@ -73,19 +103,50 @@ Pool &pool() {
   return *p;
 }
 
-// 4 KiB steps up to 64 KiB, then eighths of the next power of two below.
+// 4 KiB steps up to 64 KiB, then eighths of the next power of two below.  What is too
+// large to be kept is not stretched.
 size_t rounded(size_t bytes) {
   size_t step = 4096;
-  while (step * 16 < bytes) step *= 2;
+  while (step * 16 < bytes && bytes <= kKeep) step *= 2;
   return (bytes + step - 1) / step * step;
 }
 
-// Frees every kept block of a device (-1: of all devices); hipFree waits.
+// Frees the kept blocks of a device; hipFree waits.
 void release_kept(Pool &P, int device) {
-  for (auto &d : P.dev) {
-    if (device >= 0 && d.first != device) continue;
-    while (!d.second.blocks.empty()) (void)hipFree(d.second.take(d.second.blocks.begin()));
+  for (;;) {
+    void *p = nullptr;
+    {
+      std::lock_guard<std::mutex> lock(P.mu);
+      DevicePool &D = P.dev.at(device);
+      if (D.ages.empty()) return;
+      p = D.take(D.ages.begin()->second);
+    }
+    (void)hipFree(p);
   }
+}
+
+// A kept block that fits, nothing pending on it; null if there is none.
+void *take_kept(Pool &P, int dev, size_t size) {
+  void *p = nullptr;
+  uint64_t before = 0;
+  {
+    std::lock_guard<std::mutex> lock(P.mu);
+    DevicePool &D = P.dev[dev];
+    DevicePool::Place at;
+    if (!D.find(size, &at)) return nullptr;
+    P.live.emplace(at.it->second.p, Block{dev, at.it->first});  // may throw: before the block leaves the list
+    p = D.take(at);
+    if (!at.in_flight) return p;
+    before = D.next_age;
+  }
+  if (hipDeviceSynchronize() != hipSuccess) {  // a capture is under way, say: not this one
+    (void)hipGetLastError();
+    pool_free(p, kInFlight);
+    return nullptr;
+  }
+  std::lock_guard<std::mutex> lock(P.mu);
+  P.dev.at(dev).drained(before);
+  return p;
 }
 
 }  // namespace
@@ -95,26 +156,11 @@ hipError_t pool_alloc(void **out, size_t bytes) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
-  const size_t size = rounded(bytes ? bytes : 1);
+  if (!bytes) bytes = 1;
+  size_t size = rounded(bytes);
   Pool &P = pool();
   try {
-    std::lock_guard<std::mutex> lock(P.mu);
-    DevicePool &D = P.dev[dev];
-    auto it = D.blocks.lower_bound(size);
-    bool fits = it != D.blocks.end() && it->first <= size + size / 4;
-    if (fits && it->second.in_flight) {
-      if (hipDeviceSynchronize() == hipSuccess) {
-        for (auto &b : D.blocks) b.second.in_flight = false;
-      } else {
-        (void)hipGetLastError();
-        fits = false;
-      }
-    }
-    if (fits) {
-      P.live.emplace(it->second.p, Block{dev, it->first});  // may throw: before the block leaves the list
-      *out = D.take(it);
-      return hipSuccess;
-    }
+    if ((*out = take_kept(P, dev, size))) return hipSuccess;
     void *q = nullptr;
     e = hipMalloc(&q, size);
     if (e == hipErrorOutOfMemory) {
@@ -122,8 +168,13 @@ hipError_t pool_alloc(void **out, size_t bytes) {
       release_kept(P, dev);
       e = hipMalloc(&q, size);
     }
+    if (e == hipErrorOutOfMemory && size > bytes) {
+      (void)hipGetLastError();
+      e = hipMalloc(&q, size = bytes);
+    }
     if (e != hipSuccess) return e;
     try {
+      std::lock_guard<std::mutex> lock(P.mu);
       P.live.emplace(q, Block{dev, size});
     } catch (...) {
       (void)hipFree(q);
@@ -139,19 +190,30 @@ hipError_t pool_alloc(void **out, size_t bytes) {
 void pool_free(void *p, PoolState state) {
   if (!p) return;
   Pool &P = pool();
-  std::lock_guard<std::mutex> lock(P.mu);
-  auto it = P.live.find(p);
-  if (it == P.live.end()) return;
-  const Block b = it->second;
-  P.live.erase(it);
-  DevicePool &D = P.dev[b.device];
-  if (state != kUnknown && b.bytes <= kKeep) {
-    while (D.kept + b.bytes > kKeep) (void)hipFree(D.take(D.ages.begin()->second));
-    try {
-      D.add(b.bytes, p, state == kInFlight);
-      return;
-    } catch (const std::bad_alloc &) {
+  Block b;
+  {
+    std::lock_guard<std::mutex> lock(P.mu);
+    auto it = P.live.find(p);
+    if (it == P.live.end()) return;
+    b = it->second;
+    P.live.erase(it);
+  }
+  while (state != kUnknown && b.bytes <= kKeep) {
+    void *oldest = nullptr;
+    {
+      std::lock_guard<std::mutex> lock(P.mu);
+      DevicePool &D = P.dev.at(b.device);
+      if (D.kept + b.bytes <= kKeep) {
+        try {
+          D.add(b.bytes, p, state == kInFlight);
+          return;
+        } catch (const std::bad_alloc &) {
+          break;
+        }
+      }
+      oldest = D.take(D.ages.begin()->second);
     }
+    (void)hipFree(oldest);
   }
   (void)hipFree(p);
 }
@@ -160,6 +222,13 @@ void pool_free(void *p, PoolState state) {
 
 extern "C" void sd_release_memory(void) {
   sd::Pool &P = sd::pool();
-  std::lock_guard<std::mutex> lock(P.mu);
-  sd::release_kept(P, -1);
+  for (int device = -1;;) {
+    {
+      std::lock_guard<std::mutex> lock(P.mu);
+      auto next = P.dev.upper_bound(device);
+      if (next == P.dev.end()) return;
+      device = next->first;
+    }
+    sd::release_kept(P, device);
+  }
 }
