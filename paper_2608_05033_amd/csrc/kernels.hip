@@ -231,6 +231,7 @@ __device__ __forceinline__ void gather_rows(const int32_t *__restrict__ colidx, 
           if (t0 + u < cnt) acc += av[u] * bv[u];
       }
     }
+      if (cnt < G) break;  // the next p could pass 2^31
   } else {
     for (int32_t p = p0; p < p1; ++p) {
       if (p != p0) {
@@ -516,20 +517,21 @@ __device__ __forceinline__ typename VecOf<VW>::T slice_sum(const int32_t *__rest
                                                            int s, const float *__restrict__ Bl, int32_t n) {
   using V = typename VecOf<VW>::T;
   V acc = (V)(0.0f);
-  int32_t p = p0 + s;
-  if (p >= p1) return acc;
+  int32_t left = p1 - p0 - s;  // from p on; p itself may pass 2^31 behind the last round
+  uint32_t p = (uint32_t)p0 + s;
+  if (left <= 0) return acc;
   int32_t c[UNR];
   float v[UNR];
-  auto fetch = [&](int32_t q0) {
+  auto fetch = [&]() {
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
-      const int32_t q = min(q0 + u * S, p1 - 1);
+      const int32_t q = (int32_t)(p + min(u * S, left - 1));
       c[u] = colidx[q];
       v[u] = vals[q];
     }
   };
-  fetch(p);
-  for (; p < p1; p += S * UNR) {
+  fetch();
+  while (left > 0) {
     V b[UNR];
     float a[UNR];
 #pragma unroll
@@ -537,10 +539,13 @@ __device__ __forceinline__ typename VecOf<VW>::T slice_sum(const int32_t *__rest
       b[u] = load_v<VW>(Bl + (int64_t)c[u] * n);
       a[u] = v[u];
     }
-    fetch(p + S * UNR);
+    const int32_t here = left;
+    p += S * UNR;
+    left -= S * UNR;
+    fetch();
 #pragma unroll
     for (int u = 0; u < UNR; ++u)
-      if (p + u * S < p1) acc += a[u] * b[u];
+      if (u * S < here) acc += a[u] * b[u];
   }
   return acc;
 }
@@ -1224,6 +1229,7 @@ __global__ __launch_bounds__(256) void k_win_split(
           if (u0 + u < cnt) acc += av[u] * bv[u];
       }
     }
+      if (cnt < G) break;  // as in gather_rows
     if (row_ok && col_ok) store_cols<VW, ODD, true>(C + (int64_t)crow * n, col, n, acc);
   }
 }

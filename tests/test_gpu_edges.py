@@ -339,6 +339,32 @@ def test_split_stores_of_small_and_large_outputs(n):
     lens[::3001] = 900
     A = gen.random_rows(m, k, lens.astype(np.int32), seed=n)
     B = gen.dense_uniform(k, n, seed=n)
+@pytest.mark.parametrize("force,opts", [("csr_row", {}), ("csr_split", {}), ("csr_split", {"heavy_threshold": 4000})])
+def test_products_of_the_most_entries(force, opts):
+    """2^31 - 1 entries: the lanes' steps past the last row's (or chunk's) end pass the
+    largest int32.  Every row holds columns 0 .. 2,047, the last one all but column
+    2,047, so C's rows are sums of B's (error below 2,048 rounding steps of the sum of
+    magnitudes)."""
+    k, m = 2048, 2 ** 20
+    nnz = m * k - 1
+    cols = torch.arange(k, dtype=torch.int32, device="cuda").repeat(m)[:nnz]
+    vals = torch.ones(nnz, device="cuda")
+    rp = (torch.arange(m + 1, dtype=torch.int64) * k).clamp_(max=nnz).int().cuda()
+    for n in (1, 3, 16, 64, 200):
+        print(f"case 2^31 - 1 entries {force} {opts} n={n}", flush=True)
+        B = torch.rand(k, n, device="cuda")
+        C = torch.full((m, n), float("nan"), device="cuda")
+        with sd.sd_plan_device(rp, cols, vals, m, k, nnz, n, force=force, **opts) as plan:
+            sd.sd_spmm(plan, B, C)
+            torch.cuda.synchronize()
+        want, last = B.double().sum(0), B[:-1].double().sum(0)
+        tol = k * 2.0 ** -24
+        assert bool(((C[:-1] - want).abs() <= tol * want).all())
+        assert bool(((C[-1] - last).abs() <= tol * last).all())
+        del B, C
+    sd.sd_release_memory()
+
+
     C64, S = oracle.spmm(A, B)
     print(f"case split stores n={n}", flush=True)
     with sd.sd_plan_ex(A, n, force="csr_split") as plan:
