@@ -147,40 +147,66 @@ def test_mfma_column_tiles(fam, mb, n):
         assert_close(run(sd, plan, B, A.m), C64, S, f"tiles/{fam}/{mb}/{n}")
 
 
-@pytest.mark.parametrize("shape", ["band", "short", "empty"])
-@pytest.mark.parametrize("n", [33, 64, 96, 130, 256, 300])
+@pytest.mark.parametrize("shape,n", [("band", n) for n in (33, 64, 96, 130, 256, 300)] +
+                         [(shape, n) for shape in ("short", "empty") for n in (80, 96, 125, 256)])
 def test_streamed_rows(shape, n):
     """Rows taken by lane groups as they become free: a narrow band (rows of
     several tiles, empty rows, a last workgroup that is not full), short rows on
-    any columns, and nearly all rows empty; with 32-bit lanes as well."""
+    any columns, and mostly empty rows; B and C on a 16-byte boundary and off it."""
     rng = np.random.default_rng(n)
-    m = 66003
+    m = k = 66003
     if shape == "band":
         lens = rng.integers(0, 30, m)
         lens[::501] = 150
         lens[1000:1400] = 0
         lens[-1] = 70
         base = np.clip(np.arange(m) - 200, 0, m - 400)
+        width = 400
     else:
-        lens = rng.integers(0, 6, m) if shape == "short" else (rng.random(m) < 0.01).astype(int)
-        base = np.zeros(m, np.int64)
-    width = 400 if shape == "band" else m
+        m, k = 132003, 30000  # workgroups enough, an upper quartile above 4 entries
+        lens = rng.integers(2, 9, m) if shape == "short" else rng.integers(5, 9, m)
+        if shape == "empty":
+            lens[rng.random(m) < 0.5] = 0
+            lens[20000:40000] = 0
+        lens[::7001] = 90
+        base, width = np.zeros(m, np.int64), k
     rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     rows = np.repeat(np.arange(m), lens)
     j = np.arange(rowptr[-1]) - rowptr[rows]
     L = lens[rows]
     lo, hi = j * width // L, (j + 1) * width // L
     col = (base[rows] + lo + rng.integers(0, 1 << 30, rows.size) % np.maximum(1, hi - lo)).astype(np.int32)
-    A = gen.CSR(m, m, rowptr, col, rng.uniform(-1, 1, col.size).astype(np.float32))
-    B = gen.dense_uniform(m, n, seed=n)
+    A = gen.CSR(m, k, rowptr, col, rng.uniform(-1, 1, col.size).astype(np.float32))
+    B = gen.dense_uniform(k, n, seed=n)
     C64, S = oracle.spmm(A, B)
     print(f"case streamed rows {shape} n={n}", flush=True)
     with sd.sd_plan_ex(A, n, force="csr_row") as plan, sd.sd_plan_ex(A, n, force="csr_row", wg_order=2) as other:
+        assert plan.info["stream_rows"] > 0 and other.info["stream_rows"] == 0
         out = run(sd, plan, B, m)
         assert_close(out, C64, S, f"streamed {shape} n={n}")
         # a row is summed in the same order either way
         assert np.array_equal(out.view(np.uint32), run(sd, other, B, m).view(np.uint32))
         assert_close(run(sd, plan, B, m, misalign=True), C64, S, f"streamed misaligned {shape} n={n}")
+
+
+@pytest.mark.parametrize("n", [132, 190])
+def test_streamed_light_rows(n):
+    """The split's light rows streamed by whole waves: 16,000 workgroups and a few, the
+    last one not full, beside chunks of heavy rows."""
+    m, k = 16 * 16003 + 5, 4000
+    lens = np.random.default_rng(n).integers(0, 8, m)
+    lens[::9001] = 1500
+    A = gen.random_rows(m, k, lens.astype(np.int32), seed=n)
+    B = gen.dense_uniform(k, n, seed=n)
+    C64, S = oracle.spmm(A, B)
+    print(f"case streamed light rows n={n}", flush=True)
+    kw = dict(force="csr_split", heavy_threshold=500, chunk_nnz=256, col_tile=256)
+    with sd.sd_plan_ex(A, n, **kw) as plan, sd.sd_plan_ex(A, n, rows_per_group=1, **kw) as other:
+        assert plan.info["stream_rows"] == 4 and other.info["stream_rows"] == 0
+        assert plan.info["n_light"] % 16 != 0 and plan.info["n_heavy"] > 20
+        out = run(sd, plan, B, m)
+        assert_close(out, C64, S, f"streamed light rows n={n}")
+        assert np.array_equal(out.view(np.uint32), run(sd, other, B, m).view(np.uint32))
 
 
 ODD_FAMILIES = [("csr_row", {}), ("csr_row", {"row_slices": 1}), ("csr_split", {"heavy_threshold": 40, "chunk_nnz": 17}),
@@ -313,32 +339,6 @@ def test_analysis_of_the_most_entries():
     assert e.value.status == sd.SD_ERR_INVALID_CSR
 
 
-def test_merge_path_of_the_most_rows():
-    """2^31 - 1 rows, nearly all empty: the last piece's tile of row ends passes the
-    largest row number."""
-    m, n = 2 ** 31 - 1, 1
-    rp = torch.full((m + 1,), 2, dtype=torch.int32, device="cuda")
-    rp[0], rp[1:6], rp[m] = 0, 1, 3  # one entry in rows 0, 5 and m - 1
-    cols = torch.tensor([1, 0, 2], dtype=torch.int32, device="cuda")
-    vals = torch.tensor([2.0, 3.0, 5.0], device="cuda")
-    B = torch.tensor([[7.0], [11.0], [13.0]], device="cuda")
-    C = torch.full((m, n), -7.0, device="cuda")
-    print("case merge path of 2^31 - 1 rows", flush=True)
-    sd.sd_spmm_merge_noalloc(rp, cols, vals, m, 3, 3, n, B, C)
-    torch.cuda.synchronize()
-    assert [float(C[r, 0]) for r in (0, 5, m - 1)] == [22.0, 21.0, 65.0]
-    assert int(torch.count_nonzero(C)) == 3
-
-
-@pytest.mark.parametrize("n", [1, 7, 8, 9, 12, 31])
-def test_split_stores_of_small_and_large_outputs(n):
-    """Light rows of the narrow split below and above the size of C from which they
-    are stored past L2 (2 MiB), whole widths and odd ones."""
-    m, k = 60013, 4000
-    lens = np.random.default_rng(n).integers(0, 9, m)
-    lens[::3001] = 900
-    A = gen.random_rows(m, k, lens.astype(np.int32), seed=n)
-    B = gen.dense_uniform(k, n, seed=n)
 @pytest.mark.parametrize("force,opts", [("csr_row", {}), ("csr_split", {}), ("csr_split", {"heavy_threshold": 4000})])
 def test_products_of_the_most_entries(force, opts):
     """2^31 - 1 entries: the lanes' steps past the last row's (or chunk's) end pass the
@@ -365,6 +365,32 @@ def test_products_of_the_most_entries(force, opts):
     sd.sd_release_memory()
 
 
+def test_merge_path_of_the_most_rows():
+    """2^31 - 1 rows, nearly all empty: the last piece's tile of row ends passes the
+    largest row number."""
+    m, n = 2 ** 31 - 1, 1
+    rp = torch.full((m + 1,), 2, dtype=torch.int32, device="cuda")
+    rp[0], rp[1:6], rp[m] = 0, 1, 3  # one entry in rows 0, 5 and m - 1
+    cols = torch.tensor([1, 0, 2], dtype=torch.int32, device="cuda")
+    vals = torch.tensor([2.0, 3.0, 5.0], device="cuda")
+    B = torch.tensor([[7.0], [11.0], [13.0]], device="cuda")
+    C = torch.full((m, n), -7.0, device="cuda")
+    print("case merge path of 2^31 - 1 rows", flush=True)
+    sd.sd_spmm_merge_noalloc(rp, cols, vals, m, 3, 3, n, B, C)
+    torch.cuda.synchronize()
+    assert [float(C[r, 0]) for r in (0, 5, m - 1)] == [22.0, 21.0, 65.0]
+    assert int(torch.count_nonzero(C)) == 3
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 12, 31])
+def test_split_stores_of_small_and_large_outputs(n):
+    """Light rows of the narrow split below and above the size of C from which they
+    are stored past L2 (2 MiB), whole widths and odd ones."""
+    m, k = 60013, 4000
+    lens = np.random.default_rng(n).integers(0, 9, m)
+    lens[::3001] = 900
+    A = gen.random_rows(m, k, lens.astype(np.int32), seed=n)
+    B = gen.dense_uniform(k, n, seed=n)
     C64, S = oracle.spmm(A, B)
     print(f"case split stores n={n}", flush=True)
     with sd.sd_plan_ex(A, n, force="csr_split") as plan:
