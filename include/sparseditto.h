@@ -144,8 +144,8 @@ int sd_analyze_device(const sd_csr_t *A, int32_t dense_threshold, sd_stats_t *ou
  * template set (Sec. "Energy-Based Model for Optimization Templates"), plus
  * the padded-row, packed-window and sliced layouts of the design space
  * (Appendix "Compilation-Plan Design Space", SpMM and SpMV rows):
- *   CSR_ROW    CSR; a lane group per row covers the dense width with 128-bit
- *              loads of B rows; one write of each C row.
+ *   CSR_ROW    CSR; a lane group per row covers the dense width, mostly with
+ *              128-bit loads of B rows; one write of each C row.
  *   CSR_SPLIT  CSR; rows with r_i >= heavy_threshold are cut into chunks of at
  *              most chunk_nnz nonzeros (Appendix "Case Studies", SpMM web
  *              graph).  Chunk partials go to a workspace and a fix-up kernel
@@ -233,7 +233,8 @@ typedef struct {
   int32_t col_tile;        /* CSR and ELL families: dense columns per lane group (the K-tile
                               width of the paper's SpMM hardware mapping), a power of two
                               >= 4; the dense width is processed in ceil(n / col_tile)
-                              column passes (0 = the whole width, up to 256) */
+                              column passes (0 = planner default: the whole width, or
+                              passes of 64 or 128 columns) */
   int32_t window_rows;     /* WIN: light rows per window R, >= 1 (0 = 64); a window
                               stages at most the columns whose B rows fit 16 KiB of
                               LDS, its most used */
@@ -247,9 +248,9 @@ typedef struct {
                               the adjacent ones) */
   int32_t wg_chunk;        /* wg_order 3: workgroups per chunk, >= 2 (0 = 64) */
   int32_t sell_sigma;      /* SELL: sort window in rows, >= 1 (0 = 8 slices) */
-  int32_t row_slices;      /* CSR_ROW / CSR_SPLIT at narrow widths (lanes per row G <= 8,
-                              i.e. n <= 32 with 128-bit accesses): lane groups that share
-                              one row (or chunk), each taking every row_slices-th nonzero,
+  int32_t row_slices;      /* CSR_ROW / CSR_SPLIT at narrow widths (n <= 32; lanes per row
+                              G <= 8): lane groups that share one row (or chunk), each
+                              taking every row_slices-th nonzero,
                               their partial sums added across lanes in a fixed order.
                               A power of two with G * row_slices <= 64; 1 = one lane group
                               per row (0 = planner default) */
@@ -302,10 +303,11 @@ int sd_plan_device(const sd_csr_t *A, int32_t n, const sd_plan_opts_t *opts, voi
  * a transpose plan).  C: device, rows_C x n row-major (rows_C = m, or k), fully
  * overwritten (no accumulation).  B and C must not overlap (checked:
  * SD_ERR_INVALID_VALUE).  B and C need the
- * 4-byte alignment of their elements and no more; from n = 4 on they are used
- * with 128-bit accesses whatever n and the pointers.  No allocation, no host synchronisation, no memset:
- * the call may be captured into a HIP graph and replayed (the plan's
- * workspace is fixed at plan time; replays on one plan must not overlap).
+ * 4-byte alignment of their elements and no more: the plan's accesses (128-bit ones
+ * at n = 4, 8, 12 ...; at other widths the planner chooses) are the same whatever the
+ * pointers.  No allocation, no host synchronisation, no memset: the call may be
+ * captured into a HIP graph and replayed (the plan's workspace is fixed at plan
+ * time; replays on one plan must not overlap).
  * Errors: SD_ERR_INVALID_VALUE (null plan/pointers, overlapping B and C), SD_ERR_NO_DEVICE,
  * SD_ERR_HIP (launch failure; the stream's state is whatever HIP reports). */
 int sd_spmm(sd_plan_t plan, const float *B, float *C, void *stream);

@@ -9,12 +9,13 @@
 //
 //  * A lane group of G lanes owns one sparse row (or chunk, or merge-path
 //    piece) and covers G*VW output columns, VW = 4 giving one 128-bit load of
-//    a B row per lane per nonzero.  64/G rows share a wave.  Widths that are no
-//    multiple of 4 and pointers off 16 bytes use the same loads (they need 4-byte
-//    alignment only); the last lane takes the row's last 4 columns and stores
-//    those its neighbour does not.  One column per lane, as those cases ran
-//    before, issues four times the loads: 7-point Laplacian 60^3, N = 33: 77 us
-//    against 25; R-MAT 200 k vertices, 3 M edges, N = 101: 279 against 129.
+//    a B row per lane per nonzero.  64/G rows share a wave.  Pointers off 16 bytes
+//    use the same loads (they need 4-byte alignment only), and so do widths that
+//    are no multiple of 4: the last lane takes the row's last 4 columns and stores
+//    those its neighbour does not.  One column per lane (VW = 1) issues four times
+//    the loads (7-point Laplacian 60^3, N = 33: 77 us against 25; R-MAT 200 k
+//    vertices, 3 M edges, N = 101: 279 against 129) and is the faster one, at such
+//    widths, where waves are few or rows long or far; the planner tells them apart.
 //  * The group loads G (column, value) pairs of its nonzero stream with one
 //    coalesced load per lane, then broadcasts them inside the group with
 //    ds_bpermute; up to 8 B-row loads are issued back to back
@@ -230,8 +231,8 @@ __device__ __forceinline__ void gather_rows(const int32_t *__restrict__ colidx, 
         for (int u = 0; u < UNR; ++u)
           if (t0 + u < cnt) acc += av[u] * bv[u];
       }
-    }
       if (cnt < G) break;  // the next p could pass 2^31
+    }
   } else {
     for (int32_t p = p0; p < p1; ++p) {
       if (p != p0) {
@@ -1228,15 +1229,15 @@ __global__ __launch_bounds__(256) void k_win_split(
         for (int u = 0; u < UNR; ++u)
           if (u0 + u < cnt) acc += av[u] * bv[u];
       }
-    }
       if (cnt < G) break;  // as in gather_rows
+    }
     if (row_ok && col_ok) store_cols<VW, ODD, true>(C + (int64_t)crow * n, col, n, acc);
   }
 }
 
 // ------------------------------------------------------------- BSR / MFMA ---
-// One wave per (block-row, 16 NT NQ output columns), NT n-tiles of 16 columns
-// (4 for widths that are multiples of 64, 2 or 1 for multiples of 32 or 16).
+// One wave per (block-row, 16 NT NQ output columns), NT n-tiles of 16 columns;
+// the width's last tile may be partial (RAG), mfma_shape chooses NT and NQ.
 // For v_mfma_f32_16x16x4_f32 lane l supplies A[l%16][kk] and B[kk][l%16] for
 // kk = l/16 and receives D[4(l/16)+v][l%16], v = 0..3.  The sum over the
 // block's 16 columns is split into 4 MFMA k-steps s, lane group g = l/16
@@ -1292,8 +1293,8 @@ __device__ __forceinline__ void bsr_mfma_blocks(int64_t first, int64_t cnt, int6
         // compiler wait for the load at the join): the select is on the
         // address.  A row past K (last block-column) or a Blocked-ELL padding
         // block reads the zero row instead; its A values are the zero fill,
-        // so it adds exactly zero.  The column is always in range: the MFMA
-        // path needs n % (16 NT NQ) == 0 (RAG clamps to the last NT columns).
+        // so it adds exactly zero.  The column is always in range: without RAG
+        // n % (16 NT NQ) == 0, with it the last NT columns are the last read.
         const bool ok = valid && krow < k;
         const float *__restrict__ src = ok ? B + (int64_t)krow * n : zrow;
         const int32_t col = col0 + qq * 16 * NT + NT * c;
@@ -1481,8 +1482,7 @@ inline uint32_t blocks_for(int64_t units, int G, int J = 1) {
 
 // Rows per lane group J in {1, 2, 4} and B-row gathers per row per round
 // UNR in {4, 8} (at most G); J * UNR <= 16 keeps the in-flight B data within
-// 64 VGPRs at VW = 4.  J = 0: the streaming kernels (G >= 8; wider lane groups
-// than planned, for a misaligned B or C, stream as well).
+// 64 VGPRs at VW = 4.  J = 0: the streaming kernels (G >= 8).
 template <int G, typename F>
 hipError_t with_row_batch(int J, int UNR, F &&f) {
   if constexpr (G >= 8) {
@@ -1506,9 +1506,8 @@ hipError_t with_row_batch(int J, int UNR, F &&f) {
 // Slices per row S for lane groups of G <= 8 lanes: a power of two with
 // G * S <= 64.  UNR = 4 nonzeros per slice per round.
 constexpr int kSliceUnroll = kSliceRound;
-// The plan's slice count for the lane groups of this launch: a misaligned B
-// or C switches a 128-bit geometry to 32-bit lanes (four times the lanes per
-// row), so the count is halved until G * S <= 64 (none above G = 8).
+// The plan's slice count; a saved one that does not fit the lane groups (saved where
+// a row took fewer lanes) is halved until G * S <= 64 (none above G = 8).
 inline int32_t fit_slices(int32_t S, int32_t G) {
   if (G > 8) return 1;
   while (S > 1 && G * S > 64) S /= 2;

@@ -126,8 +126,7 @@ int device_transpose(const sd_csr_t *A, hipStream_t s, DeviceTranspose *T) {
 // device, stream ds); statistics come from the device analysis and the CSR,
 // heavy-split, merge-path and ELL representations are built on the device.
 // Packed column windows: the most staged columns one window may keep, those
-// whose B rows (one tile of the dense width in the 128-bit geometry, never
-// narrower than the 32-bit one used for unaligned B or C) fit the LDS budget.
+// whose B rows (one tile of the dense width) fit the LDS budget.
 int32_t window_cap(int32_t n, int32_t vec4, int32_t col_tile, int32_t max_lds) {
   const int64_t row_bytes = std::max<int64_t>(1, (int64_t)sd::window_lds_bytes(n, vec4, col_tile, 1));
   const int64_t budget = std::min<int64_t>(sd::kWindowLdsBudget, max_lds);
@@ -330,9 +329,7 @@ int build_plan(const sd_csr_t *A_in, int32_t n, const sd_plan_opts_t &o, sd_plan
       I.n_light = (int64_t)p->h_light.size();
       I.n_heavy = (int64_t)p->h_heavy_rows.size();
       I.n_chunks = (int64_t)p->h_chunks.size() / 3;
-      // LDS per staged column: one tile of the dense width (the 128-bit geometry,
-      // which is never narrower than the 32-bit one used for unaligned B or C);
-      // a window keeps at most the columns that fit the budget, its most used
+      // a window keeps at most the columns whose B rows fit the budget, its most used
       const int32_t cap = window_cap(n, vec4, col_tile, I.max_lds_bytes);
       const int32_t R = o.window_rows > 0 ? o.window_rows : sd::kDefaultWindowRows;
       int32_t wmax = 0;

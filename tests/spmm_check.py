@@ -9,7 +9,7 @@ TOL = 1e-5  # |C_gpu - C64| <= TOL * (1 + S) per element, S = |A|.|B|
 
 def device_buffers(B: np.ndarray, rows_out: int, misalign: bool = False):
     """Copy B to the device and allocate C.  With misalign=True both start 4
-    bytes past a 16-byte boundary, which forces the 32-bit access path."""
+    bytes past a 16-byte boundary; the same kernels run on them."""
     import torch
 
     k, n = B.shape

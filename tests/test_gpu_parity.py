@@ -81,8 +81,8 @@ def test_family_parity(mname, fam, opts, n):
 @pytest.mark.parametrize("fam", ["bsr", "bell"])
 @pytest.mark.parametrize("n", [1, 3, 8, 13, 16, 24, 32, 40, 48, 64, 80, 96, 100, 128, 160, 192, 200, 256])
 def test_block_mfma_parity(mname, fam, n):
-    """MFMA column tiles of 64, 32 and 16 (partial last tile) and, for a
-    misaligned B and C, 16-column tiles of single floats."""
+    """MFMA column tiles of 64, 32 and 16 (partial last tile), of single floats below
+    4 columns; B and C on a 16-byte boundary and off it."""
     A = matrix(mname)
     B = gen.dense_uniform(A.k, n, seed=7)
     print(f"case mfma {mname} {fam} n={n}", flush=True)
@@ -134,7 +134,7 @@ def test_block_nonfinite_unused_b_rows(fam, engine, n):
 @pytest.mark.parametrize("n", [4, 64, 128, 320, 1000])
 def test_wide_and_misaligned(fam, n):
     """n above one column tile (320 needs two tiles of 256), and buffers 4 bytes
-    off a 16-byte boundary (32-bit access path)."""
+    off a 16-byte boundary."""
     A = matrix("ragged")
     B = gen.dense_uniform(A.k, n, seed=11)
     C64, S = oracle.spmm(A, B)
@@ -179,8 +179,9 @@ def test_empty_output_dimensions():
         assert torch.all(C == 0)
 
 
-def _lanes(n, vec4):
-    lanes = -(-n // 4) if vec4 else n
+def _lanes(n):
+    """Lanes per row of whole widths and of n < 4."""
+    lanes = -(-n // 4) if n % 4 == 0 else n
     g = 1
     while g < lanes and g < 64:
         g *= 2
@@ -197,7 +198,7 @@ SLICE_OPTS = [("csr_row", {}), ("csr_split", {"heavy_threshold": 40, "chunk_nnz"
 @pytest.mark.parametrize("S", [2, 4, 8, 16, 32, 64])
 def test_row_slices_parity(mname, fam, opts, n, S):
     """Rows shared by S lane groups (narrow widths) against the oracle."""
-    G = _lanes(n, n % 4 == 0)
+    G = _lanes(n)
     if G > 8 or G * S > 64:
         pytest.skip("no sliced geometry for this width")
     A = matrix(mname)
@@ -206,7 +207,6 @@ def test_row_slices_parity(mname, fam, opts, n, S):
     with sd.sd_plan_ex(A, n, force=fam, row_slices=S, **opts) as plan:
         assert plan.info["row_slices"] == S
         C = run(sd, plan, B, A.m)
-        # a misaligned B switches to 32-bit lanes: the launch fits S to the wider group
         Cm = run(sd, plan, B, A.m, misalign=True)
     C64, S_ = oracle.spmm(A, B)
     assert_close(C, C64, S_, f"slices {mname} {fam} n={n} S={S}")

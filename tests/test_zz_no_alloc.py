@@ -95,8 +95,8 @@ def test_noalloc_rejects_without_launching():
 
 
 def test_noalloc_misaligned_operands():
-    """B and C one float past a 16-byte boundary: both paths take the 32-bit
-    lane geometry, and give the same bits as each other."""
+    """B and C one float past a 16-byte boundary: a plan and the call without one
+    give the same bits."""
     A = gen.random_rows(700, 900, ragged(700, 900, 4), seed=4)
     rp, ci, vv = device_csr(A)
     stream = torch.cuda.current_stream()
