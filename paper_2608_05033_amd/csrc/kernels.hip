@@ -1506,14 +1506,6 @@ hipError_t with_row_batch(int J, int UNR, F &&f) {
 // Slices per row S for lane groups of G <= 8 lanes: a power of two with
 // G * S <= 64.  UNR = 4 nonzeros per slice per round.
 constexpr int kSliceUnroll = kSliceRound;
-// The plan's slice count; a saved one that does not fit the lane groups (saved where
-// a row took fewer lanes) is halved until G * S <= 64 (none above G = 8).
-inline int32_t fit_slices(int32_t S, int32_t G) {
-  if (G > 8) return 1;
-  while (S > 1 && G * S > 64) S /= 2;
-  return S;
-}
-
 template <int G, typename F>
 hipError_t with_slices(int S, F &&f) {
   if constexpr (G <= 8) {
@@ -1576,8 +1568,8 @@ hipError_t launch_csr_rows(const CsrOperand &A, const DenseIO &io, int32_t rows_
   return with_geometry(geo, [&](auto gg) -> hipError_t {
     constexpr int G = decltype(gg)::G, VW = decltype(gg)::VW;
     constexpr bool ODD = decltype(gg)::ODD;
-    if (const int32_t S1 = fit_slices(slices, G); S1 > 1) {
-      return with_slices<G>(S1, [&](auto ss) -> hipError_t {
+    if (slices > 1) {
+      return with_slices<G>(slices, [&](auto ss) -> hipError_t {
         constexpr int S = decltype(ss)::value;
         const uint32_t nb = blocks_for(A.m, G * S);
         if (nb == 0) return hipSuccess;
@@ -1607,8 +1599,7 @@ hipError_t launch_csr_split(const CsrOperand &A, const int32_t *light, int32_t n
     constexpr int G = decltype(gg)::G, VW = decltype(gg)::VW;
     constexpr bool ODD = decltype(gg)::ODD;
     // narrow widths (G <= 8) take the sliced kernel, whose chunks get a whole wave
-    const int32_t S1 = fit_slices(std::max(1, slices), G);
-    hipError_t e = G <= 8 ? with_slices<G>(S1, [&](auto ss) -> hipError_t {
+    hipError_t e = G <= 8 ? with_slices<G>(std::max(1, slices), [&](auto ss) -> hipError_t {
       constexpr int S = decltype(ss)::value;
       const uint32_t cb = blocks_for(nchunks, 64), lb = blocks_for(nlight, G * S);
       if (cb + lb == 0) return hipSuccess;
@@ -1847,11 +1838,11 @@ hipError_t kernel_attributes(int32_t family, int32_t engine, int32_t n, int32_t 
                              int32_t unroll, int32_t slices, int32_t stream, int32_t col_tile, int32_t width,
                              int32_t block_rows, hipFuncAttributes *attr) {
   const int32_t G0 = geometry_for(n, vec4, col_tile).G;
-  if ((family == 1 && fit_slices(slices, G0) > 1) || (family == 2 && G0 <= 8)) {
+  if ((family == 1 && slices > 1) || (family == 2 && G0 <= 8)) {
     return with_geometry(geometry_for(n, vec4, col_tile), [&](auto gg) -> hipError_t {
       constexpr int G = decltype(gg)::G, VW = decltype(gg)::VW;
       constexpr bool ODD = decltype(gg)::ODD;
-      return with_slices<G>(fit_slices(std::max(1, slices), G), [&](auto ss) -> hipError_t {
+      return with_slices<G>(std::max(1, slices), [&](auto ss) -> hipError_t {
         constexpr int S = decltype(ss)::value;
         const void *fn = family == 2 ? (const void *)&k_split_slices<G, VW, ODD, S, kSliceUnroll>
                                      : (const void *)&k_csr_slices<G, VW, ODD, S, kSliceUnroll>;
