@@ -98,13 +98,16 @@ static void devices_apart() {
   CHECK(apart);
 }
 
-// An idle block that fits is taken before one that has to be waited for.
+// An idle block is taken before one of its size that has to be waited for; a larger idle
+// one is kept for requests of its own size.
 static void idle_first() {
-  void *busy = take(MiB), *idle = take(MiB + MiB / 8);
+  void *busy = take(MiB), *idle = take(MiB - 100), *large = take(MiB + MiB / 8);
   sd::pool_free(busy, sd::kInFlight);
   sd::pool_free(idle, sd::kIdle);
-  CHECK(take(MiB) == idle && syncs == 0);
-  CHECK(take(MiB) == busy && syncs == 1);  // nothing else is left
+  sd::pool_free(large, sd::kIdle);
+  CHECK(take(MiB - 10) == idle && syncs == 0);
+  CHECK(take(MiB) == busy && syncs == 1);  // nothing else of its size is left
+  CHECK(take(MiB) == large && syncs == 1 && mallocs == 3);
   // blocks given back while a synchronisation runs are not covered by it
   sd::pool_free(busy, sd::kInFlight);
   hold_sync = true;
